@@ -119,16 +119,14 @@ template <int NT> __device__ __forceinline__ int block_exclusive_scan(int x, int
     return off + inc - x;
 }
 
-// fp32 vector of VEC elements with the alignment of its size.
+// fp32 vector of VEC (1 or 4) elements, 4-byte aligned: one load or store.
 template <int VEC> struct Vec;
 template <> struct Vec<1> {
     float v[1];
 };
-template <> struct alignas(8) Vec<2> {
-    float v[2];
-};
-template <> struct alignas(16) Vec<4> {
-    float v[4];
+template <> struct Vec<4> {
+    typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+    f4 v;
 };
 
 template <int VEC>
@@ -148,8 +146,10 @@ __device__ __forceinline__ void st_vec(float *p, const Vec<VEC> &v)
 template <int VEC>
 __device__ __forceinline__ void st_vec_stream(float *p, const Vec<VEC> &v)
 {
-#pragma unroll
-    for (int i = 0; i < VEC; i++) __builtin_nontemporal_store(v.v[i], p + i);
+    if constexpr (VEC == 4)
+        __builtin_nontemporal_store(v.v, reinterpret_cast<typename Vec<4>::f4 *>(p));
+    else
+        __builtin_nontemporal_store(v.v[0], p);
 }
 
 template <class T>

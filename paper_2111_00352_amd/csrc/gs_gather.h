@@ -2,64 +2,234 @@
 // holds a batch of (column, value) pairs, one per lane, and gathers the
 // corresponding X rows B at a time, each lane loading NQ float4 at columns
 // c0 + 4*G*q (so one load instruction reads G*16 contiguous bytes of a row).
+// Any width of at least 4 columns and any 4-byte aligned operands are taken
+// this way: quads need no 16-byte alignment, and a width that is no multiple
+// of 4 ends in a quad that overlaps the one before it.
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
+#include <utility>
 
 namespace gs {
-
-// Gathered X rows: plain cached loads (non-temporal loads for every row
-// measured slower: hub rows are reused from L2 and the MALL).
-__device__ __forceinline__ float4 load_x4(const float *p)
-{
-    return *reinterpret_cast<const float4 *>(p);
-}
-
-// Non-temporal gather of a row that few entries reference: its lines are
-// inserted for early eviction, so they do not push the rows of often
-// referenced columns out of L2.
-__device__ __forceinline__ float4 load_x4_nt(const float *p)
-{
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    const f4 v = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(p));
-    return make_float4(v.x, v.y, v.z, v.w);
-}
 
 // Column words with a reference class: bits 27..30 hold the class of the
 // column (bit length of its entry count, at most 15), bits 0..26 the column.
 constexpr int kColClassShift = 27;
 constexpr int kColMask = (1 << kColClassShift) - 1;
 
+// Four floats at any 4-byte aligned address: one 16-byte load or store (the
+// memory pipeline needs dword alignment only; an access that straddles a
+// 128-byte line costs that line's second request).
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double d4 __attribute__((ext_vector_type(4), aligned(8)));
+
+// Accumulator quads: fp32, or fp64 where the products are summed exactly.
+template <class A> struct Quad;
+template <> struct Quad<float> {
+    typedef f4u type;
+};
+template <> struct Quad<double> {
+    typedef d4 type;
+};
+
+// Lane t's value of entry J of the group's batch (J a compile-time lane).
+// Groups of 16 lanes and more hold the same batch of 16 entries in every DPP
+// row of 16 lanes, so one row_newbcast serves them; smaller groups hold a
+// batch of G entries.  No LDS round trip, unlike a shuffle.
+template <int J, int G> __device__ __forceinline__ int bcast_entry(int v)
+{
+    if constexpr (G == 4) {
+        return __builtin_amdgcn_update_dpp(0, v, J * 0x55, 0xf, 0xf, true);  // quad_perm: lane J of each quad
+    } else if constexpr (G == 8) {
+        const int lo = __builtin_amdgcn_update_dpp(0, v, 0x150 + J, 0xf, 0xf, true);
+        return __builtin_amdgcn_update_dpp(lo, v, 0x150 + 8 + J, 0xf, 0xc, true);  // banks 2, 3: the upper group
+    } else {
+        return __builtin_amdgcn_update_dpp(0, v, 0x150 + J, 0xf, 0xf, true);  // row_newbcast:J
+    }
+}
+
+// Entries per batch of a group of G lanes.
+template <int G> constexpr int kEntryBatch = G < 16 ? G : 16;
+
+// Column quads of a lane: quad q starts at column c0 + 4 G q, the last one
+// of a width that is no multiple of 4 moved back to end at column F (the
+// lanes that overlap then compute and store the same sums twice), quads past
+// the width folded onto it and not stored.
+template <int NQ, int G, bool FULL> struct Quads {
+    int c0;               // (F is at most 2^24)
+    int col[FULL ? 1 : NQ];
+    bool live[FULL ? 1 : NQ];
+    __device__ __forceinline__ Quads(int64_t cbase, int lane, int64_t F)
+    {
+        c0 = (int)cbase + 4 * lane;
+        if constexpr (!FULL) {
+#pragma unroll
+            for (int q = 0; q < NQ; q++) {
+                const int c = c0 + 4 * G * q;
+                live[q] = c < (int)F;
+                col[q] = c < (int)F - 4 ? c : (int)F - 4;
+            }
+        }
+    }
+    // column of quad q = base(q) + step(q), step a compile-time constant
+    __device__ __forceinline__ int base(int q) const { return FULL ? c0 : col[FULL ? 0 : q]; }
+    __device__ __forceinline__ int step(int q) const { return FULL ? 4 * G * q : 0; }
+    __device__ __forceinline__ bool ok(int q) const { return FULL || live[FULL ? 0 : q]; }
+};
+
+// How the X row of an entry is addressed: the column becomes its row's offset
+// in the lane that loads the entry, so that only offsets are broadcast.
+//   kOff32: byte offset in 32 bits (X spans less than 4 GiB)
+//   kOff64: byte offset in 64 bits
+enum { kOff32 = 0, kOff64 = 1 };
+
+template <int OFF> struct RowRef {
+    uint32_t lo = 0, hi = 0;
+    __device__ __forceinline__ void set(int col, int64_t ldx)
+    {
+        if constexpr (OFF == kOff32) {
+            lo = (uint32_t)col * (uint32_t)(ldx * 4);
+        } else {
+            const uint64_t o = (uint64_t)(uint32_t)col * (uint64_t)ldx * 4u;
+            lo = (uint32_t)o;
+            hi = (uint32_t)(o >> 32);
+        }
+    }
+};
+
+// Address of quad q of the lane in the X row of entry J.
+template <int J, int G, int OFF, class Q>
+__device__ __forceinline__ const float *x_at(const float *X, uint32_t lo, uint32_t hi, const Q &cols, int q)
+{
+    const char *b = reinterpret_cast<const char *>(X);
+    if constexpr (OFF == kOff32)
+        return reinterpret_cast<const float *>(b + (uint64_t)(lo + 4u * (uint32_t)cols.base(q))) + cols.step(q);
+    else
+        return reinterpret_cast<const float *>(b + (((uint64_t)hi << 32) | lo)) + (int64_t)cols.base(q) + cols.step(q);
+}
+
+// Entries J0 .. J0+B-1 of the group's batch (ref, v: one entry per lane): B
+// X rows requested back to back, then B multiply-adds into acc.  MASKED:
+// entries past the t-th gather nothing (a dead gather costs as much as a live
+// one) and add -0 * 0 = -0, which leaves every sum as it is.  CLS: entries
+// whose lane set `cold` are gathered non-temporally.
+template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, class Q, class A>
+__device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
+                                            const Q &cols, A *acc)
+{
+    f4u x[B][NQ];
+    float vv[B];
+    [&]<int... U>(std::integer_sequence<int, U...>) {
+        (
+            [&] {
+                const uint32_t lo = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo);
+                uint32_t hi = 0;
+                if constexpr (OFF == kOff64) hi = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi);
+                vv[U] = __int_as_float(bcast_entry<J0 + U, G>(__float_as_int(v)));
+                int c = 0;
+                if constexpr (CLS) c = bcast_entry<J0 + U, G>(cold);
+                if (MASKED) {
+#pragma unroll
+                    for (int q = 0; q < NQ; q++) x[U][q] = f4u{0.f, 0.f, 0.f, 0.f};
+                }
+                if (!MASKED || J0 + U < t) {
+                    if (CLS && c) {
+                        // (the empty asm statements keep the compiler from merging the two branches' loads
+                        // into one that has lost the non-temporal hint)
+                        asm volatile("");
+#pragma unroll
+                        for (int q = 0; q < NQ; q++)
+                            x[U][q] = __builtin_nontemporal_load(
+                                reinterpret_cast<const f4u *>(x_at<J0 + U, G, OFF>(X, lo, hi, cols, q)));
+                        asm volatile("");
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < NQ; q++)
+                            x[U][q] = *reinterpret_cast<const f4u *>(x_at<J0 + U, G, OFF>(X, lo, hi, cols, q));
+                    }
+                }
+            }(),
+            ...);
+    }(std::make_integer_sequence<int, B>{});
+#pragma unroll
+    for (int u = 0; u < B; u++)
+#pragma unroll
+        for (int q = 0; q < NQ; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++)
+                acc[4 * q + i] = __builtin_elementwise_fma((A)vv[u], (A)x[u][q][i], acc[4 * q + i]);
+}
+
+// The first t (1 .. kEntryBatch<G>) entries of the group's batch, U at a time.
+template <int J0, int U, int NQ, int G, int OFF, bool CLS, class Q, class A>
+__device__ __forceinline__ void gather_entries_of(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
+                                                  const Q &cols, A *acc)
+{
+    if constexpr (J0 < kEntryBatch<G>) {
+        if (t >= J0 + U) {
+            gather_step<J0, U, NQ, G, false, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+            gather_entries_of<J0 + U, U, NQ, G, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+        } else if (t > J0) {
+            if (U > 1 && t - J0 <= U / 2)
+                gather_step<J0, (U > 1 ? U / 2 : 1), NQ, G, true, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+            else
+                gather_step<J0, U, NQ, G, true, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+        }
+    }
+}
+
+// Stores the lane's quads of acc (rounded to fp32) at the row pointer p,
+// streaming: Y is not read again by this kernel, so it does not displace the
+// gathered X rows.
+template <int NQ, class Q, class A>
+__device__ __forceinline__ void store_quads_stream(float *p, const Q &cols, const A *acc)
+{
+#pragma unroll
+    for (int q = 0; q < NQ; q++)
+        if (cols.ok(q)) {
+            const f4u r = {(float)acc[4 * q], (float)acc[4 * q + 1], (float)acc[4 * q + 2], (float)acc[4 * q + 3]};
+            __builtin_nontemporal_store(r, reinterpret_cast<f4u *>(p + cols.base(q) + cols.step(q)));
+        }
+}
+
+// The lane's quads of acc at p, unrounded (partial sums).
+template <int NQ, class Q, class A>
+__device__ __forceinline__ void store_quads(A *p, const Q &cols, const A *acc)
+{
+#pragma unroll
+    for (int q = 0; q < NQ; q++)
+        if (cols.ok(q))
+            *reinterpret_cast<typename Quad<A>::type *>(p + cols.base(q) + cols.step(q)) = {
+                acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+}
+
 // One batch of B entries j .. j+B-1 of the group's current index batch:
 // B X-row loads issued back to back, then B fused multiply-adds.  MASKED
-// batches may run past the last entry m: those slots gather a valid row
-// (lane wrap) and are dropped by a select, so Inf/NaN in X cannot leak in.
-//
-// CLS: cj holds class-tagged column words; rows of columns whose class is
-// below hot_cls are gathered non-temporally.
-template <int B, int NQ, int G, bool MASKED, bool CLS = false, bool FENCE = false>
-__device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m,
-                                             const float *__restrict__ X, int64_t ldx, int64_t c0,
-                                             const bool *qok, float *acc, int hot_cls = 0)
+// batches may run past the last entry m: those slots gather nothing (on a
+// 512 x 512 mesh one dead gather a row made the DIA kernel 7% slower) and add
+// -0 * 0 = -0, which leaves every sum as it is.
+template <int B, int NQ, int G, bool MASKED, bool FENCE = false, class Q>
+__device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m, const float *__restrict__ X, int64_t ldx,
+                                             const Q &cols, float *acc)
 {
-    float4 x[B][NQ];
+    f4u x[B][NQ];
     float v[B];
 #pragma unroll
     for (int u = 0; u < B; u++) {
-        const int cw = __shfl(cj, j + u, G);
-        const int cu = CLS ? (cw & kColMask) : cw;
+        const int cu = __shfl(cj, j + u, G);
         v[u] = __shfl(vj, j + u, G);
-        const float *xp = X + (int64_t)cu * ldx + c0;
-        if (CLS && (cw >> kColClassShift) < hot_cls) {
+        const float *xp = X + (int64_t)cu * ldx;
+        if (MASKED) {
 #pragma unroll
-            for (int q = 0; q < NQ; q++)
-                x[u][q] = qok[q] ? load_x4_nt(xp + 4 * G * q) : make_float4(0.f, 0.f, 0.f, 0.f);
-        } else {
+            for (int q = 0; q < NQ; q++) x[u][q] = f4u{0.f, 0.f, 0.f, 0.f};
+            if (j + u >= m) v[u] = -0.0f;
+        }
+        if (!MASKED || j + u < m) {
 #pragma unroll
-            for (int q = 0; q < NQ; q++)
-                x[u][q] = qok[q] ? load_x4(xp + 4 * G * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < NQ; q++) x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
         }
     }
     // FENCE: every load of the batch is issued before the first use.  Where
@@ -68,35 +238,25 @@ __device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m,
     // with chain folds: 50 VGPRs and twice the time on a power-law matrix).
     if constexpr (FENCE) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < B; u++) {
-        const bool live = !MASKED || j + u < m;
+    for (int u = 0; u < B; u++)
 #pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            const float a0 = __builtin_fmaf(v[u], x[u][q].x, acc[4 * q + 0]);
-            const float a1 = __builtin_fmaf(v[u], x[u][q].y, acc[4 * q + 1]);
-            const float a2 = __builtin_fmaf(v[u], x[u][q].z, acc[4 * q + 2]);
-            const float a3 = __builtin_fmaf(v[u], x[u][q].w, acc[4 * q + 3]);
-            acc[4 * q + 0] = live ? a0 : acc[4 * q + 0];
-            acc[4 * q + 1] = live ? a1 : acc[4 * q + 1];
-            acc[4 * q + 2] = live ? a2 : acc[4 * q + 2];
-            acc[4 * q + 3] = live ? a3 : acc[4 * q + 3];
-        }
-    }
+        for (int q = 0; q < NQ; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc[4 * q + i] = __builtin_fmaf(v[u], x[u][q][i], acc[4 * q + i]);
 }
-
 
 // One batch of B entries j .. j+B-1 of the group's index batch in a row
 // tile whose X rows [w0, w1) are staged in LDS (xs, G*NQ float4 per row, the
 // lane's float4 at lane + G*q): in-window rows are read from LDS, the others
 // from global memory.  Slots past m gather a valid row and are dropped by a
 // select.
-template <int B, int NQ, int G>
+template <int B, int NQ, int G, class Q>
 __device__ __forceinline__ void window_batch(int cj, float vj, int j, int m, const float4 *xs, int64_t w0,
                                              int64_t w1, int lane, const float *__restrict__ X, int64_t ldx,
-                                             int64_t c0, const bool *qok, float *acc)
+                                             const Q &cols, float *acc)
 {
     constexpr int RW = G * NQ;
-    float4 x[B][NQ];
+    f4u x[B][NQ];
     float v[B];
 #pragma unroll
     for (int u = 0; u < B; u++) {
@@ -105,51 +265,41 @@ __device__ __forceinline__ void window_batch(int cj, float vj, int j, int m, con
         if (cu >= w0 && cu < w1) {
             const float4 *xr = xs + (int64_t)(cu - w0) * RW + lane;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) x[u][q] = xr[q * G];
+            for (int q = 0; q < NQ; q++) {
+                const float4 r = xr[q * G];
+                x[u][q] = f4u{r.x, r.y, r.z, r.w};
+            }
         } else {
-            const float *xp = X + (int64_t)cu * ldx + c0;
+            const float *xp = X + (int64_t)cu * ldx;
 #pragma unroll
-            for (int q = 0; q < NQ; q++)
-                x[u][q] = qok[q] ? load_x4(xp + 4 * G * q) : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < NQ; q++) x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
         }
     }
 #pragma unroll
     for (int u = 0; u < B; u++) {
         const bool live = j + u < m;
 #pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            const float a0 = __builtin_fmaf(v[u], x[u][q].x, acc[4 * q + 0]);
-            const float a1 = __builtin_fmaf(v[u], x[u][q].y, acc[4 * q + 1]);
-            const float a2 = __builtin_fmaf(v[u], x[u][q].z, acc[4 * q + 2]);
-            const float a3 = __builtin_fmaf(v[u], x[u][q].w, acc[4 * q + 3]);
-            acc[4 * q + 0] = live ? a0 : acc[4 * q + 0];
-            acc[4 * q + 1] = live ? a1 : acc[4 * q + 1];
-            acc[4 * q + 2] = live ? a2 : acc[4 * q + 2];
-            acc[4 * q + 3] = live ? a3 : acc[4 * q + 3];
-        }
+        for (int q = 0; q < NQ; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float a = __builtin_fmaf(v[u], x[u][q][i], acc[4 * q + i]);
+                acc[4 * q + i] = live ? a : acc[4 * q + i];
+            }
     }
 }
 
-// Stores NQ float4 of acc to row pointer p (columns c0 + 4*G*q), streaming.
-template <int NQ, int G>
-__device__ __forceinline__ void store_row_stream(float *p, const bool *qok, const float *acc)
+// Copies X rows [w0, w0 + W) of the column slice at cbase into LDS, RW quads
+// per row, the quads placed as Quads places them.
+template <int RW, int NT>
+__device__ __forceinline__ void stage_window(float4 *xs, int W, int64_t w0, const float *__restrict__ X, int64_t ldx,
+                                             int64_t cbase, int64_t F)
 {
-#pragma unroll
-    for (int q = 0; q < NQ; q++)
-        if (qok[q]) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) __builtin_nontemporal_store(acc[4 * q + i], p + 4 * G * q + i);
-        }
-}
-
-template <int NQ, int G>
-__device__ __forceinline__ void store_row(float *p, const bool *qok, const float *acc)
-{
-#pragma unroll
-    for (int q = 0; q < NQ; q++)
-        if (qok[q])
-            *reinterpret_cast<float4 *>(p + 4 * G * q) =
-                make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
+    for (int idx = threadIdx.x; idx < W * RW; idx += NT) {
+        const int wr = idx / RW, j = idx - wr * RW;
+        const int64_t c = cbase + 4 * j;
+        const f4u v = *reinterpret_cast<const f4u *>(X + (w0 + wr) * ldx + (c < F - 4 ? c : F - 4));
+        xs[idx] = make_float4(v[0], v[1], v[2], v[3]);
+    }
 }
 
 }  // namespace gs

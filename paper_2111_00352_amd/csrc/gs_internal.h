@@ -322,6 +322,9 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
 // (compute units x 8), queried once.
 int resident_workgroups();
 int compute_units();
+// Workgroups of `threads` threads of a kernel (without dynamic LDS) that one
+// compute unit keeps resident, queried once per kernel.
+int resident_blocks(const void *fn, int threads);
 // LDS bytes one workgroup may use (the device's limit), queried once.
 int64_t max_lds_bytes();
 

@@ -2,7 +2,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <map>
+#include <mutex>
 #include <new>
+#include <utility>
 
 #include "gs_internal.h"
 
@@ -116,6 +119,19 @@ int compute_units()
 }
 
 int resident_workgroups() { return compute_units() * 8; }
+
+int resident_blocks(const void *fn, int threads)
+{
+    static std::mutex mu;
+    static std::map<std::pair<const void *, int>, int> cache;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto key = std::make_pair(fn, threads);
+    auto it = cache.find(key);
+    if (it != cache.end()) return it->second;
+    int n = 0;
+    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, 0));
+    return cache[key] = n > 0 ? n : 1;
+}
 
 int64_t max_lds_bytes()
 {

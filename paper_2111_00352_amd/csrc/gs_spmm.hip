@@ -19,7 +19,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
-#include <mutex>
 #include <vector>
 
 #include "gs_device.h"
@@ -123,8 +122,9 @@ __global__ __launch_bounds__(kBlock) void k_csr_items_generic(
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const bool active = c0 < F;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
+    const bool active = cl < F;
     const int64_t it = (int64_t)blockIdx.x * GPB + g;
     if (it >= n_items) return;
     const int4 d = items[it];
@@ -150,9 +150,10 @@ __global__ __launch_bounds__(kBlock) void k_csr_combine(const int32_t *__restric
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
     const int64_t lr = (int64_t)blockIdx.x * GPB + g;
-    if (lr >= n_long || c0 >= F) return;
+    if (lr >= n_long || cl >= F) return;
     Acc<VEC> acc;
     acc.zero();
     for (int64_t ch = long_first[lr]; ch < long_first[lr + 1]; ch++) {
@@ -279,8 +280,9 @@ __global__ __launch_bounds__(kBlock) void k_coo_main(int64_t Z, const int32_t *_
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const bool active = c0 < F;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
+    const bool active = cl < F;
     const int64_t q = xcd_tile(blockIdx.x, gridDim.x) * GPB + g;
     if (q >= T) return;
     const int gbase = (threadIdx.x % kWave) / G * G;  // first lane of this group in the wave
@@ -363,26 +365,26 @@ __global__ __launch_bounds__(kBlock) void k_coo_main(int64_t Z, const int32_t *_
 }
 
 // The same ranges, segments and carry slots in the lane layout of the
-// vectorised CSR kernels (F a multiple of 4, 16-byte aligned operands): lane
+// vectorised CSR kernels (F of 4 and more): lane
 // l of a group holds NQ float4 at columns c0 + 4*G*q, so the per-entry
 // shuffles and row-change tests serve 4*NQ columns of a lane instead of VEC,
 // and the X rows of UB entries (8 float4 loads per lane) are requested
 // before the first is consumed.
-template <int NQ, int G>
+template <int NQ, class Q>
 __device__ __forceinline__ void coo_flush4(const float *acc, const float *tot, bool folded, int64_t row,
                                            bool first_seg, bool last_seg, bool head_cont, bool tail_cont,
                                            int64_t q, float *__restrict__ Y, int64_t ldy,
-                                           float *__restrict__ work, int64_t F, int64_t c0, const bool *qok)
+                                           float *__restrict__ work, int64_t F, const Q &cols)
 {
     float v[4 * NQ];
 #pragma unroll
     for (int i = 0; i < 4 * NQ; i++) v[i] = folded ? tot[i] + acc[i] : acc[i];
     if (first_seg && head_cont)
-        store_row<NQ, G>(work + (q * 2 + 0) * F + c0, qok, v);
+        store_quads<NQ>(work + (q * 2 + 0) * F, cols, v);
     else if (last_seg && tail_cont)
-        store_row<NQ, G>(work + (q * 2 + 1) * F + c0, qok, v);
+        store_quads<NQ>(work + (q * 2 + 1) * F, cols, v);
     else
-        store_row_stream<NQ, G>(Y + row * ldy + c0, qok, v);
+        store_quads_stream<NQ>(Y + row * ldy, cols, v);
 }
 
 template <int NQ, int G, bool FOLD>
@@ -397,10 +399,7 @@ __global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *
     constexpr int GPB = kBlock / G;
     constexpr int UB = NQ >= 4 ? 2 : NQ == 2 ? 4 : 8;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (4 * G * NQ) + (int64_t)lane * 4;
-    bool qok[NQ];
-#pragma unroll
-    for (int i = 0; i < NQ; i++) qok[i] = c0 + 4 * G * i < F;
+    const Quads<NQ, G, false> cols((int64_t)blockIdx.y * (4 * G * NQ), lane, F);
     const int64_t q = xcd_tile(blockIdx.x, gridDim.x) * GPB + g;
     if (q >= T) return;
     const int gbase = (threadIdx.x % kWave) / G * G;
@@ -439,7 +438,7 @@ __global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *
         const int n = (int)((k1 - kb) < G ? (k1 - kb) : G);
         // entries past n gather row 0 of X (cj = 0: a valid row) and are skipped
         for (int j0 = 0; j0 < n; j0 += UB) {
-            float4 xs[UB][NQ];
+            f4u xs[UB][NQ];
             float vs[UB];
             int rs[UB];
 #pragma unroll
@@ -447,18 +446,18 @@ __global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *
                 const int c_u = __shfl(cj, j0 + u, G);
                 vs[u] = __shfl(vj, j0 + u, G);
                 rs[u] = __shfl(rj, j0 + u, G);
-                const float *xp = X + (int64_t)c_u * ldx + c0;
+                const float *xp = X + (int64_t)c_u * ldx;
 #pragma unroll
                 for (int i = 0; i < NQ; i++)
-                    xs[u][i] = qok[i] ? load_x4(xp + 4 * G * i) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    xs[u][i] = *reinterpret_cast<const f4u *>(xp + cols.base(i) + cols.step(i));
             }
 #pragma unroll
             for (int u = 0; u < UB; u++) {
                 const int j = j0 + u;
                 if (j >= n) break;
                 if ((j == 0 && rs[u] != cur) || ((heads >> j) & 1ull)) {
-                    coo_flush4<NQ, G>(acc, tot, folded, cur, first_seg, false, head_cont, tail_cont, q, Y, ldy,
-                                      work, F, c0, qok);
+                    coo_flush4<NQ>(acc, tot, folded, cur, first_seg, false, head_cont, tail_cont, q, Y, ldy, work, F,
+                                   cols);
                     first_seg = false;
 #pragma unroll
                     for (int i = 0; i < 4 * NQ; i++) acc[i] = tot[i] = 0.0f;
@@ -467,12 +466,10 @@ __global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *
                     cur = rs[u];
                 }
 #pragma unroll
-                for (int i = 0; i < NQ; i++) {
-                    acc[4 * i + 0] = __builtin_fmaf(vs[u], xs[u][i].x, acc[4 * i + 0]);
-                    acc[4 * i + 1] = __builtin_fmaf(vs[u], xs[u][i].y, acc[4 * i + 1]);
-                    acc[4 * i + 2] = __builtin_fmaf(vs[u], xs[u][i].z, acc[4 * i + 2]);
-                    acc[4 * i + 3] = __builtin_fmaf(vs[u], xs[u][i].w, acc[4 * i + 3]);
-                }
+                for (int i = 0; i < NQ; i++)
+#pragma unroll
+                    for (int e = 0; e < 4; e++)
+                        acc[4 * i + e] = __builtin_fmaf(vs[u], xs[u][i][e], acc[4 * i + e]);
                 if (FOLD && ++nin == kCooFold) {
 #pragma unroll
                     for (int i = 0; i < 4 * NQ; i++) {
@@ -485,7 +482,7 @@ __global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *
             }
         }
     }
-    coo_flush4<NQ, G>(acc, tot, folded, cur, first_seg, true, head_cont, tail_cont, q, Y, ldy, work, F, c0, qok);
+    coo_flush4<NQ>(acc, tot, folded, cur, first_seg, true, head_cont, tail_cont, q, Y, ldy, work, F, cols);
 }
 
 // Groups [0, n_split): split row e = {range q, row r, n, 0}: range q begins
@@ -501,9 +498,10 @@ __global__ __launch_bounds__(kBlock) void k_coo_fixup(int64_t n_split, const int
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
     const int64_t e = (int64_t)blockIdx.x * GPB + g;
-    if (c0 >= F) return;
+    if (cl >= F) return;
     if (e < n_split) {
         const int4 d4 = split[e];
         const int64_t q = d4.x;
@@ -616,8 +614,9 @@ __global__ __launch_bounds__(kBlock) void k_ell(int64_t R, int64_t K, const int3
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const bool active = c0 < F;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
+    const bool active = cl < F;
     const int64_t row = xcd_tile(blockIdx.x, n_tiles) * GPB + g;
     if (row >= R) return;
     const int gbase = (threadIdx.x % kWave) / G * G;
@@ -680,8 +679,9 @@ __global__ __launch_bounds__(kBlock) void k_dia(int64_t R, int64_t C, int64_t ND
 {
     constexpr int GPB = kBlock / G;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const bool active = c0 < F;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
+    const bool active = cl < F;
     const int64_t row = xcd_tile(blockIdx.x, n_tiles) * GPB + g;
     if (row >= R) return;
     Acc<VEC> a0, a1, tot;
@@ -733,8 +733,9 @@ __global__ __launch_bounds__(kBlock) void k_bsr(int64_t R, int64_t C, int b, int
     constexpr int RG = kBlock / G;  // row groups
     __shared__ float blk_lds[64 * 64];
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const bool active = c0 < F;
+    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
+    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
+    const bool active = cl < F;
     const int64_t br = xcd_tile(blockIdx.x, nbr);
     const int bb = b * b;
     Acc<VEC> acc[RPT], tot[RPT];
@@ -787,14 +788,10 @@ struct Shape {
     int64_t fslices;  // grid.y
 };
 
-Shape pick_shape(const float *X, int64_t ldx, const float *Y, int64_t ldy, int64_t F)
+// Four columns per lane from F = 4 on (any alignment, see Quads), one below.
+Shape pick_shape(int64_t F)
 {
-    auto al = [](const void *p, int n) { return ((uintptr_t)p % n) == 0; };
-    int vec = 1;
-    if (F % 4 == 0 && ldx % 4 == 0 && ldy % 4 == 0 && al(X, 16) && al(Y, 16))
-        vec = 4;
-    else if (F % 2 == 0 && ldx % 2 == 0 && ldy % 2 == 0 && al(X, 8) && al(Y, 8))
-        vec = 2;
+    const int vec = F >= 4 ? 4 : 1;
     const int64_t lanes = ceil_div(F, vec);
     const int g = lanes <= 8 ? 8 : lanes <= 16 ? 16 : lanes <= 32 ? 32 : 64;
     return Shape{vec, g, ceil_div(F, (int64_t)g * vec)};
@@ -807,8 +804,7 @@ void dispatch(const Shape &sh, Fn &&fn)
 #define GS_CASE(V, GG) \
     if (sh.vec == V && sh.g == GG) return fn.template operator()<V, GG>();
     GS_CASE(4, 8) GS_CASE(4, 16) GS_CASE(4, 32) GS_CASE(4, 64)
-    GS_CASE(2, 8) GS_CASE(2, 16) GS_CASE(2, 32) GS_CASE(2, 64)
-    GS_CASE(1, 8) GS_CASE(1, 16) GS_CASE(1, 32) GS_CASE(1, 64)
+    GS_CASE(1, 8)
 #undef GS_CASE
     fail(GS_ERR_UNSUPPORTED, "no kernel for vec=%d g=%d", sh.vec, sh.g);
 }
@@ -911,7 +907,7 @@ void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
         plan_csr(m, s);
     }
     if (spmm_csr_vec4(m, X, ldx, Y, ldy, F, s, fixed)) return;
-    const Shape sh = pick_shape(X, ldx, Y, ldy, F);
+    const Shape sh = pick_shape(F);
     float *work = m.n_long_chunks ? (float *)work_for(m, fixed, (size_t)m.n_long_chunks * F * 4, s) : nullptr;
     dispatch(sh, [&]<int VEC, int G>() {
         constexpr int GPB = kBlock / G;
@@ -992,19 +988,6 @@ CooMain pick_coo_main(const Shape &sh, int64_t C, int64_t F)
     return c;
 }
 
-// Resident workgroups per CU of a main-pass kernel.
-int coo_occupancy(CooMainFn fn)
-{
-    static std::mutex mu;
-    static std::map<CooMainFn, int> cache;
-    std::lock_guard<std::mutex> lock(mu);
-    auto it = cache.find(fn);
-    if (it != cache.end()) return it->second;
-    int n = 0;
-    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, kBlock, 0));
-    return cache[fn] = n > 0 ? n : 1;
-}
-
 }  // namespace
 
 void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
@@ -1012,7 +995,7 @@ void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 {
     // the range tables are built (and allocated) per launch shape on first use
     if (fixed) fail(GS_ERR_UNSUPPORTED, "COO handles are not supported without allocation");
-    const Shape sh = pick_shape(X, ldx, Y, ldy, F);
+    const Shape sh = pick_shape(F);
     const CooMain cm = pick_coo_main(sh, m.C, F);  // main pass; the fixup keeps the generic shape
     const int64_t Z = m.Z;
     dispatch(sh, [&]<int VEC, int G>() {
@@ -1049,8 +1032,8 @@ void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
                 if (const char *e = std::getenv("GS_COO_SNAP"); e && *e)  // tests and tuning
                     S = (int)std::clamp<int64_t>(std::atoll(e), 0, kCooSnap);
             };
-            split(coo_occupancy(cm.fold));
-            if (per + S <= kCooFold) split(coo_occupancy(cm.plain));  // the launch will not fold: its own occupancy
+            split(resident_blocks((const void *)cm.fold, kBlock));
+            if (per + S <= kCooFold) split(resident_blocks((const void *)cm.plain, kBlock));  // the launch will not fold: its own occupancy
             auto key = std::make_tuple(T, per, S);
             auto it = m.coo_ranges.find(key);
             if (it == m.coo_ranges.end()) {  // first call with this split: boundaries and split rows
@@ -1122,7 +1105,7 @@ void spmm_ell(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s)
 {
     if (spmm_ell_fast(m, X, ldx, Y, ldy, F, s)) return;
-    const Shape sh = pick_shape(X, ldx, Y, ldy, F);
+    const Shape sh = pick_shape(F);
     dispatch(sh, [&]<int VEC, int G>() {
         constexpr int GPB = kBlock / G;
         const int64_t tiles = ceil_div(m.R, GPB);
@@ -1138,7 +1121,7 @@ void spmm_dia(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s)
 {
     if (spmm_dia_fast(m, X, ldx, Y, ldy, F, s)) return;
-    const Shape sh = pick_shape(X, ldx, Y, ldy, F);
+    const Shape sh = pick_shape(F);
     dispatch(sh, [&]<int VEC, int G>() {
         constexpr int GPB = kBlock / G;
         const int64_t tiles = ceil_div(m.R, GPB);
@@ -1154,7 +1137,7 @@ void spmm_bsr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s)
 {
     if (spmm_bsr16_mfma(m, X, ldx, Y, ldy, F, s)) return;
-    const Shape sh = pick_shape(X, ldx, Y, ldy, F);
+    const Shape sh = pick_shape(F);
     const int64_t nbr = ceil_div(m.R, m.b);
     if (!nbr) return;
     dispatch(sh, [&]<int VEC, int G>() {

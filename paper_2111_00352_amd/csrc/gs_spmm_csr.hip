@@ -1,4 +1,4 @@
-// CSR SpMM, vectorised path (F a multiple of 4, 16-byte aligned operands).
+// CSR SpMM, vectorised path (F of 4 and more).
 //
 // Work is cut at plan time into three tiers by row length:
 //  * short rows (at most `long_thr` entries): one group of G lanes per row;
@@ -39,176 +39,221 @@ constexpr int kBlock = 256;
 // each with halo 0 and 1.
 constexpr int kWinCands = 4;
 
-// Accumulates the entries [k0, k1) of one row into acc (NQ float4 per lane).
-// CLS: col holds class-tagged column words (see gather_batch).
-template <int NQ, int G, int U, bool CLS>
-__device__ __forceinline__ void gather_entries(const int32_t *__restrict__ col,
-                                               const float *__restrict__ val, int64_t k0,
-                                               int64_t k1, const float *__restrict__ X,
-                                               int64_t ldx, int64_t c0, const bool *qok,
-                                               float *acc, int lane, int hot_cls)
+// The group's next batch of entries: [k, k + n) of the entry arrays, one per
+// lane (every 16 lanes of a wider group load the same 16).  Lanes past the
+// last entry hold a valid column and the value -0.
+template <int G, int OFF, bool CLS> struct Batch {
+    int c;
+    float v;
+    // (zlast: the matrix's last entry, read in the place of an empty row's)
+    __device__ __forceinline__ void load(const int32_t *__restrict__ col, const float *__restrict__ val, int k, int n,
+                                         int zlast, int lane)
+    {
+        constexpr int EB = kEntryBatch<G>;
+        const int e = lane % EB;
+        int i = k + (e < n ? e : n > 0 ? n - 1 : 0);
+        i = i < zlast ? i : zlast;
+        c = ld_stream(col + i);
+        v = ld_stream(val + i);
+        if (e >= n) v = -0.0f;
+    }
+    __device__ __forceinline__ void refs(int64_t ldx, int hot_cls, RowRef<OFF> &ref, int &cold) const
+    {
+        ref.set(CLS ? (c & kColMask) : c, ldx);
+        cold = CLS ? (c >> kColClassShift) < hot_cls : 0;
+    }
+};
+
+// Accumulates the n entries from k0 on into acc, the next batch's
+// entries requested while the current one's X rows are gathered.
+template <int NQ, int G, int U, int OFF, bool CLS, class Q, class A>
+__device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, const float *__restrict__ val, int k0,
+                                            int n, int zlast, const float *__restrict__ X, int64_t ldx, const Q &cols,
+                                            int lane, int hot_cls, A *acc)
 {
-    for (int64_t kb = k0; kb < k1; kb += G) {
-        const int m = (k1 - kb) < G ? (int)(k1 - kb) : G;
-        int cj = 0;
-        float vj = 0.0f;
-        if (lane < m) {
-            cj = ld_stream(col + kb + lane);
-            vj = ld_stream(val + kb + lane);
-        }
-        int j = 0;
-        for (; j + U <= m; j += U)
-            gather_batch<U, NQ, G, false, CLS>(cj, vj, j, m, X, ldx, c0, qok, acc, hot_cls);
-        if (j < m) {
-            if (U > 1 && m - j <= U / 2)
-                gather_batch<(U > 1 ? U / 2 : 1), NQ, G, true, CLS>(cj, vj, j, m, X, ldx, c0, qok, acc, hot_cls);
-            else
-                gather_batch<U, NQ, G, true, CLS>(cj, vj, j, m, X, ldx, c0, qok, acc, hot_cls);
-        }
+    constexpr int EB = kEntryBatch<G>;
+    Batch<G, OFF, CLS> b;
+    b.load(col, val, k0, n < EB ? n : EB, zlast, lane);
+    for (int kb = 0; kb < n; kb += EB) {
+        const int left = n - kb;
+        RowRef<OFF> ref;
+        int cold;
+        b.refs(ldx, hot_cls, ref, cold);
+        const float v = b.v;
+        const int nl = left > EB ? left - EB : 0;
+        b.load(col, val, k0 + kb + (left > EB ? EB : 0), nl < EB ? nl : EB, zlast, lane);
+        gather_entries_of<0, U, NQ, G, OFF, CLS>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
     }
 }
 
-// GROUPED: the plan's group tier is active, so short items may be rows of up
-// to the group limit, summed chunk by chunk (compiled out otherwise).
-template <int CPL, int G, bool FULL, bool CLS, bool GROUPED>
+// A: the accumulator type (double: the products are summed exactly enough
+// that one rounding to fp32 is the only one that matters).
+//
+// Bound by the L2 fills of the gathered X rows (7.3 TB/s) where X exceeds the
+// L2s, by the L2's gather rate (16 TB/s) where it does not, and on small
+// matrices by the chain item -> entries -> X rows: a lane group runs its items
+// in a software pipeline, holding the next item's descriptor and first batch
+// of entries while it gathers the current one's X rows, and broadcasts entries
+// by DPP (no LDS round trip).  Against shuffled batches of G entries without
+// the pipeline: power-law graph (F = 128) 61.6 -> 60.2 us, block graph
+// (F = 256) 199 -> 185, a 30,011 x 100,003 block of 450,000 entries at F = 47
+// 23.1 -> 20.3.
+//
+// GROUPED: the plan's group tier is active, so items may be rows of up to the
+// group limit, folded every kChainFold entries (compiled out otherwise).
+template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A>
 __global__ __launch_bounds__(kBlock) void k_csr_rows(
-    int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp,
-    int chunk, int64_t n_short, const int4 *__restrict__ items, const int32_t *__restrict__ col,
-    const float *__restrict__ val, const float *__restrict__ X, int64_t ldx, float *__restrict__ Y,
-    int64_t ldy, int64_t F, float *__restrict__ work, int hot_cls)
+    int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
+    const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
+    const float *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t F, A *__restrict__ work,
+    int hot_cls, int natural)
 {
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
-    constexpr int U0 = 32 / CPL > 0 ? 32 / CPL : 1;  // 8 float4 loads in flight per lane
-    constexpr int U = U0 < G ? U0 : G;
-    __shared__ float4 part[GPB][G * NQ];
+    constexpr int EB = kEntryBatch<G>;
+        constexpr int U0 = CLS ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;  // 8 float4 loads in flight per lane (CLS: below)
+    constexpr int U = U0 < EB ? U0 : EB;
+    typedef typename Quad<A>::type A4;
+    __shared__ A4 part[GPB][G * NQ];
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * CPL) + (int64_t)lane * 4;
-    bool qok[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; q++) qok[q] = FULL || (c0 + 4 * G * q < F);
-    const int64_t tiles = n_long + (n_short + GPB - 1) / GPB;
+    const Quads<NQ, G, FULL> cols((int64_t)blockIdx.y * (G * CPL), lane, F);
+    // natural row order: each XCD takes neighbouring rows, which share X rows
+    const int64_t wg = natural ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
 
-    for (int64_t t = blockIdx.x; t < tiles; t += gridDim.x) {
-        float acc[CPL];
+    // long rows first, a workgroup each
+    int64_t t = wg;
+    for (; t < n_long; t += gridDim.x) {
+        const int64_t row = long_rows[t];
+        const int64_t s = rp[row], e = rp[row + 1];
+        A acc[CPL];
 #pragma unroll
-        for (int i = 0; i < CPL; i++) acc[i] = 0.0f;
-        if (t < n_long) {  // workgroup-uniform branch: one long row for all groups
-            const int64_t row = long_rows[t];
-            const int64_t s = rp[row], e = rp[row + 1];
-            for (int64_t cs = s + (int64_t)g * chunk; cs < e; cs += (int64_t)GPB * chunk) {
-                float part_acc[CPL];
+        for (int i = 0; i < CPL; i++) acc[i] = 0;
+        for (int64_t cs = s + (int64_t)g * chunk; cs < e; cs += (int64_t)GPB * chunk) {
+            A part_acc[CPL];
 #pragma unroll
-                for (int i = 0; i < CPL; i++) part_acc[i] = 0.0f;
-                const int64_t ce = cs + chunk < e ? cs + chunk : e;
-                gather_entries<NQ, G, U, CLS>(col, val, cs, ce, X, ldx, c0, qok, part_acc, lane, hot_cls);
+            for (int i = 0; i < CPL; i++) part_acc[i] = 0;
+            gather_span<NQ, G, U, OFF, CLS>(col, val, (int)cs, e - cs < chunk ? (int)(e - cs) : chunk, zlast, X, ldx,
+                                            cols, lane, hot_cls, part_acc);
 #pragma unroll
-                for (int i = 0; i < CPL; i++) acc[i] += part_acc[i];
-            }
-#pragma unroll
-            for (int q = 0; q < NQ; q++)
-                part[g][q * G + lane] = make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
-            __syncthreads();
-            if (g == 0) {
-#pragma unroll
-                for (int q = 0; q < NQ; q++) {
-                    float4 a = part[0][q * G + lane];
-                    for (int gg = 1; gg < GPB; gg++) {
-                        const float4 b = part[gg][q * G + lane];
-                        a.x += b.x;
-                        a.y += b.y;
-                        a.z += b.z;
-                        a.w += b.w;
-                    }
-                    acc[4 * q] = a.x;
-                    acc[4 * q + 1] = a.y;
-                    acc[4 * q + 2] = a.z;
-                    acc[4 * q + 3] = a.w;
-                }
-                store_row_stream<NQ, G>(Y + row * ldy + c0, qok, acc);
-            }
-            __syncthreads();  // part[] is reused by the next long row
-        } else {
-            const int64_t it = (t - n_long) * GPB + g;
-            if (it >= n_short) break;  // later tiles of this workgroup are past the end too
-            const int4 d = items[it];
-            if (!GROUPED || d.z <= chunk) {
-                gather_entries<NQ, G, U, CLS>(col, val, d.y, (int64_t)d.y + d.z, X, ldx, c0, qok, acc, lane,
-                                              hot_cls);
-            } else {  // a row of up to the group limit: chunk by chunk, each summed in fresh registers
-                const int64_t e = (int64_t)d.y + d.z;
-                for (int64_t cs = d.y; cs < e; cs += chunk) {
-                    float part_acc[CPL];
-#pragma unroll
-                    for (int i = 0; i < CPL; i++) part_acc[i] = 0.0f;
-                    gather_entries<NQ, G, U, CLS>(col, val, cs, cs + chunk < e ? cs + chunk : e, X, ldx, c0, qok,
-                                                  part_acc, lane, hot_cls);
-#pragma unroll
-                    for (int i = 0; i < CPL; i++) acc[i] += part_acc[i];
-                }
-            }
-            if (d.w < 0)
-                store_row_stream<NQ, G>(Y + (int64_t)d.x * ldy + c0, qok, acc);
-            else  // a chunk of a huge row: its partial sum, added later in slot order
-                store_row<NQ, G>(work + (int64_t)d.w * F + c0, qok, acc);
+            for (int i = 0; i < CPL; i++) acc[i] += part_acc[i];
         }
+#pragma unroll
+        for (int q = 0; q < NQ; q++)
+            part[g][q * G + lane] = A4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+        __syncthreads();
+        if (g == 0) {
+#pragma unroll
+            for (int q = 0; q < NQ; q++) {
+                A4 a = part[0][q * G + lane];
+#pragma unroll 4
+                for (int gg = 1; gg < GPB; gg++) a += part[gg][q * G + lane];
+#pragma unroll
+                for (int i = 0; i < 4; i++) acc[4 * q + i] = a[i];
+            }
+            store_quads_stream<NQ>(Y + row * ldy, cols, acc);
+        }
+        __syncthreads();  // part[] is reused by the next long row
+    }
+
+    // items: the tiles after the long rows, GPB items each
+    const int64_t stride = (int64_t)gridDim.x * GPB;
+    int64_t it = (t - n_long) * GPB + g;
+    if (it >= n_items) return;
+    const int64_t last = n_items - 1;
+    int4 d = items[it];
+    int4 dn = items[it + stride < last ? it + stride : last];
+    Batch<G, OFF, CLS> b;
+    b.load(col, val, d.y, d.z < EB ? d.z : EB, zlast, lane);
+    while (true) {
+        A acc[CPL], tot[GROUPED ? CPL : 1];
+#pragma unroll
+        for (int i = 0; i < CPL; i++) acc[i] = 0;
+        if constexpr (GROUPED) {
+#pragma unroll
+            for (int i = 0; i < CPL; i++) tot[i] = 0;
+        }
+        for (int kb = 0;; kb += EB) {
+            const int left = d.z - kb;
+            const bool more = left > EB;
+            RowRef<OFF> ref;
+            int cold;
+            b.refs(ldx, hot_cls, ref, cold);
+            const float v = b.v;
+            // the next batch: of this row, or the next item's first
+            const int nk = more ? d.y + kb + EB : dn.y, nn = more ? left - EB : dn.z;
+            b.load(col, val, nk, nn < EB ? nn : EB, zlast, lane);
+            gather_entries_of<0, U, NQ, G, OFF, CLS>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
+            if constexpr (GROUPED) {
+                if ((kb + EB) % kChainFold == 0) {
+#pragma unroll
+                    for (int i = 0; i < CPL; i++) {
+                        tot[i] += acc[i];
+                        acc[i] = 0;
+                    }
+                }
+            }
+            if (!more) break;
+        }
+        if constexpr (GROUPED) {
+#pragma unroll
+            for (int i = 0; i < CPL; i++) acc[i] = tot[i] + acc[i];
+        }
+        if (d.w < 0)
+            store_quads_stream<NQ>(Y + (int64_t)d.x * ldy, cols, acc);
+        else  // a chunk of a huge row: its partial sum, added later in slot order
+            store_quads<NQ>(work + (int64_t)d.w * F, cols, acc);
+        it += stride;
+        if (it >= n_items) break;
+        d = dn;
+        dn = items[it + stride < last ? it + stride : last];
     }
 }
 
 // One group per huge row: adds the row's chunk partials (consecutive slots)
 // in slot order, sixteen float4 per lane in flight, and writes the row of Y.
-template <int CPL, int G>
+template <int CPL, int G, class A>
 __global__ __launch_bounds__(kBlock) void k_csr_combine(const int32_t *__restrict__ rows,
                                                         const int32_t *__restrict__ first,
-                                                        int64_t n, const float *__restrict__ work,
+                                                        int64_t n, const A *__restrict__ work,
                                                         float *__restrict__ Y, int64_t ldy, int64_t F)
 {
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
+    typedef typename Quad<A>::type A4;
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
     const int64_t r = (int64_t)blockIdx.x * GPB + g;
     if (r >= n) return;
-    const int64_t c0 = (int64_t)blockIdx.y * (G * CPL) + (int64_t)lane * 4;
-    bool qok[NQ];
+    const Quads<NQ, G, false> cols((int64_t)blockIdx.y * (G * CPL), lane, F);
+    A acc[CPL];
 #pragma unroll
-    for (int q = 0; q < NQ; q++) qok[q] = c0 + 4 * G * q < F;
-    float acc[CPL];
-#pragma unroll
-    for (int i = 0; i < CPL; i++) acc[i] = 0.0f;
+    for (int i = 0; i < CPL; i++) acc[i] = 0;
     const int64_t s0 = first[r], s1 = first[r + 1];
     // B partials in flight, summed as a tree (zeros past the last) before
     // they join the running sum: a row of n chunks adds log2(B) + n / B terms
     // in sequence
-    constexpr int B = NQ >= 4 ? 4 : NQ == 2 ? 8 : 16;  // 16 float4 of partials per lane
+    constexpr int B = (NQ >= 4 ? 4 : NQ == 2 ? 8 : 16) / (sizeof(A) / 4);  // 16 float4 of partials per lane
     for (int64_t sl = s0; sl < s1; sl += B) {
-        float4 p[B][NQ];
+        A4 p[B][NQ];
 #pragma unroll
         for (int u = 0; u < B; u++)
 #pragma unroll
-            for (int q = 0; q < NQ; q++)
-                p[u][q] = (sl + u < s1 && qok[q])
-                              ? *reinterpret_cast<const float4 *>(work + (sl + u) * F + c0 + 4 * G * q)
-                              : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int q = 0; q < NQ; q++) {
+                p[u][q] = A4{0, 0, 0, 0};
+                if (sl + u < s1)
+                    p[u][q] = *reinterpret_cast<const A4 *>(work + (sl + u) * F + cols.base(q) + cols.step(q));
+            }
 #pragma unroll
         for (int w = 1; w < B; w <<= 1)
 #pragma unroll
             for (int u = 0; u < B; u += 2 * w)
 #pragma unroll
-                for (int q = 0; q < NQ; q++) {
-                    p[u][q].x += p[u + w][q].x;
-                    p[u][q].y += p[u + w][q].y;
-                    p[u][q].z += p[u + w][q].z;
-                    p[u][q].w += p[u + w][q].w;
-                }
+                for (int q = 0; q < NQ; q++) p[u][q] += p[u + w][q];
 #pragma unroll
-        for (int q = 0; q < NQ; q++) {
-            acc[4 * q] += p[0][q].x;
-            acc[4 * q + 1] += p[0][q].y;
-            acc[4 * q + 2] += p[0][q].z;
-            acc[4 * q + 3] += p[0][q].w;
-        }
+        for (int q = 0; q < NQ; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) acc[4 * q + i] += p[0][q][i];
     }
-    store_row_stream<NQ, G>(Y + (int64_t)rows[r] * ldy + c0, qok, acc);
+    store_quads_stream<NQ>(Y + (int64_t)rows[r] * ldy, cols, acc);
 }
 
 // Row tiles with their X window staged in LDS (natural row order, rows of at
@@ -233,10 +278,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_window(
     extern __shared__ float4 xs[];
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
     const int64_t cbase = (int64_t)blockIdx.y * (G * CPL);
-    const int64_t c0 = cbase + (int64_t)lane * 4;
-    bool qok[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; q++) qok[q] = FULL || (c0 + 4 * G * q < F);
+    const Quads<NQ, G, FULL> cols(cbase, lane, F);
 
     for (int64_t t = blockIdx.x; t < ntiles; t += gridDim.x) {
         const int64_t r0 = t * T, r1 = r0 + T < R ? r0 + T : R;
@@ -244,11 +286,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_window(
         const int64_t w1 = r1 + halo < C ? r1 + halo : C;
         const int W = w1 > w0 ? (int)(w1 - w0) : 0;
         __syncthreads();  // the previous tile's rows are done with xs
-        for (int idx = threadIdx.x; idx < W * RW; idx += kBlock) {
-            const int wr = idx / RW, j = idx - wr * RW;
-            const int64_t cc = cbase + 4 * j;
-            xs[idx] = (FULL || cc < F) ? load_x4(X + (w0 + wr) * ldx + cc) : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        stage_window<RW, kBlock>(xs, W, w0, X, ldx, cbase, F);
         __syncthreads();
         for (int64_t r = r0 + g; r < r1; r += GPB) {
             float acc[CPL];  // rows hold at most the short-row limit of entries: one chain
@@ -264,9 +302,9 @@ __global__ __launch_bounds__(kBlock) void k_csr_window(
                     vj = ld_stream(val + kb + lane);
                 }
                 for (int j = 0; j < m; j += B)
-                    window_batch<B, NQ, G>(cj, vj, j, m, xs, w0, w1, lane, X, ldx, c0, qok, acc);
+                    window_batch<B, NQ, G>(cj, vj, j, m, xs, w0, w1, lane, X, ldx, cols, acc);
             }
-            store_row_stream<NQ, G>(Y + r * ldy + c0, qok, acc);
+            store_quads_stream<NQ>(Y + r * ldy, cols, acc);
         }
     }
 }
@@ -774,11 +812,47 @@ void plan_csr(gs_matrix_ &m, hipStream_t s)
 
 // ------------------------------------------------------------- launcher
 
+namespace {
+
+// Kernel modes: full column slices with 32-bit X offsets, any width with
+// them, and any width with 64-bit offsets (X of 4 GiB and more).
+enum { kModeFull = 0, kModeAny = 1, kModeWide = 2 };
+
+// Dynamic LDS of the class gathers, which keep 4 X rows in flight per lane
+// group instead of 8 and, through this LDS, 4 workgroups per CU instead of 6.
+// Their X exceeds every cache and the kernel runs at the rate of the L2
+// fills (7.3 TB/s), so what counts is the L2 hit rate, and every row in flight
+// takes 512 B of a 4 MiB L2: 8 rows and 6 workgroups measured 3078 us on the
+// 2M-row graph, 4 rows 3005, 4 rows and 4 workgroups 2969 (2 rows 3059; 3
+// workgroups 3004).
+constexpr size_t kClassLds = 32000;
+
+// Every byte offset into X stays below 4 GiB.
+bool fits_off32(int64_t C, int64_t ldx, int64_t F)
+{
+    constexpr int64_t lim = 1ll << 30;  // elements
+    return C <= 1 || (ldx < lim && (C - 1) <= (lim - F) / ldx);
+}
+
+// Workgroups of a row kernel: `rounds` times those resident on the chip, whose
+// lane groups loop over their items.  A single round left the end of the
+// launch unbalanced (items are dealt out statically): 1 / 2 / 4 / 8 rounds
+// measured 68.1 / 61.7 / 60.2 / 61.1 us on the power-law graph, 137 / 163 /
+// 108 / 107 on a 9,000-row uniform matrix (8% dense, F = 64), 190 (2) / 187 /
+// 185 on the block graph and, gathering by class, 2969 (8) / 2955 (16) on the
+// 2M-row graph.
+unsigned rows_grid(const void *fn, int64_t tiles, int64_t slices, int rounds)
+{
+    const int64_t cap = (int64_t)resident_blocks(fn, kBlock) * compute_units() * env_int("GS_WG_MULT", rounds);
+    return (unsigned)std::max<int64_t>(1, std::min(tiles, cap / slices));
+}
+
+}  // namespace
+
 bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
                    hipStream_t s, const WorkArea *fixed)
 {
-    auto al = [](const void *p) { return ((uintptr_t)p % 16) == 0; };
-    if (F % 4 || ldx % 4 || ldy % 4 || !al(X) || !al(Y)) return false;
+    if (F < 4) return false;
     // Lane shape, measured over 160 profiled matrices at F = 64..256: four
     // columns per lane (wide groups, 8 X rows in flight per lane) is best or
     // near it, except in natural row order for very short rows (fewer than 8
@@ -793,6 +867,7 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     const int g = lanes <= 4 ? 4 : lanes <= 8 ? 8 : lanes <= 16 ? 16 : lanes <= 32 ? 32 : 64;
     const int64_t slices = ceil_div(F, (int64_t)g * cpl);
     const bool full = (F % ((int64_t)g * cpl)) == 0;
+    const int mode = !fits_off32(m.C, ldx, F) ? kModeWide : full ? kModeFull : kModeAny;
     // Reference classes: the rows of the most referenced columns, whole
     // classes of them up to GS_CSR_HOT_KB (64 MiB) at this width, are
     // gathered with plain loads, every other row non-temporally, so that
@@ -828,9 +903,10 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     // (with today's plain kernel both take 203 us there).
     int win_T = 0, win_h = 0;
     if (m.n_long_rows == 0 && !m.csr_grouped) pick_window(m, (int64_t)g * cpl * 4, win_T, win_h);
-    auto launch = [&](auto cpl_t, auto g_t, auto full_t) {
-        constexpr int CPL = decltype(cpl_t)::value, G = decltype(g_t)::value;
-        constexpr bool FU = decltype(full_t)::value;
+    auto launch = [&](auto cpl_t, auto g_t, auto mode_t) {
+        constexpr int CPL = decltype(cpl_t)::value, G = decltype(g_t)::value, M = decltype(mode_t)::value;
+        constexpr bool FU = M == kModeFull;
+        constexpr int OFF = M == kModeWide ? kOff64 : kOff32;
         constexpr int GPB = kBlock / G;
         if (win_T > 0) {
             const int64_t ntiles = ceil_div(m.R, win_T);
@@ -848,16 +924,16 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         const int64_t tiles = m.n_medium_rows + ceil_div(n_group_items, GPB);
         if (!tiles) return;
         float *work = n_huge ? (float *)work_for(m, fixed, (size_t)m.n_long_chunks * F * 4, s) : nullptr;
-        // persistent grid: a few resident workgroups per CU (measured: 4 for
-        // length-sorted rows, 8 -- about one tile each -- for natural order)
-        const int64_t cap = (int64_t)resident_workgroups() * env_int("GS_WG_MULT", m.csr_sorted ? 4 : 8);
-        dim3 grid((unsigned)std::max<int64_t>(1, std::min(tiles, cap / slices)), (unsigned)slices);
         auto rows = [&](auto cls_t, auto grp_t, const int32_t *cols) {
             constexpr bool CL = decltype(cls_t)::value, GR = decltype(grp_t)::value;
-            k_csr_rows<CPL, G, FU, CL, GR><<<grid, kBlock, 0, s>>>(
-                m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(), m.csr_chunk, n_group_items,
-                m.csr_items.as<int4>() + m.n_medium_chunks, cols, m.val.as<float>(), X, ldx, Y, ldy, F, work,
-                hot_cls);
+            const auto fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float>;
+            dim3 grid(rows_grid((const void *)fn, tiles, slices, CL ? 16 : m.csr_sorted ? 4 : 8), (unsigned)slices);
+            fn<<<grid, kBlock, CL ? kClassLds : 0, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
+                                       m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
+                                       cols ? cols : m.row_ptr.as<int32_t>(),
+                                       m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),
+                                       (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls,
+                                       m.csr_sorted ? 0 : 1);
             GS_HIP(hipGetLastError());
         };
         bool done = false;
@@ -878,20 +954,23 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         }
         if (n_huge) {
             dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
-            k_csr_combine<CPL, G><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>() + m.n_medium_rows,
-                                                        m.long_first.as<int32_t>() + m.n_medium_rows,
-                                                        n_huge, work, Y, ldy, F);
+            k_csr_combine<CPL, G, float><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>() + m.n_medium_rows,
+                                                               m.long_first.as<int32_t>() + m.n_medium_rows,
+                                                               n_huge, work, Y, ldy, F);
             GS_HIP(hipGetLastError());
         }
     };
-#define GS_L(C, GG)                                                                                  \
-    if (cpl == C && g == GG) {                                                                       \
-        if (full)                                                                                    \
-            launch(std::integral_constant<int, C>{}, std::integral_constant<int, GG>{}, std::true_type{}); \
-        else                                                                                         \
-            launch(std::integral_constant<int, C>{}, std::integral_constant<int, GG>{}, std::false_type{}); \
-        return true;                                                                                 \
-    }
+    auto by_mode = [&](auto cpl_t, auto g_t) {
+        if (mode == kModeFull)
+            launch(cpl_t, g_t, std::integral_constant<int, kModeFull>{});
+        else if (mode == kModeAny)
+            launch(cpl_t, g_t, std::integral_constant<int, kModeAny>{});
+        else
+            launch(cpl_t, g_t, std::integral_constant<int, kModeWide>{});
+        return true;
+    };
+#define GS_L(C, GG) \
+    if (cpl == C && g == GG) return by_mode(std::integral_constant<int, C>{}, std::integral_constant<int, GG>{});
     GS_L(16, 4) GS_L(16, 8) GS_L(16, 16) GS_L(16, 32) GS_L(16, 64)
     GS_L(8, 4) GS_L(8, 8) GS_L(8, 16) GS_L(8, 32) GS_L(8, 64)
     GS_L(4, 4) GS_L(4, 8) GS_L(4, 16) GS_L(4, 32) GS_L(4, 64)

@@ -198,6 +198,34 @@ def test_long_and_dense_rows(fmt):
     check_spmm(case, m, X)
 
 
+@pytest.mark.parametrize("F", [4, 5, 7, 15, 17, 31, 33, 61, 66, 127, 131, 257])
+@pytest.mark.parametrize("fmt", FMTS)
+def test_spmm_any_width_and_alignment(fmt, F):
+    # widths around the column quads, lanes and slices of every kernel, with
+    # operands at every 4-byte alignment (columns cut out of wider tensors);
+    # rows of 0..40, 300 and 2,100 entries.  X rows that no entry references
+    # hold NaN and must not leak in through the tails of batches.
+    case = _uniform_long_rows(230, 2300, 0, 40, 60 + F, hubs=(3,))
+    keep = (case.crow != 7) | (np.cumsum(case.crow == 7) <= 15)  # and one row cut short
+    keep &= ~((case.crow == 3) & (case.ccol >= 2100))
+    case = Case(case.R, case.C, case.crow[keep], case.ccol[keep], case.cval[keep])
+    used = np.zeros(case.C, bool)
+    used[case.ccol] = True
+    X = graphgen.features_x(case.C, F, 61, "normal")
+    m = case.build(fmt)
+    Yref, M = oracle.spmm(case.R, case.rp, case.ccol, case.cval, X)
+    X[~used] = np.nan
+    for off in range(4):
+        Xd = torch.full((case.C, F + 5), float("inf"), dtype=torch.float32, device=DEV)
+        Xd[:, off:off + F] = _dev(X)
+        out = torch.full((case.R, F + 7), 7.0, dtype=torch.float32, device=DEV)
+        m.spmm(Xd[:, off:off + F], out=out[:, 3 - off:3 - off + F])
+        got = _host(out)
+        ok, worst = oracle.check_spmm(got[:, 3 - off:3 - off + F], Yref, M)
+        assert ok, (off, worst)
+        assert (got[:, :3 - off] == 7.0).all() and (got[:, 3 - off + F:] == 7.0).all(), "wrote outside Y"
+
+
 def _uniform_long_rows(R, C, lo, hi, seed, hubs=()):
     # every row holds lo..hi entries at uniformly drawn columns, plus dense hub rows
     rng = np.random.default_rng(seed)
