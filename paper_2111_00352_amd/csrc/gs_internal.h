@@ -5,9 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
-#include <map>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "../../include/gnnspmm.h"
@@ -100,7 +98,8 @@ struct gs_matrix_ {
     int64_t R = 0, C = 0, Z = 0;
     hipStream_t stream = nullptr;  // stream the arrays were allocated on
 
-    // COO (row, col, val) and CSR (row_ptr, col, val) share col/val; CSC
+    // COO (row, col, val; row_ptr for its SpMM) and CSR (row_ptr, col, val)
+    // share col/val; CSC
     // keeps its col_ptr / row indices / values in row_ptr / col / val (it is
     // the CSR of the transpose).
     gs::DevBuf row, row_ptr, col, val;
@@ -121,6 +120,10 @@ struct gs_matrix_ {
     bool hyb_planned = false;
     int64_t hyb_ndense = 0, hyb_nrest = 0;
     gs::DevBuf hyb_dptr, hyb_didx, hyb_rrp, hyb_rcol, hyb_rval;
+
+    // CSC: the same matrix by rows, which the SpMM reads (a scatter by columns
+    // has to add every product into Y through memory)
+    gs_matrix_ *by_rows = nullptr;
 
     // Kernel plans built once per matrix.
     // CSR: rows longer than the short-row limit, split into chunks.
@@ -150,21 +153,7 @@ struct gs_matrix_ {
     // long rows only; win_counted says whether they were counted)
     bool win_counted = false;
     int64_t win_entries[8] = {};
-    // COO: rows with no entries (zeroed by the COO fixup launch), and the
-    // entries with |col - row| < 4096 (which sets the number of rounds)
-    int64_t n_empty_rows = 0;
-    gs::DevBuf empty_rows;
-    int64_t coo_local = 0;
-    // COO: range boundaries (T + 1) and the split rows, {range q that begins
-    // the row, row, later ranges the row runs into, 0}, per (T, per, S) the
-    // SpMM calls have used
-    struct CooRanges {
-        gs::DevBuf bounds, split;
-        int64_t n_split = 0;
-    };
-    std::map<std::tuple<int64_t, int64_t, int>, CooRanges> coo_ranges;
-
-    // F-dependent workspace (partials / carries), grown on demand.
+    // F-dependent workspace (partials), grown on demand.
     gs::DevBuf work;
 
     uint64_t device_bytes = 0;
@@ -173,7 +162,10 @@ struct gs_matrix_ {
     // (an SpMM, to_coo or an array copy): an event recorded after the last
     // such call, waited for before the arrays are freed (they are freed in
     // `stream` order, which does not cover other streams).
+    // Once there was one, calls on `stream` are recorded too: plans and
+    // workspaces may have been allocated on the other stream.
     hipEvent_t last_foreign = nullptr;
+    bool foreign = false;
 
     gs_matrix_() = default;
     gs_matrix_(const gs_matrix_ &) = delete;
@@ -184,6 +176,7 @@ struct gs_matrix_ {
             (void)hipEventSynchronize(last_foreign);
             (void)hipEventDestroy(last_foreign);
         }
+        delete by_rows;
     }
 };
 
@@ -202,15 +195,6 @@ constexpr int kCsrWgRow = 1024;
 // With many more long rows than resident workgroups, rows up to this many
 // entries take one lane group each (summed in chunks of kCsrChunk).
 constexpr int kCsrGroupRow = 2048;
-// COO: range boundaries move to the next row start within at most kCooSnap
-// entries, and a segment's running sum is folded every kCooFold entries;
-// ranges hold at least kCooMinRange entries, and about kCooBandRange when
-// they come in several rounds (so that with the move they stay within
-// kCooFold).
-constexpr int kCooSnap = 32;
-constexpr int kCooFold = 128;
-constexpr int kCooMinRange = 32;
-constexpr int kCooBandRange = 48;
 // BSR(16) hybrid plan: a block with at least this many entries (of 256)
 // runs on the matrix cores, the entries of sparser blocks as a row list.
 constexpr int kHybridDenseMin = 64;
@@ -255,6 +239,9 @@ void canonicalize(const gs_coo &A, bool assume_canonical, hipStream_t s, CanonCO
 // plan = false leaves the SpMM work plan to the first use of the handle
 // (feature extraction reads only row_ptr / col).
 gs_matrix_ *csr_from_canon(CanonCOO &&c, hipStream_t s, bool plan = true);
+
+// Row pointers of a COO handle from its sorted row indices.
+void row_pointers(gs_matrix_ &m, hipStream_t s);
 
 // Builds format fmt from a CSR handle (not consumed).
 gs_matrix_ *convert_from_csr(const gs_matrix_ &csr, int fmt, int bsr_block, uint64_t max_bytes,
@@ -301,8 +288,10 @@ void spmm_bsr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 void spmm_csc(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s, const WorkArea *fixed = nullptr);
 
-// Plans built at conversion time for the CSR and COO kernels.
-void plan_csr(gs_matrix_ &m, hipStream_t s);
+// The row plan (built or copied with a CSR, COO or CSC handle).
+// gathers = false leaves out what only spmm_csr uses (reference classes and
+// row windows).
+void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers = true);
 // Entries inside their row tile's window for every candidate tile (T = 32,
 // 64, 128, 256 rows, halo 0 / 1) of the matrix with CSR arrays rp, col, into
 // m.win_entries (synchronises s).
@@ -312,7 +301,11 @@ void count_windows(gs_matrix_ &m, const int32_t *rp, const int32_t *col, hipStre
 // when at least 65% of the entries are inside and the matrix has at least two
 // tiles per resident workgroup (false: no window).
 bool pick_window(const gs_matrix_ &m, int64_t row_bytes, int &T, int &h);
-void plan_coo(gs_matrix_ &m, const int32_t *row_ptr, hipStream_t s);
+
+// Y = A.X for a planned CSR handle with the products summed in fp64 and rounded
+// once.  fixed: as for spmm_csr, and never refused for lack of workspace.
+void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
+                   hipStream_t s, const WorkArea *fixed = nullptr);
 
 // Vectorised CSR path; returns false when F / alignment do not allow it.
 bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,

@@ -94,7 +94,8 @@ void *work_for(gs_matrix_ &m, const WorkArea *fixed, size_t bytes, hipStream_t s
 
 void note_use(gs_matrix_ &m, hipStream_t s)
 {
-    if (s == m.stream) return;
+    if (s != m.stream) m.foreign = true;
+    if (!m.foreign) return;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &cs) != hipSuccess) {  // e.g. the legacy stream during a capture
         (void)hipGetLastError();

@@ -18,7 +18,6 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
-#include <map>
 #include <vector>
 
 #include "gs_device.h"
@@ -162,442 +161,6 @@ __global__ __launch_bounds__(kBlock) void k_csr_combine(const int32_t *__restric
         for (int i = 0; i < VEC; i++) acc.v[i] += p.v[i];
     }
     st_vec_stream<VEC>(Y + (int64_t)long_rows[lr] * ldy + c0, acc.vec());
-}
-
-// ---------------------------------------------------------------- COO
-// Segmented reduction over the (row, col)-sorted triplets.  The entries are
-// cut into T ranges of about per entries, each boundary q*per moved forward
-// to the first row start within S entries (a row of at most S entries is
-// never cut; a longer one may be), so group q's range is [snap(q*per),
-// snap((q+1)*per)) and all groups have the same work, within S entries,
-// whatever the row lengths.  S = per / 3 (4 to 32) when most entries lie
-// near the diagonal, where rows are short and alike; else 0, exact ranges.  T is one round of the lane groups resident on the chip, or,
-// when most entries lie near the diagonal, as many rounds as give ranges of
-// about 110 entries: the groups at work at any moment then cover one band
-// of rows, which share their X rows in L2.
-// Row boundaries inside a range are found with a ballot over "row differs
-// from the previous entry"; a segment is written straight to Y unless its
-// row continues into a neighbouring range, in which case its partial goes to
-// a carry slot: slot H (index 0) for the range's first segment when that row
-// began in an earlier range, slot T (index 1) for the range's last segment
-// when its row begins there and continues.  Inside a segment the running sum
-// is folded every CH entries into a second sum (FOLD: only when a range can
-// hold more than CH entries), so no fp32 chain is longer than CH plus the
-// number of folds.  The boundaries, and for each range the split row it
-// begins (its last row, continuing past it, or -1) with the number of later
-// ranges the row runs into, depend only on the matrix and (T, per, S):
-// they are computed once per handle and key.  k_coo_fixup then adds each
-// split row's carries in range order.
-
-// Range boundaries b[q] = the first row start in [q*per, q*per + S] (Z
-// counts as one) or q*per itself, for q in [0, T] (b[0] = 0, b[T] = Z); then
-// the split row each range begins: its last row when that row continues
-// past the range and did not begin before it, else -1.
-__global__ __launch_bounds__(kBlock) void k_coo_bounds(const int32_t *__restrict__ row, int64_t Z, int64_t per,
-                                                       int S, int64_t T, int32_t *__restrict__ bounds)
-{
-    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q <= T; q += (int64_t)gridDim.x * kBlock) {
-        const int64_t p = q * per;
-        int64_t b = p <= 0 ? 0 : p >= Z ? Z : -1;
-        if (b < 0) {
-            const int64_t lim = p + S < Z ? p + S : Z;
-            b = p;
-            for (int64_t k = p; k <= lim; k++)
-                if (k == Z || row[k] != row[k - 1]) {
-                    b = k;
-                    break;
-                }
-        }
-        bounds[q] = (int32_t)b;
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_coo_split_rows(const int32_t *__restrict__ row, int64_t Z, int64_t T,
-                                                           const int32_t *__restrict__ bounds,
-                                                           int4 *__restrict__ split, int32_t *__restrict__ flag)
-{
-    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < T; q += (int64_t)gridDim.x * kBlock) {
-        const int64_t k0 = bounds[q], k1 = bounds[q + 1];
-        int4 d = make_int4((int)q, -1, 0, 0);
-        if (k0 < k1 && k1 < Z && row[k1] == row[k1 - 1] && !(k0 > 0 && row[k0 - 1] == row[k1 - 1])) {
-            // row r continues into ranges q+1 .. q+n: those whose first entry
-            // is r (a prefix of the later ranges, found by bisection)
-            const int32_t r = row[k1 - 1];
-            int64_t lo = q + 1, hi = T;  // ranges q+1 .. lo-1 open with r; hi and later do not
-            while (lo < hi) {
-                const int64_t mid = (lo + hi) >> 1;
-                const int64_t b = bounds[mid];
-                if (b < Z && row[b] == r)
-                    lo = mid + 1;
-                else
-                    hi = mid;
-            }
-            d = make_int4((int)q, r, (int)(lo - q - 1), 0);
-        }
-        split[q] = d;
-        flag[q] = d.y >= 0;
-    }
-}
-
-// The ranges that begin a split row, in range order: split[q] for the q
-// with flag (exclusive prefix pos).
-__global__ __launch_bounds__(kBlock) void k_coo_split_list(const int4 *__restrict__ split, int64_t T,
-                                                           const int32_t *__restrict__ pos,
-                                                           int4 *__restrict__ list)
-{
-    for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < T; q += (int64_t)gridDim.x * kBlock)
-        if (pos[q + 1] > pos[q]) list[pos[q]] = split[q];
-}
-
-template <int VEC>
-__device__ __forceinline__ void coo_flush(const Acc<VEC> &acc, const Acc<VEC> &tot, bool folded, int64_t row,
-                                          bool first_seg, bool last_seg, bool head_cont, bool tail_cont,
-                                          int64_t q, float *__restrict__ Y, int64_t ldy,
-                                          float *__restrict__ work, int64_t F, int64_t c0, bool active)
-{
-    if (!active) return;
-    Acc<VEC> v = acc;
-    if (folded) {
-        v = tot;
-        v.add(acc);
-    }
-    if (first_seg && head_cont)
-        st_vec<VEC>(work + (q * 2 + 0) * F + c0, v.vec());
-    else if (last_seg && tail_cont)
-        st_vec<VEC>(work + (q * 2 + 1) * F + c0, v.vec());
-    else
-        st_vec_stream<VEC>(Y + row * ldy + c0, v.vec());
-}
-
-template <int VEC, int G, bool FOLD>
-__global__ __launch_bounds__(kBlock) void k_coo_main(int64_t Z, const int32_t *__restrict__ row,
-                                                     const int32_t *__restrict__ col,
-                                                     const float *__restrict__ val,
-                                                     const float *__restrict__ X, int64_t ldx,
-                                                     float *__restrict__ Y, int64_t ldy, int64_t F,
-                                                     const int32_t *__restrict__ bounds, int64_t per,
-                                                     int64_t T, float *__restrict__ work)
-{
-    constexpr int GPB = kBlock / G;
-    const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
-    const bool active = cl < F;
-    const int64_t q = xcd_tile(blockIdx.x, gridDim.x) * GPB + g;
-    if (q >= T) return;
-    const int gbase = (threadIdx.x % kWave) / G * G;  // first lane of this group in the wave
-    int64_t k0, k1;
-    if (bounds) {
-        k0 = bounds[q];
-        k1 = bounds[q + 1];
-    } else {  // exact ranges
-        k0 = q * per < Z ? q * per : Z;
-        k1 = k0 + per < Z ? k0 + per : Z;
-    }
-    if (k0 >= k1) return;
-    const bool head_cont = k0 > 0 && row[k0 - 1] == row[k0];
-    const bool tail_cont = k1 < Z && row[k1] == row[k1 - 1];
-
-    Acc<VEC> acc, tot;
-    acc.zero();
-    tot.zero();
-    bool folded = false;
-    int nin = 0;  // entries in acc since the segment began or acc was last folded
-    int64_t cur = row[k0];
-    bool first_seg = true;
-    for (int64_t kb = k0; kb < k1; kb += G) {
-        const int64_t k = kb + lane;
-        int rj = -1, cj = 0;
-        float vj = 0.0f;
-        if (k < k1) {
-            rj = ld_stream(row + k);
-            cj = ld_stream(col + k);
-            vj = ld_stream(val + k);
-        }
-        // bit j set: entry kb+j starts a new row relative to entry kb+j-1
-        const int rprev = __shfl(rj, lane == 0 ? 0 : lane - 1, G);
-        const bool starts = (k < k1) && lane > 0 && rj != rprev;
-        const unsigned long long heads =
-            (__ballot(starts) >> gbase) & (G == 64 ? ~0ull : ((1ull << G) - 1));
-        const int n = (int)((k1 - kb) < G ? (k1 - kb) : G);
-        // X rows of UB entries are requested before any of them is consumed;
-        // entries past n gather row 0 of X (a valid row) and are skipped.
-        constexpr int UB = 8;
-        for (int j0 = 0; j0 < n; j0 += UB) {
-            Vec<VEC> xs[UB];
-            float vs[UB];
-            int rs[UB];
-#pragma unroll
-            for (int u = 0; u < UB; u++) {
-                const int j = j0 + u;
-                const int c_u = __shfl(cj, j, G);
-                vs[u] = __shfl(vj, j, G);
-                rs[u] = __shfl(rj, j, G);
-                if (active) xs[u] = ld_vec<VEC>(X + (int64_t)c_u * ldx + c0);
-            }
-#pragma unroll
-            for (int u = 0; u < UB; u++) {
-                const int j = j0 + u;
-                if (j >= n) break;
-                if ((j == 0 && rs[u] != cur) || ((heads >> j) & 1ull)) {
-                    // the row changes before entry j: flush the finished segment
-                    coo_flush<VEC>(acc, tot, folded, cur, first_seg, false, head_cont, tail_cont, q, Y, ldy,
-                                   work, F, c0, active);
-                    first_seg = false;
-                    acc.zero();
-                    tot.zero();
-                    folded = false;
-                    nin = 0;
-                    cur = rs[u];
-                }
-                if (active) acc.fma(vs[u], xs[u]);
-                if (FOLD && ++nin == kCooFold) {
-                    tot.add(acc);
-                    acc.zero();
-                    folded = true;
-                    nin = 0;
-                }
-            }
-        }
-    }
-    coo_flush<VEC>(acc, tot, folded, cur, first_seg, true, head_cont, tail_cont, q, Y, ldy, work, F, c0,
-                   active);
-}
-
-// The same ranges, segments and carry slots in the lane layout of the
-// vectorised CSR kernels (F of 4 and more): lane
-// l of a group holds NQ float4 at columns c0 + 4*G*q, so the per-entry
-// shuffles and row-change tests serve 4*NQ columns of a lane instead of VEC,
-// and the X rows of UB entries (8 float4 loads per lane) are requested
-// before the first is consumed.
-template <int NQ, class Q>
-__device__ __forceinline__ void coo_flush4(const float *acc, const float *tot, bool folded, int64_t row,
-                                           bool first_seg, bool last_seg, bool head_cont, bool tail_cont,
-                                           int64_t q, float *__restrict__ Y, int64_t ldy,
-                                           float *__restrict__ work, int64_t F, const Q &cols)
-{
-    float v[4 * NQ];
-#pragma unroll
-    for (int i = 0; i < 4 * NQ; i++) v[i] = folded ? tot[i] + acc[i] : acc[i];
-    if (first_seg && head_cont)
-        store_quads<NQ>(work + (q * 2 + 0) * F, cols, v);
-    else if (last_seg && tail_cont)
-        store_quads<NQ>(work + (q * 2 + 1) * F, cols, v);
-    else
-        store_quads_stream<NQ>(Y + row * ldy, cols, v);
-}
-
-template <int NQ, int G, bool FOLD>
-__global__ __launch_bounds__(kBlock) void k_coo_main4(int64_t Z, const int32_t *__restrict__ row,
-                                                      const int32_t *__restrict__ col,
-                                                      const float *__restrict__ val,
-                                                      const float *__restrict__ X, int64_t ldx,
-                                                      float *__restrict__ Y, int64_t ldy, int64_t F,
-                                                      const int32_t *__restrict__ bounds, int64_t per,
-                                                      int64_t T, float *__restrict__ work)
-{
-    constexpr int GPB = kBlock / G;
-    constexpr int UB = NQ >= 4 ? 2 : NQ == 2 ? 4 : 8;
-    const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const Quads<NQ, G, false> cols((int64_t)blockIdx.y * (4 * G * NQ), lane, F);
-    const int64_t q = xcd_tile(blockIdx.x, gridDim.x) * GPB + g;
-    if (q >= T) return;
-    const int gbase = (threadIdx.x % kWave) / G * G;
-    int64_t k0, k1;
-    if (bounds) {
-        k0 = bounds[q];
-        k1 = bounds[q + 1];
-    } else {
-        k0 = q * per < Z ? q * per : Z;
-        k1 = k0 + per < Z ? k0 + per : Z;
-    }
-    if (k0 >= k1) return;
-    const bool head_cont = k0 > 0 && row[k0 - 1] == row[k0];
-    const bool tail_cont = k1 < Z && row[k1] == row[k1 - 1];
-
-    float acc[4 * NQ], tot[4 * NQ];
-#pragma unroll
-    for (int i = 0; i < 4 * NQ; i++) acc[i] = tot[i] = 0.0f;
-    bool folded = false;
-    int nin = 0;
-    int64_t cur = row[k0];
-    bool first_seg = true;
-    for (int64_t kb = k0; kb < k1; kb += G) {
-        const int64_t k = kb + lane;
-        int rj = -1, cj = 0;
-        float vj = 0.0f;
-        if (k < k1) {
-            rj = ld_stream(row + k);
-            cj = ld_stream(col + k);
-            vj = ld_stream(val + k);
-        }
-        const int rprev = __shfl(rj, lane == 0 ? 0 : lane - 1, G);
-        const bool starts = (k < k1) && lane > 0 && rj != rprev;
-        const unsigned long long heads =
-            (__ballot(starts) >> gbase) & (G == 64 ? ~0ull : ((1ull << G) - 1));
-        const int n = (int)((k1 - kb) < G ? (k1 - kb) : G);
-        // entries past n gather row 0 of X (cj = 0: a valid row) and are skipped
-        for (int j0 = 0; j0 < n; j0 += UB) {
-            f4u xs[UB][NQ];
-            float vs[UB];
-            int rs[UB];
-#pragma unroll
-            for (int u = 0; u < UB; u++) {
-                const int c_u = __shfl(cj, j0 + u, G);
-                vs[u] = __shfl(vj, j0 + u, G);
-                rs[u] = __shfl(rj, j0 + u, G);
-                const float *xp = X + (int64_t)c_u * ldx;
-#pragma unroll
-                for (int i = 0; i < NQ; i++)
-                    xs[u][i] = *reinterpret_cast<const f4u *>(xp + cols.base(i) + cols.step(i));
-            }
-#pragma unroll
-            for (int u = 0; u < UB; u++) {
-                const int j = j0 + u;
-                if (j >= n) break;
-                if ((j == 0 && rs[u] != cur) || ((heads >> j) & 1ull)) {
-                    coo_flush4<NQ>(acc, tot, folded, cur, first_seg, false, head_cont, tail_cont, q, Y, ldy, work, F,
-                                   cols);
-                    first_seg = false;
-#pragma unroll
-                    for (int i = 0; i < 4 * NQ; i++) acc[i] = tot[i] = 0.0f;
-                    folded = false;
-                    nin = 0;
-                    cur = rs[u];
-                }
-#pragma unroll
-                for (int i = 0; i < NQ; i++)
-#pragma unroll
-                    for (int e = 0; e < 4; e++)
-                        acc[4 * i + e] = __builtin_fmaf(vs[u], xs[u][i][e], acc[4 * i + e]);
-                if (FOLD && ++nin == kCooFold) {
-#pragma unroll
-                    for (int i = 0; i < 4 * NQ; i++) {
-                        tot[i] += acc[i];
-                        acc[i] = 0.0f;
-                    }
-                    folded = true;
-                    nin = 0;
-                }
-            }
-        }
-    }
-    coo_flush4<NQ>(acc, tot, folded, cur, first_seg, true, head_cont, tail_cont, q, Y, ldy, work, F, cols);
-}
-
-// Groups [0, n_split): split row e = {range q, row r, n, 0}: range q begins
-// row r, which continues into the next n ranges; the group adds slot T of q
-// and then slot H of q+1 .. q+n in range order, sixteen loads in flight,
-// and writes Y.  The groups after those zero the empty rows.
-template <int VEC, int G>
-__global__ __launch_bounds__(kBlock) void k_coo_fixup(int64_t n_split, const int4 *__restrict__ split,
-                                                      const float *__restrict__ work,
-                                                      const int32_t *__restrict__ empty_rows,
-                                                      int64_t n_empty, float *__restrict__ Y,
-                                                      int64_t ldy, int64_t F)
-{
-    constexpr int GPB = kBlock / G;
-    const int g = threadIdx.x / G, lane = threadIdx.x % G;
-    const int64_t cl = (int64_t)blockIdx.y * (G * VEC) + (int64_t)lane * VEC;
-    const int64_t c0 = cl < F - VEC ? cl : F - VEC;  // a ragged width ends in a lane that overlaps the one before
-    const int64_t e = (int64_t)blockIdx.x * GPB + g;
-    if (cl >= F) return;
-    if (e < n_split) {
-        const int4 d4 = split[e];
-        const int64_t q = d4.x;
-        const int2 d = make_int2(d4.y, d4.z);
-        Acc<VEC> acc;
-        const Vec<VEC> t = ld_vec<VEC>(work + (q * 2 + 1) * F + c0);
-#pragma unroll
-        for (int i = 0; i < VEC; i++) acc.v[i] = t.v[i];
-        // each batch of B carries is summed as a tree (zeros past the last)
-        // before it joins the running sum: a row cut across n ranges adds
-        // log2(B) + n / B terms in sequence, not n
-        constexpr int B = 16;
-        for (int64_t p0 = 1; p0 <= d.y; p0 += B) {
-            Vec<VEC> h[B];
-#pragma unroll
-            for (int u = 0; u < B; u++) {
-                if (p0 + u <= d.y) {
-                    h[u] = ld_vec<VEC>(work + ((q + p0 + u) * 2 + 0) * F + c0);
-                } else {
-#pragma unroll
-                    for (int i = 0; i < VEC; i++) h[u].v[i] = 0.0f;
-                }
-            }
-#pragma unroll
-            for (int w = 1; w < B; w <<= 1)
-#pragma unroll
-                for (int u = 0; u < B; u += 2 * w)
-#pragma unroll
-                    for (int i = 0; i < VEC; i++) h[u].v[i] += h[u + w].v[i];
-#pragma unroll
-            for (int i = 0; i < VEC; i++) acc.v[i] += h[0].v[i];
-        }
-        st_vec_stream<VEC>(Y + (int64_t)d.x * ldy + c0, acc.vec());
-    } else {
-        const int64_t k = e - n_split;
-        if (k >= n_empty) return;
-        Vec<VEC> z;
-#pragma unroll
-        for (int i = 0; i < VEC; i++) z.v[i] = 0.0f;
-        st_vec_stream<VEC>(Y + (int64_t)empty_rows[k] * ldy + c0, z);
-    }
-}
-
-// ---------------------------------------------------------------- CSC
-// Column j of A scatters a_ij * X[j,:] into row i of Y for each of its
-// entries, so rows are summed by many workgroups at once.  The products are
-// exact in fp64 (24-bit mantissas), they are added with fp64 atomics into a
-// workspace W (R x F doubles), and W is rounded to Y once: the fp64 sums
-// carry no error that matters at fp32, whatever their order.  One wave per
-// column, lanes over the F columns of X.
-
-__global__ __launch_bounds__(kBlock) void k_fill_f64(double *__restrict__ w, int64_t n)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < n;
-         k += (int64_t)gridDim.x * kBlock)
-        w[k] = 0.0;
-}
-
-__global__ __launch_bounds__(kBlock) void k_csc_scatter(int64_t C, const int32_t *__restrict__ cp,
-                                                        const int32_t *__restrict__ ri,
-                                                        const float *__restrict__ val,
-                                                        const float *__restrict__ X, int64_t ldx,
-                                                        int64_t F, double *__restrict__ W)
-{
-    const int lane = threadIdx.x % kWave;
-    const int64_t waves = (int64_t)gridDim.x * (kBlock / kWave);
-    for (int64_t j = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave; j < C; j += waves) {
-        const int32_t k0 = cp[j], k1 = cp[j + 1];
-        if (k0 == k1) continue;
-        for (int64_t c0 = 0; c0 < F; c0 += 2 * kWave) {  // two X values per lane
-            const int64_t ca = c0 + lane, cb = c0 + kWave + lane;
-            const double xa = ca < F ? (double)X[j * ldx + ca] : 0.0;
-            const double xb = cb < F ? (double)X[j * ldx + cb] : 0.0;
-            // the column's entries 64 at a time: one row index and value per
-            // lane, broadcast to the wave by shuffles
-            for (int32_t kb = k0; kb < k1; kb += kWave) {
-                const int n = k1 - kb < kWave ? k1 - kb : kWave;
-                const int32_t rl = lane < n ? ri[kb + lane] : 0;
-                const float vl = lane < n ? val[kb + lane] : 0.0f;
-                for (int u = 0; u < n; u++) {
-                    const int64_t r = __shfl(rl, u);
-                    const double v = (double)__shfl(vl, u);
-                    if (ca < F) unsafeAtomicAdd(&W[r * F + ca], v * xa);
-                    if (cb < F) unsafeAtomicAdd(&W[r * F + cb], v * xb);
-                }
-            }
-        }
-    }
-}
-
-__global__ __launch_bounds__(kBlock) void k_round_f64(const double *__restrict__ W, int64_t R,
-                                                      int64_t F, float *__restrict__ Y, int64_t ldy)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x; k < R * F;
-         k += (int64_t)gridDim.x * kBlock)
-        Y[(k / F) * ldy + k % F] = (float)W[k];
 }
 
 // ---------------------------------------------------------------- ELL
@@ -817,86 +380,6 @@ unsigned u32_grid(int64_t n)
 
 }  // namespace
 
-// --------------------------------------------------------------- plans
-
-// The COO plan lists the empty rows, which the SpMM must zero (the kernel
-// writes only rows that hold entries), and counts the entries near the
-// diagonal, which sets the number of rounds of ranges per SpMM.
-
-namespace {
-
-constexpr int kPB = 256;
-
-inline unsigned plan_blocks(int64_t n)
-{
-    int64_t g = ceil_div(n, (int64_t)kPB);
-    return (unsigned)(g < 1 ? 1 : g > 8192 ? 8192 : g);
-}
-
-__global__ __launch_bounds__(kPB) void k_empty_flags(const int32_t *__restrict__ rp, int64_t R,
-                                                     int32_t *__restrict__ is_empty)
-{
-    for (int64_t i = (int64_t)blockIdx.x * kPB + threadIdx.x; i < R; i += (int64_t)gridDim.x * kPB)
-        is_empty[i] = rp[i + 1] == rp[i];
-}
-
-__global__ __launch_bounds__(kPB) void k_empty_list(int64_t R, const int32_t *__restrict__ off,
-                                                    int32_t *__restrict__ empty)
-{
-    for (int64_t i = (int64_t)blockIdx.x * kPB + threadIdx.x; i < R; i += (int64_t)gridDim.x * kPB)
-        if (off[i + 1] > off[i]) empty[off[i]] = (int32_t)i;
-}
-
-// Entries with |col - row| < kCooNear, one partial per workgroup.
-constexpr int64_t kCooNear = 4096;
-__global__ __launch_bounds__(kPB) void k_coo_near(const int32_t *__restrict__ row, const int32_t *__restrict__ col,
-                                                  int64_t Z, unsigned long long *__restrict__ part)
-{
-    __shared__ unsigned long long t64[kPB / kWave];
-    unsigned long long n = 0;
-    for (int64_t k = (int64_t)blockIdx.x * kPB + threadIdx.x; k < Z; k += (int64_t)gridDim.x * kPB) {
-        const int64_t d = (int64_t)col[k] - row[k];
-        n += d > -kCooNear && d < kCooNear;
-    }
-    n = block_sum_u64<kPB>(n, t64);
-    if (threadIdx.x == 0) part[blockIdx.x] = n;
-}
-
-}  // namespace
-
-void plan_coo(gs_matrix_ &m, const int32_t *row_ptr, hipStream_t s)
-{
-    const int64_t R = m.R, Z = m.Z;
-    DevBuf emp, near;
-    emp.alloc((size_t)(R + 1) * 4, s);
-    near.alloc(sizeof(unsigned long long) * 2049, s);
-    unsigned long long *d_near = near.as<unsigned long long>() + 2048;
-    GS_HIP(hipMemsetAsync(d_near, 0, sizeof(unsigned long long), s));
-    if (R > 0) {
-        k_empty_flags<<<plan_blocks(R), kPB, 0, s>>>(row_ptr, R, emp.as<int32_t>());
-        GS_HIP(hipGetLastError());
-    }
-    exclusive_scan_i32(emp.as<int32_t>(), emp.as<int32_t>(), R, true, s);
-    if (Z > 0) {
-        const unsigned G = (unsigned)std::min<int64_t>(2048, ceil_div(Z, (int64_t)kPB * 8));
-        k_coo_near<<<G, kPB, 0, s>>>(m.row.as<int32_t>(), m.col.as<int32_t>(), Z, near.as<unsigned long long>());
-        GS_HIP(hipGetLastError());
-        add_partials_u64(near.as<unsigned long long>(), G, d_near, s);
-    }
-    int32_t n_empty = 0;
-    unsigned long long n_near = 0;
-    GS_HIP(hipMemcpyAsync(&n_empty, emp.as<int32_t>() + R, 4, hipMemcpyDeviceToHost, s));
-    GS_HIP(hipMemcpyAsync(&n_near, d_near, sizeof n_near, hipMemcpyDeviceToHost, s));
-    GS_HIP(hipStreamSynchronize(s));
-    m.coo_local = (int64_t)n_near;
-    m.n_empty_rows = n_empty;
-    m.empty_rows.alloc((size_t)n_empty * 4, s);
-    if (n_empty) {
-        k_empty_list<<<plan_blocks(R), kPB, 0, s>>>(R, emp.as<int32_t>(), m.empty_rows.as<int32_t>());
-        GS_HIP(hipGetLastError());
-    }
-}
-
 // --------------------------------------------------------------- launchers
 
 void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
@@ -928,177 +411,32 @@ void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
     });
 }
 
-namespace {
-
-using CooMainFn = void (*)(int64_t, const int32_t *, const int32_t *, const float *, const float *, int64_t,
-                           float *, int64_t, int64_t, const int32_t *, int64_t, int64_t, float *);
-
-// The main COO pass for one lane shape: its plain and folding variants, lane
-// groups per workgroup and column slices of F.
-struct CooMain {
-    CooMainFn plain = nullptr, fold = nullptr;
-    int gpb = 0;
-    int64_t fslices = 0;
-};
-
-// float4 per lane of the vectorised pass: GS_COO_CPL (columns per lane: 4, 8
-// or 16) where set.  Otherwise 8 columns per lane from F = 64 on while X fits
-// in the 256 MiB memory-side cache; an X that does not is gathered from HBM,
-// where 4 columns per lane (one wider load per X row) measured faster.
-int coo_nq(int64_t C, int64_t F)
-{
-    if (const char *e = std::getenv("GS_COO_CPL")) {
-        const int c = std::atoi(e);
-        if (c == 4 || c == 8 || c == 16) return c / 4;
-    }
-    return F >= 64 && C * F * 4 <= (256ll << 20) ? 2 : 1;
-}
-
-template <int NQ, int G>
-CooMain coo_main4()
-{
-    CooMain c;
-    c.plain = k_coo_main4<NQ, G, false>;
-    c.fold = k_coo_main4<NQ, G, true>;
-    c.gpb = kBlock / G;
-    return c;
-}
-
-CooMain pick_coo_main(const Shape &sh, int64_t C, int64_t F)
-{
-    CooMain c;
-    const int nq = sh.vec == 4 ? coo_nq(C, F) : 1;
-    if (nq > 1) {
-        const int64_t lanes = ceil_div(F, (int64_t)4 * nq);
-        const int g = lanes <= 8 ? 8 : lanes <= 16 ? 16 : lanes <= 32 ? 32 : 64;
-#define GS_C4(N, GG) \
-    if (nq == N && g == GG) c = coo_main4<N, GG>();
-        GS_C4(2, 8) GS_C4(2, 16) GS_C4(2, 32) GS_C4(2, 64)
-        GS_C4(4, 8) GS_C4(4, 16) GS_C4(4, 32) GS_C4(4, 64)
-#undef GS_C4
-        c.fslices = ceil_div(F, (int64_t)4 * g * nq);
-        return c;
-    }
-    dispatch(sh, [&]<int VEC, int G>() {
-        c.plain = k_coo_main<VEC, G, false>;
-        c.fold = k_coo_main<VEC, G, true>;
-        c.gpb = kBlock / G;
-        c.fslices = sh.fslices;
-    });
-    return c;
-}
-
-}  // namespace
-
+// COO: the entries are in row order, so their column and value arrays are
+// those of the CSR form and the row kernel reads them as they are, by the row
+// plan that the handle keeps beside them and row pointers made at the first
+// SpMM.  (Equal ranges
+// of entries with a segmented sum, the schedule this replaces, took 43.8 us on
+// the power-law graph at F = 64 against 34.3 us, 255 against 185 us on the
+// block graph and 3.5 against 3.0 ms on the 2M-row graph: cut rows went through
+// carry slots and a second launch.)
 void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s, const WorkArea *fixed)
 {
-    // the range tables are built (and allocated) per launch shape on first use
     if (fixed) fail(GS_ERR_UNSUPPORTED, "COO handles are not supported without allocation");
-    const Shape sh = pick_shape(F);
-    const CooMain cm = pick_coo_main(sh, m.C, F);  // main pass; the fixup keeps the generic shape
-    const int64_t Z = m.Z;
-    dispatch(sh, [&]<int VEC, int G>() {
-        constexpr int GPB = kBlock / G;
-        int64_t T = 0, per = 0;
-        int S = 0;
-        const int32_t *bounds = nullptr;
-        const int4 *split_list = nullptr;
-        int64_t n_split = 0;
-        if (Z > 0) {
-            const bool local = 2 * m.coo_local >= Z;
-            const char *force_T = std::getenv("GS_COO_RANGES");  // tests
-            // ranges of one round of the resident lane groups (shared by the
-            // F slices); as many rounds as give ranges of about kCooBandRange
-            // entries when most entries lie near the diagonal.  Row-aligned
-            // boundaries pay where rows are short and alike (near-diagonal
-            // matrices); on random graphs the cut rows are long anyway, and
-            // exact ranges keep the single round balanced.
-            auto split = [&](int occ) {
-                const int64_t round = std::max<int64_t>(1, (int64_t)occ * compute_units() * cm.gpb / cm.fslices);
-                const int64_t rounds = local ? std::max<int64_t>(1, Z / (round * kCooBandRange)) : 1;
-                T = std::min<int64_t>(rounds * round, ceil_div(Z, (int64_t)kCooMinRange));
-                if (force_T && *force_T) T = std::max<int64_t>(1, std::atoll(force_T));
-                per = ceil_div(Z, T);
-                T = ceil_div(Z, per);  // no range past the last entry
-                // (at most kCooFold - per where that leaves 4 or more: then no
-                // range exceeds kCooFold entries and the launch needs no folds)
-                S = 0;
-                if (local) {
-                    int64_t w = std::min<int64_t>(kCooSnap, per / 3);
-                    if (kCooFold - per >= 4) w = std::min<int64_t>(w, kCooFold - per);
-                    S = (int)std::max<int64_t>(4, w);
-                }
-                if (const char *e = std::getenv("GS_COO_SNAP"); e && *e)  // tests and tuning
-                    S = (int)std::clamp<int64_t>(std::atoll(e), 0, kCooSnap);
-            };
-            split(resident_blocks((const void *)cm.fold, kBlock));
-            if (per + S <= kCooFold) split(resident_blocks((const void *)cm.plain, kBlock));  // the launch will not fold: its own occupancy
-            auto key = std::make_tuple(T, per, S);
-            auto it = m.coo_ranges.find(key);
-            if (it == m.coo_ranges.end()) {  // first call with this split: boundaries and split rows
-                gs_matrix_::CooRanges cr;
-                cr.bounds.alloc((size_t)(T + 1) * 4, s);
-                DevBuf all, pos;
-                all.alloc((size_t)T * sizeof(int4), s);
-                pos.alloc((size_t)(T + 1) * 4, s);
-                const unsigned gb = (unsigned)std::min<int64_t>(4096, ceil_div(T + 1, (int64_t)kBlock));
-                k_coo_bounds<<<gb, kBlock, 0, s>>>(m.row.as<int32_t>(), Z, per, S, T, cr.bounds.as<int32_t>());
-                GS_HIP(hipGetLastError());
-                k_coo_split_rows<<<gb, kBlock, 0, s>>>(m.row.as<int32_t>(), Z, T, cr.bounds.as<int32_t>(),
-                                                       all.as<int4>(), pos.as<int32_t>());
-                GS_HIP(hipGetLastError());
-                exclusive_scan_i32(pos.as<int32_t>(), pos.as<int32_t>(), T, true, s);
-                int32_t ns = 0;
-                GS_HIP(hipMemcpyAsync(&ns, pos.as<int32_t>() + T, 4, hipMemcpyDeviceToHost, s));
-                GS_HIP(hipStreamSynchronize(s));
-                cr.n_split = ns;
-                cr.split.alloc((size_t)ns * sizeof(int4), s);
-                if (ns) {
-                    k_coo_split_list<<<gb, kBlock, 0, s>>>(all.as<int4>(), T, pos.as<int32_t>(), cr.split.as<int4>());
-                    GS_HIP(hipGetLastError());
-                }
-                it = m.coo_ranges.emplace(key, std::move(cr)).first;
-            }
-            bounds = S ? it->second.bounds.as<int32_t>() : nullptr;  // exact ranges: q * per
-            split_list = it->second.split.as<int4>();
-            n_split = it->second.n_split;
-            if (T > 1) ensure_work(m, (size_t)T * 2 * F * 4, s);  // two carry slots of F floats per range
-            dim3 grid(u32_grid(ceil_div(T, (int64_t)cm.gpb)), (unsigned)cm.fslices);
-            const CooMainFn fn = per + S > kCooFold ? cm.fold : cm.plain;
-            fn<<<grid, kBlock, 0, s>>>(Z, m.row.as<int32_t>(), m.col.as<int32_t>(), m.val.as<float>(), X, ldx, Y,
-                                       ldy, F, bounds, per, T, m.work.as<float>());
-            GS_HIP(hipGetLastError());
-        }
-        const int64_t groups = n_split + m.n_empty_rows;
-        if (groups) {
-            dim3 g2(u32_grid(ceil_div(groups, GPB)), (unsigned)sh.fslices);
-            k_coo_fixup<VEC, G><<<g2, kBlock, 0, s>>>(n_split, split_list, m.work.as<float>(),
-                                                      m.empty_rows.as<int32_t>(), m.n_empty_rows, Y, ldy, F);
-            GS_HIP(hipGetLastError());
-        }
-    });
+    if (!m.row_ptr.p) row_pointers(m, s);
+    spmm_csr(m, X, ldx, Y, ldy, F, s, fixed);
 }
 
+// CSC: rows gathered from the handle's row form, the products summed in fp64
+// (they are exact there) and rounded once.  Scattering the columns into an
+// R x F fp64 accumulator with atomics, which this replaces, took 781 us on the
+// power-law graph at F = 64 (180 billion atomics a second) against 38 us.
+// Without allocation the accumulator's size, 8 R F bytes, remains the limit.
 void spmm_csc(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s, const WorkArea *fixed)
 {
-    const int64_t n = m.R * F;
-    if (n == 0) return;
-    double *W = (double *)work_for(m, fixed, (size_t)n * 8, s);
-    auto grid = [](int64_t items) {
-        int64_t g = ceil_div(items, (int64_t)kBlock);
-        return (unsigned)(g < 1 ? 1 : g > 65536 ? 65536 : g);
-    };
-    k_fill_f64<<<grid(n), kBlock, 0, s>>>(W, n);
-    GS_HIP(hipGetLastError());
-    if (m.Z) {
-        k_csc_scatter<<<grid(m.C * kWave), kBlock, 0, s>>>(m.C, m.row_ptr.as<int32_t>(), m.col.as<int32_t>(),
-                                                             m.val.as<float>(), X, ldx, F, W);
-        GS_HIP(hipGetLastError());
-    }
-    k_round_f64<<<grid(n), kBlock, 0, s>>>(W, m.R, F, Y, ldy);
-    GS_HIP(hipGetLastError());
+    if (fixed) (void)work_for(m, fixed, (size_t)(m.R * F) * 8, s);
+    spmm_rows_f64(*m.by_rows, X, ldx, Y, ldy, F, s, fixed);
 }
 
 void spmm_ell(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,

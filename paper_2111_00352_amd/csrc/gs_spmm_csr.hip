@@ -111,7 +111,8 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
     constexpr int EB = kEntryBatch<G>;
-        constexpr int U0 = CLS ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;  // 8 float4 loads in flight per lane (CLS: below)
+        // 8 float4 loads in flight per lane (4 where registers or L2 lines are short: fp64 sums, class gathers)
+    constexpr int U0 = CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
     constexpr int U = U0 < EB ? U0 : EB;
     typedef typename Quad<A>::type A4;
     __shared__ A4 part[GPB][G * NQ];
@@ -254,6 +255,59 @@ __global__ __launch_bounds__(kBlock) void k_csr_combine(const int32_t *__restric
             for (int i = 0; i < 4; i++) acc[4 * q + i] += p[0][q][i];
     }
     store_quads_stream<NQ>(Y + (int64_t)rows[r] * ldy, cols, acc);
+}
+
+// Widths below 4, in fp64: a wave per item of the plan (or, without items, per
+// row), its lanes over the entries, one sum per column.  Chunks of long rows
+// go to work[slot * F + c].
+__global__ __launch_bounds__(kBlock) void k_rows_f64_narrow(int64_t n, const int4 *__restrict__ items,
+                                                            const int32_t *__restrict__ rp,
+                                                            const int32_t *__restrict__ col,
+                                                            const float *__restrict__ val, const float *__restrict__ X,
+                                                            int64_t ldx, float *__restrict__ Y, int64_t ldy, int F,
+                                                            double *__restrict__ work)
+{
+    const int lane = threadIdx.x % kWave;
+    const int64_t waves = (int64_t)gridDim.x * (kBlock / kWave);
+    for (int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave; i < n; i += waves) {
+        int4 d;
+        if (items)
+            d = items[i];
+        else
+            d = make_int4((int)i, rp[i], rp[i + 1] - rp[i], -1);
+        double a[3] = {0.0, 0.0, 0.0};
+        for (int k = lane; k < d.z; k += kWave) {
+            const double v = val[d.y + k];
+            const float *x = X + (int64_t)col[d.y + k] * ldx;
+            for (int c = 0; c < F; c++) a[c] = __builtin_fma(v, (double)x[c], a[c]);
+        }
+        for (int c = 0; c < F; c++) {
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) a[c] += __shfl_xor(a[c], o, kWave);
+            if (lane != 0) continue;
+            if (d.w < 0)
+                Y[(int64_t)d.x * ldy + c] = (float)a[c];
+            else
+                work[(int64_t)d.w * F + c] = a[c];
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_combine_f64_narrow(int64_t n, const int32_t *__restrict__ rows,
+                                                               const int32_t *__restrict__ first,
+                                                               const double *__restrict__ work,
+                                                               float *__restrict__ Y, int64_t ldy, int F)
+{
+    const int64_t r = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
+    const int lane = threadIdx.x % kWave;
+    if (r >= n) return;
+    for (int c = 0; c < F; c++) {
+        double a = 0.0;
+        for (int64_t sl = first[r] + lane; sl < first[r + 1]; sl += kWave) a += work[sl * F + c];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, kWave);
+        if (lane == 0) Y[(int64_t)rows[r] * ldy + c] = (float)a;
+    }
 }
 
 // Row tiles with their X window staged in LDS (natural row order, rows of at
@@ -697,7 +751,7 @@ void plan_col_classes(gs_matrix_ &m, hipStream_t s)
     for (int c = 0; c < 16; c++) m.col_class_cols[c] = h[c];
 }
 
-void plan_csr(gs_matrix_ &m, hipStream_t s)
+void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
 {
     const int thr = env_int("GS_CSR_LONG_ROW", kCsrLongRow);
     const int chunk = std::min(env_int("GS_CSR_CHUNK", kCsrChunk), thr);
@@ -805,8 +859,10 @@ void plan_csr(gs_matrix_ &m, hipStream_t s)
     } else {
         GS_HIP(hipMemsetAsync(m.long_first.p, 0, 4, s));
     }
-    plan_col_classes(m, s);
-    plan_windows(m, s);
+    if (gathers) {
+        plan_col_classes(m, s);
+        plan_windows(m, s);
+    }
     m.csr_planned = true;
 }
 
@@ -976,6 +1032,74 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     GS_L(4, 4) GS_L(4, 8) GS_L(4, 16) GS_L(4, 32) GS_L(4, 64)
 #undef GS_L
     return false;
+}
+
+void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F, hipStream_t s,
+                   const WorkArea *fixed)
+{
+    // Partial sums of the long rows cut into chunks.  A fixed workspace too
+    // small for them: no chunks, every long row takes a workgroup (a wave).
+    const size_t need = (size_t)m.n_long_chunks * F * 8;
+    const bool chunks = !fixed || need <= fixed->cap;
+    const int32_t *rp = m.row_ptr.as<int32_t>();
+    const int32_t *col = m.Z ? m.col.as<int32_t>() : rp;
+    const float *val = m.Z ? m.val.as<float>() : m.row_ptr.as<float>();
+    const int4 *items = m.csr_items.as<int4>();
+    if (F < 4) {
+        double *work = chunks && need ? (double *)work_for(m, fixed, need, s) : nullptr;
+        const int64_t n = chunks ? m.n_items : m.R;
+        const int64_t g = std::min<int64_t>(ceil_div(n, kBlock / kWave), 1 << 16);
+        k_rows_f64_narrow<<<(unsigned)std::max<int64_t>(g, 1), kBlock, 0, s>>>(n, chunks ? items : nullptr, rp, col, val,
+                                                                              X, ldx, Y, ldy, (int)F, work);
+        GS_HIP(hipGetLastError());
+        if (chunks && m.n_long_rows) {
+            k_combine_f64_narrow<<<(unsigned)ceil_div(m.n_long_rows, kBlock / kWave), kBlock, 0, s>>>(
+                m.n_long_rows, m.long_rows.as<int32_t>(), m.long_first.as<int32_t>(), work, Y, ldy, (int)F);
+            GS_HIP(hipGetLastError());
+        }
+        return;
+    }
+    const int64_t lanes = ceil_div(F, 4);
+    const int g = lanes <= 4 ? 4 : lanes <= 8 ? 8 : lanes <= 16 ? 16 : lanes <= 32 ? 32 : 64;
+    const int64_t slices = ceil_div(F, (int64_t)g * 4);
+    const int64_t n_wg = chunks ? m.n_medium_rows : m.n_long_rows;       // long rows that take a workgroup
+    const int64_t skip = chunks ? m.n_medium_chunks : m.n_long_chunks;   // their chunk items
+    const int64_t n_huge = m.n_long_rows - n_wg;
+    double *work = n_huge ? (double *)work_for(m, fixed, need, s) : nullptr;
+    auto launch = [&](auto g_t, auto mode_t) {
+        constexpr int G = decltype(g_t)::value, M = decltype(mode_t)::value, GPB = kBlock / G;
+        const auto fn = k_csr_rows<4, G, M == kModeFull, M == kModeWide ? kOff64 : kOff32, false, false, double>;
+        const int64_t tiles = n_wg + ceil_div(m.n_items - skip, GPB);
+        if (!tiles) return;
+        dim3 grid(rows_grid((const void *)fn, tiles, slices, m.csr_sorted ? 4 : 8), (unsigned)slices);
+        fn<<<grid, kBlock, 0, s>>>(n_wg, m.long_rows.as<int32_t>(), rp, m.csr_chunk, m.n_items - skip, items + skip, col,
+                                   val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0,
+                                   m.csr_sorted ? 0 : 1);
+        GS_HIP(hipGetLastError());
+        if (n_huge) {
+            dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
+            k_csr_combine<4, G, double><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>() + n_wg,
+                                                              m.long_first.as<int32_t>() + n_wg, n_huge, work, Y, ldy,
+                                                              F);
+            GS_HIP(hipGetLastError());
+        }
+    };
+    const bool full = F % ((int64_t)g * 4) == 0, wide = !fits_off32(m.C, ldx, F);
+    auto by_g = [&](auto mode_t) {
+        switch (g) {
+        case 4: launch(std::integral_constant<int, 4>{}, mode_t); break;
+        case 8: launch(std::integral_constant<int, 8>{}, mode_t); break;
+        case 16: launch(std::integral_constant<int, 16>{}, mode_t); break;
+        case 32: launch(std::integral_constant<int, 32>{}, mode_t); break;
+        default: launch(std::integral_constant<int, 64>{}, mode_t); break;
+        }
+    };
+    if (wide)
+        by_g(std::integral_constant<int, kModeWide>{});
+    else if (full)
+        by_g(std::integral_constant<int, kModeFull>{});
+    else
+        by_g(std::integral_constant<int, kModeAny>{});
 }
 
 }  // namespace gs

@@ -226,6 +226,27 @@ def test_spmm_any_width_and_alignment(fmt, F):
         assert (got[:, :3 - off] == 7.0).all() and (got[:, 3 - off + F:] == 7.0).all(), "wrote outside Y"
 
 
+@pytest.mark.parametrize("F", [1, 2, 3, 4, 50, 260])
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_csc_row_sums_in_fp64(F, noalloc):
+    # the row form behind a CSC handle: short rows, rows of one workgroup
+    # (129..1,024 entries), chunked rows.  For noalloc at F = 260 the chunks'
+    # partial sums (8 F bytes each) exceed the fixed scratch while the refusal
+    # rule (8 R F bytes) does not apply, so the long rows take a workgroup
+    # each; every width equals the oracle's fp64 sum rounded once, up to one
+    # fp32 step where a sum sits on a rounding boundary.
+    n_long = 40_000 if noalloc and F == 260 else 3_000
+    case = _uniform_long_rows(130, n_long, 0, 400, 70, hubs=range(0, 130, 1 if n_long > 3000 else 40))
+    X = graphgen.features_x(case.C, F, 71, "normal")
+    m = case.build("csc")
+    Xd = _dev(X)
+    out = torch.full((case.R, F), 7.0, dtype=torch.float32, device=DEV)
+    (m.spmm_noalloc if noalloc else m.spmm)(Xd, out)
+    Yref, _ = oracle.spmm(case.R, case.rp, case.ccol, case.cval, X)
+    want = Yref.astype(np.float32)
+    assert np.all(np.abs(_host(out) - want) <= np.spacing(np.abs(want)))
+
+
 def _uniform_long_rows(R, C, lo, hi, seed, hubs=()):
     # every row holds lo..hi entries at uniformly drawn columns, plus dense hub rows
     rng = np.random.default_rng(seed)
