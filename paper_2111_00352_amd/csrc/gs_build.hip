@@ -87,19 +87,19 @@ __global__ __launch_bounds__(kTB) void k_validate(const int32_t *__restrict__ ro
 }
 
 // ------------------------------------------------------------ radix sort
-// LSD radix sort of the 64-bit keys (row << 32 | col), 8-bit digits, stable
-// per pass, carrying the original position as payload.
+// LSD radix sort of the 64-bit keys (row << col_bits | col), 8-bit digits,
+// stable per pass, carrying the original position as payload.
 
-constexpr int kRI = 16;             // keys per thread per tile
+constexpr int kRI = 8;              // keys per thread per tile
 constexpr int kRT = kTB * kRI;      // keys per tile
 
 __global__ __launch_bounds__(kTB) void k_make_keys(const int32_t *__restrict__ row,
-                                                   const int32_t *__restrict__ col, int64_t Z,
+                                                   const int32_t *__restrict__ col, int64_t Z, int col_bits,
                                                    uint64_t *__restrict__ keys)
 {
     for (int64_t k = (int64_t)blockIdx.x * kTB + threadIdx.x; k < Z;
          k += (int64_t)gridDim.x * kTB)
-        keys[k] = ((uint64_t)(uint32_t)row[k] << 32) | (uint32_t)col[k];
+        keys[k] = ((uint64_t)(uint32_t)row[k] << col_bits) | (uint32_t)col[k];
 }
 
 __global__ __launch_bounds__(kTB) void k_radix_hist(const uint64_t *__restrict__ keys, int64_t n,
@@ -110,10 +110,15 @@ __global__ __launch_bounds__(kTB) void k_radix_hist(const uint64_t *__restrict__
     h[threadIdx.x] = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kRT;
-    for (int i = 0; i < kRI; i++) {
-        int64_t k = base + (int64_t)i * kTB + threadIdx.x;
-        if (k < n) atomicAdd(&h[(keys[k] >> shift) & 255], 1);
+    uint64_t key[kRI];
+#pragma unroll
+    for (int i = 0; i < kRI; i++) {  // clamped: no load behind a branch
+        const int64_t k = base + (int64_t)i * kTB + threadIdx.x;
+        key[i] = keys[k < n ? k : n - 1];
     }
+#pragma unroll
+    for (int i = 0; i < kRI; i++)
+        if (base + (int64_t)i * kTB + threadIdx.x < n) atomicAdd(&h[(key[i] >> shift) & 255], 1);
     __syncthreads();
     hist[(int64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
 }
@@ -133,10 +138,22 @@ __global__ __launch_bounds__(kTB) void k_radix_scatter(
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * kRT;
     const uint64_t lt = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+    // the tile's keys and payloads, all requested before the first round
+    // (loaded round by round behind its barriers they cost a round trip each:
+    // 19.4 us a pass over 10^6 keys, 12.4 now with 8 keys per thread)
+    uint64_t keys[kRI];
+    uint32_t pays[kRI];
+#pragma unroll
+    for (int r = 0; r < kRI; r++) {
+        const int64_t k = base + (int64_t)r * kTB + t, kc = k < n ? k : n - 1;
+        keys[r] = kin[kc];
+        pays[r] = pin ? pin[kc] : (uint32_t)k;
+    }
+#pragma unroll
     for (int r = 0; r < kRI; r++) {
         const int64_t k = base + (int64_t)r * kTB + t;
         const bool valid = k < n;
-        const uint64_t key = valid ? kin[k] : 0ull;
+        const uint64_t key = keys[r];
         const int d = (int)((key >> shift) & 255);
         // lanes of this wave holding the same digit
         uint64_t peers = __ballot(valid);
@@ -154,7 +171,7 @@ __global__ __launch_bounds__(kTB) void k_radix_scatter(
             for (int i = 0; i < W; i++)
                 if (i < w) pos += cnt[i][d];
             kout[pos] = key;
-            pout[pos] = pin ? pin[k] : (uint32_t)k;
+            pout[pos] = pays[r];
         }
         __syncthreads();
         int add = 0;
@@ -170,7 +187,7 @@ __global__ __launch_bounds__(kTB) void k_radix_scatter(
 
 __global__ __launch_bounds__(kTB) void k_unpack_sorted(const uint64_t *__restrict__ keys,
                                                        const uint32_t *__restrict__ perm,
-                                                       const float *__restrict__ val, int64_t Z,
+                                                       const float *__restrict__ val, int64_t Z, int col_bits,
                                                        int32_t *__restrict__ orow,
                                                        int32_t *__restrict__ ocol,
                                                        float *__restrict__ oval,
@@ -180,8 +197,8 @@ __global__ __launch_bounds__(kTB) void k_unpack_sorted(const uint64_t *__restric
     for (int64_t k = (int64_t)blockIdx.x * kTB + threadIdx.x; k < Z;
          k += (int64_t)gridDim.x * kTB) {
         uint64_t key = keys[k];
-        orow[k] = (int32_t)(key >> 32);
-        ocol[k] = (int32_t)(key & 0xffffffffu);
+        orow[k] = (int32_t)(key >> col_bits);
+        ocol[k] = (int32_t)(key & ((1ull << col_bits) - 1));
         oval[k] = val[perm ? perm[k] : k];
         if (k > 0 && keys[k - 1] == key) f |= kFlagDup;
     }
@@ -749,17 +766,24 @@ void radix_sort_pairs(uint64_t *ka, uint64_t *kb, uint32_t *pa, uint32_t *pb, in
     *perm = pin;
 }
 
-// Sorts the triplets (major[k], minor[k], val[k]) by (major, minor) into
-// omajor / ominor / oval (a stable LSD radix sort over the bits in use).
-// Used to move from row-major to column-major order.
+// Shifts of the 8-bit digits of the key bits [from, to).
+std::vector<int> digit_shifts(int from, int to)
+{
+    std::vector<int> sh;
+    for (int b = from; b < to; b += 8) sh.push_back(b);
+    return sh;
+}
+
+// Sorts the triplets (major[k], minor[k], val[k]), given in (minor, major)
+// order, by (major, minor) into omajor / ominor / oval: a stable LSD radix sort
+// on the major index alone.  Used to move from row-major to column-major order.
 void sort_triplets(const int32_t *major, const int32_t *minor, const float *val, int64_t Z,
                    int64_t n_major, int64_t n_minor, int32_t *omajor, int32_t *ominor, float *oval,
                    hipStream_t s)
 {
     if (Z == 0) return;
-    std::vector<int> shifts;
-    for (int sft = 0; sft < bits_for(n_minor - 1); sft += 8) shifts.push_back(sft);
-    for (int sft = 0; sft < bits_for(n_major - 1); sft += 8) shifts.push_back(32 + sft);
+    const int bits = bits_for(n_minor - 1);
+    const std::vector<int> shifts = digit_shifts(bits, bits + bits_for(n_major - 1));
     DevBuf k0, k1, p0, p1, flags;
     k0.alloc((size_t)Z * 8, s);
     k1.alloc((size_t)Z * 8, s);
@@ -767,13 +791,13 @@ void sort_triplets(const int32_t *major, const int32_t *minor, const float *val,
     p1.alloc((size_t)Z * 4, s);
     flags.alloc(sizeof(int), s);
     GS_HIP(hipMemsetAsync(flags.p, 0, sizeof(int), s));
-    k_make_keys<<<elem_grid(Z), kTB, 0, s>>>(major, minor, Z, k0.as<uint64_t>());
+    k_make_keys<<<elem_grid(Z), kTB, 0, s>>>(major, minor, Z, bits, k0.as<uint64_t>());
     GS_LAUNCH_CHECK();
     uint64_t *keys = nullptr;
     uint32_t *perm = nullptr;
     radix_sort_pairs(k0.as<uint64_t>(), k1.as<uint64_t>(), p0.as<uint32_t>(), p1.as<uint32_t>(), Z,
                      shifts, s, &keys, &perm);
-    k_unpack_sorted<<<elem_grid(Z), kTB, 0, s>>>(keys, perm, val, Z, omajor, ominor, oval,
+    k_unpack_sorted<<<elem_grid(Z), kTB, 0, s>>>(keys, perm, val, Z, bits, omajor, ominor, oval,
                                                  flags.as<int>());
     GS_LAUNCH_CHECK();
 }
@@ -812,23 +836,21 @@ void canonicalize(const gs_coo &A, bool assume_canonical, hipStream_t s, CanonCO
         fail(GS_ERR_INVALID_ARG, "assume_canonical set but the COO is not strictly (row,col)-sorted");
 
     // LSD radix sort over the bits that are in use.
-    const int bc = bits_for(C - 1), br = bits_for(R - 1);
-    std::vector<int> shifts;
-    for (int sft = 0; sft < bc; sft += 8) shifts.push_back(sft);
-    for (int sft = 0; sft < br; sft += 8) shifts.push_back(32 + sft);
+    const int bits = bits_for(C - 1);
+    const std::vector<int> shifts = digit_shifts(0, bits + bits_for(R - 1));
     DevBuf k0, k1, p0, p1;
     k0.alloc((size_t)Z * 8, s);
     k1.alloc((size_t)Z * 8, s);
     p0.alloc((size_t)Z * 4, s);
     p1.alloc((size_t)Z * 4, s);
-    k_make_keys<<<elem_grid(Z), kTB, 0, s>>>(A.row, A.col, Z, k0.as<uint64_t>());
+    k_make_keys<<<elem_grid(Z), kTB, 0, s>>>(A.row, A.col, Z, bits, k0.as<uint64_t>());
     GS_LAUNCH_CHECK();
     uint64_t *kin = nullptr;
     uint32_t *pin = nullptr;
     radix_sort_pairs(k0.as<uint64_t>(), k1.as<uint64_t>(), p0.as<uint32_t>(), p1.as<uint32_t>(), Z,
                      shifts, s, &kin, &pin);
     GS_HIP(hipMemsetAsync(flags.p, 0, sizeof(int), s));
-    k_unpack_sorted<<<elem_grid(Z), kTB, 0, s>>>(kin, pin, A.val, Z, out.row.as<int32_t>(),
+    k_unpack_sorted<<<elem_grid(Z), kTB, 0, s>>>(kin, pin, A.val, Z, bits, out.row.as<int32_t>(),
                                                  out.col.as<int32_t>(), out.val.as<float>(),
                                                  flags.as<int>());
     GS_LAUNCH_CHECK();

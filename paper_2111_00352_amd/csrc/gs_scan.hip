@@ -1,5 +1,5 @@
-// Device exclusive prefix sum over int32 (reduce -> scan of tile sums ->
-// scan of tiles), used by the format builders for row pointers, block
+// Device exclusive prefix sum over int32 (reduce -> scan of tiles, with a scan
+// of the tile sums between them for long inputs), used by the format builders for row pointers, block
 // pointers, diagonal numbering and output positions.
 #include "gs_device.h"
 #include "gs_internal.h"
@@ -51,10 +51,24 @@ __global__ __launch_bounds__(kSB) void k_tile_sums(const int32_t *__restrict__ i
     if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
+// tile_off: exclusive offsets of the tiles, or (sums set) the tiles' sums, of
+// which every workgroup adds those before its own tile itself: up to
+// kSumsTiles tiles that is cheaper than a launch that scans them (3 us).
+constexpr int64_t kSumsTiles = 4096;
+
 __global__ __launch_bounds__(kSB) void k_scan_tiles(const int32_t *in, int32_t *out, int64_t n,
-                                                    const int32_t *__restrict__ tile_off,
+                                                    const int32_t *__restrict__ tile_off, int sums,
                                                     int write_total)
 {
+    __shared__ unsigned long long t64[kSB / kWave];
+    int off = 0;
+    if (sums) {
+        int part = 0;
+        for (int64_t t = threadIdx.x; t < blockIdx.x; t += kSB) part += tile_off[t];
+        off = (int)block_sum_u64<kSB>((unsigned long long)(unsigned)part, t64);
+    } else if (tile_off) {
+        off = tile_off[blockIdx.x];
+    }
     const int64_t base = (int64_t)blockIdx.x * kST + (int64_t)threadIdx.x * kSI;
     int v[kSI];
     int s = 0;
@@ -64,7 +78,7 @@ __global__ __launch_bounds__(kSB) void k_scan_tiles(const int32_t *in, int32_t *
         s += v[i];
     }
     int total;
-    int run = block_exclusive_scan(s, &total) + (tile_off ? tile_off[blockIdx.x] : 0);
+    int run = block_exclusive_scan(s, &total) + off;
 #pragma unroll
     for (int i = 0; i < kSI; i++) {
         if (base + i < n) {
@@ -97,7 +111,7 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, bool out_has
     }
     const int64_t tiles = ceil_div(n, kST);
     if (tiles == 1) {
-        k_scan_tiles<<<1, kSB, 0, s>>>(in, out, n, nullptr, out_has_total ? 1 : 0);
+        k_scan_tiles<<<1, kSB, 0, s>>>(in, out, n, nullptr, 0, out_has_total ? 1 : 0);
         GS_HIP(hipGetLastError());
         return;
     }
@@ -105,9 +119,9 @@ void exclusive_scan_i32(const int32_t *in, int32_t *out, int64_t n, bool out_has
     sums.alloc((size_t)tiles * sizeof(int32_t), s);
     k_tile_sums<<<(unsigned)tiles, kSB, 0, s>>>(in, n, sums.as<int32_t>());
     GS_HIP(hipGetLastError());
-    exclusive_scan_i32(sums.as<int32_t>(), sums.as<int32_t>(), tiles, false, s);
-    k_scan_tiles<<<(unsigned)tiles, kSB, 0, s>>>(in, out, n, sums.as<int32_t>(),
-                                                  out_has_total ? 1 : 0);
+    const bool few = tiles <= kSumsTiles;
+    if (!few) exclusive_scan_i32(sums.as<int32_t>(), sums.as<int32_t>(), tiles, false, s);
+    k_scan_tiles<<<(unsigned)tiles, kSB, 0, s>>>(in, out, n, sums.as<int32_t>(), few ? 1 : 0, out_has_total ? 1 : 0);
     GS_HIP(hipGetLastError());
 }
 

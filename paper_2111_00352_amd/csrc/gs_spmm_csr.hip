@@ -657,28 +657,26 @@ __global__ __launch_bounds__(kBlock) void k_win_counts(const int32_t *__restrict
 }  // namespace
 
 // Locality of the row tiles: how many entries fall in their tile's window
-// for each candidate tile and halo (read back), for the LDS-staged kernel.
-// Counted for natural-order matrices without long rows (GS_CSR_WINDOW = off
-// skips it).
+// for each candidate tile and halo, for the LDS-staged kernel, into
+// counts[2 * kWinCands] [dev].
+static void enqueue_window_counts(const gs_matrix_ &m, const int32_t *rp, const int32_t *col,
+                                  unsigned long long *counts, hipStream_t s)
+{
+    GS_HIP(hipMemsetAsync(counts, 0, sizeof(unsigned long long) * 2 * kWinCands, s));
+    k_win_counts<<<stats_grid(m.R), kBlock, 0, s>>>(rp, col, m.R, m.C, counts);
+    GS_HIP(hipGetLastError());
+}
+
 void count_windows(gs_matrix_ &m, const int32_t *rp, const int32_t *col, hipStream_t s)
 {
     DevBuf cnt;
-    cnt.alloc(sizeof(unsigned long long) * 2 * kWinCands, s);
-    GS_HIP(hipMemsetAsync(cnt.p, 0, cnt.bytes, s));
-    k_win_counts<<<stats_grid(m.R), kBlock, 0, s>>>(rp, col, m.R, m.C, cnt.as<unsigned long long>());
-    GS_HIP(hipGetLastError());
     unsigned long long h[2 * kWinCands];
+    cnt.alloc(sizeof h, s);
+    enqueue_window_counts(m, rp, col, cnt.as<unsigned long long>(), s);
     GS_HIP(hipMemcpyAsync(h, cnt.p, sizeof h, hipMemcpyDeviceToHost, s));
     GS_HIP(hipStreamSynchronize(s));
     for (int i = 0; i < 2 * kWinCands; i++) m.win_entries[i] = (int64_t)h[i];
     m.win_counted = true;
-}
-
-void plan_windows(gs_matrix_ &m, hipStream_t s)
-{
-    const char *e = std::getenv("GS_CSR_WINDOW");
-    if ((e && std::string(e) == "off") || m.csr_sorted || m.csr_grouped || m.n_long_rows > 0 || m.Z == 0) return;
-    count_windows(m, m.row_ptr.as<int32_t>(), m.col.as<int32_t>(), s);
 }
 
 // Measured (F = 64..256): a tile pays for its staging only when most of its
@@ -719,19 +717,20 @@ bool pick_window(const gs_matrix_ &m, int64_t row_bytes, int &T, int &h)
 
 // Reference classes of the columns, for gathers that keep often referenced X
 // rows in the caches: counts per column, each column's class (one byte) and
-// the number of columns in each class (read back).  The class-tagged copy of
-// the column indices is made by the first SpMM that uses the classes.  Built
-// for skewed matrices (rows ordered by length; GS_CSR_HOTCOLD = on / off
-// forces it) whose column count fits the 27-bit column field.
-void plan_col_classes(gs_matrix_ &m, hipStream_t s)
+// the number of columns in each class into hist[16] [dev].  The class-tagged
+// copy of the column indices is made by the first SpMM that uses the classes.
+// Built for skewed matrices (rows ordered by length; GS_CSR_HOTCOLD = on / off
+// forces it) whose column count fits the 27-bit column field; false: no
+// classes.
+static bool enqueue_col_classes(gs_matrix_ &m, int32_t *hist, hipStream_t s)
 {
     const char *e = std::getenv("GS_CSR_HOTCOLD");
     const bool on = e && *e ? std::string(e) == "on" : m.csr_sorted;
     if (!on || m.Z == 0 || m.C > kColMask + 1) {
         m.col_counts.reset();
-        return;
+        return false;
     }
-    DevBuf cc = std::move(m.col_counts), hist;  // counted by feature extraction, if it ran
+    DevBuf cc = std::move(m.col_counts);  // counted by feature extraction, if it ran
     if (!cc.p) {
         cc.alloc((size_t)m.C * 4, s);
         column_counts(m.col.as<int32_t>(), m.C, m.Z, cc.as<int32_t>(), s);
@@ -739,16 +738,12 @@ void plan_col_classes(gs_matrix_ &m, hipStream_t s)
     const unsigned G = std::min(plan_grid(ceil_div(m.C, 4)), 512u);
     DevBuf part;
     part.alloc((size_t)G * 16 * 4, s);
-    hist.alloc(16 * 4, s);
     m.col_cls.alloc((size_t)m.C, s);
     k_col_classes<<<G, kBlock, 0, s>>>(cc.as<int32_t>(), m.C, m.col_cls.as<uint8_t>(), part.as<int32_t>());
     GS_HIP(hipGetLastError());
-    k_class_total<<<1, kBlock, 0, s>>>(part.as<int32_t>(), (int)G, hist.as<int32_t>());
+    k_class_total<<<1, kBlock, 0, s>>>(part.as<int32_t>(), (int)G, hist);
     GS_HIP(hipGetLastError());
-    int32_t h[16];
-    GS_HIP(hipMemcpyAsync(h, hist.p, sizeof h, hipMemcpyDeviceToHost, s));
-    GS_HIP(hipStreamSynchronize(s));
-    for (int c = 0; c < 16; c++) m.col_class_cols[c] = h[c];
+    return true;
 }
 
 void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
@@ -814,7 +809,16 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
     m.n_medium_rows = n_long - n_huge;
     m.n_short = R - n_long;
 
-    int32_t h_off[3] = {0, 0, 0};
+    // what the host needs of the plan, read back in one copy: the item counts
+    // at the tier boundaries, the columns of each class, the window counts
+    struct Back {
+        int32_t off[4];
+        int32_t cls[16];
+        unsigned long long win[2 * kWinCands];
+    } back = {};
+    DevBuf d_back;
+    d_back.alloc(sizeof back, s);
+    Back *db = d_back.as<Back>();
     DevBuf ka, kb, pa, pb, cnt;
     uint32_t *perm = nullptr;
     if (R > 0) {
@@ -838,16 +842,26 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
         k_plan_count<<<plan_grid(R), kBlock, 0, s>>>(rp, keys, perm, R, chunk, L, cnt.as<int32_t>());
         GS_HIP(hipGetLastError());
         exclusive_scan_i32(cnt.as<int32_t>(), cnt.as<int32_t>(), R, true, s);
-        DevBuf picked;
-        picked.alloc(sizeof h_off, s);
-        k_pick3<<<1, kWave, 0, s>>>(cnt.as<int32_t>(), m.n_medium_rows, n_long, R, picked.as<int32_t>());
+        k_pick3<<<1, kWave, 0, s>>>(cnt.as<int32_t>(), m.n_medium_rows, n_long, R, db->off);
         GS_HIP(hipGetLastError());
-        GS_HIP(hipMemcpyAsync(h_off, picked.p, sizeof h_off, hipMemcpyDeviceToHost, s));
+    }
+    const char *no_win = std::getenv("GS_CSR_WINDOW");
+    const bool classes = gathers && enqueue_col_classes(m, db->cls, s);
+    const bool windows = gathers && !(no_win && std::string(no_win) == "off") && !m.csr_sorted && !m.csr_grouped &&
+                         m.n_long_rows == 0 && m.Z > 0;
+    if (windows) enqueue_window_counts(m, rp, m.col.as<int32_t>(), db->win, s);
+    if (R > 0) {
+        GS_HIP(hipMemcpyAsync(&back, d_back.p, sizeof back, hipMemcpyDeviceToHost, s));
         GS_HIP(hipStreamSynchronize(s));
     }
-    m.n_medium_chunks = h_off[0];
-    m.n_long_chunks = h_off[1];
-    m.n_items = h_off[2];
+    m.n_medium_chunks = back.off[0];
+    m.n_long_chunks = back.off[1];
+    m.n_items = back.off[2];
+    if (classes) std::copy(back.cls, back.cls + 16, m.col_class_cols);
+    if (windows) {
+        std::copy(back.win, back.win + 2 * kWinCands, m.win_entries);
+        m.win_counted = true;
+    }
     m.csr_items.alloc((size_t)m.n_items * sizeof(int4), s);
     m.long_rows.alloc((size_t)n_long * 4, s);
     m.long_first.alloc((size_t)(n_long + 1) * 4, s);
@@ -858,10 +872,6 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
         GS_HIP(hipGetLastError());
     } else {
         GS_HIP(hipMemsetAsync(m.long_first.p, 0, 4, s));
-    }
-    if (gathers) {
-        plan_col_classes(m, s);
-        plan_windows(m, s);
     }
     m.csr_planned = true;
 }

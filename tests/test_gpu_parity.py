@@ -1010,6 +1010,27 @@ def test_column_count_paths_agree(monkeypatch, path):
     check_features(_random_case(50_000, 70_001, 1_200_000, 95, empty=0.05))
 
 
+@pytest.mark.parametrize("C,nnz", [(32_767, 16_384), (32_769, 16_383), (262_144, 70_000), (262_145, 70_000),
+                                   (70_001, 4_300_000)])
+def test_column_counts_by_windows(C, nnz):
+    # the column counts around the limits of their three paths: one window
+    # short of full, one column into the second, all eight, one over (atomics)
+    # and more entries than are read once per window (bucketed)
+    check_features(_random_case(20_000, C, nnz, 96))
+
+
+@pytest.mark.parametrize("C", [1, 255, 256, 257, 70_000])
+@pytest.mark.parametrize("n", [2_047, 2_048, 2_049, 20_000])
+def test_sort_and_scan_at_tile_edges(n, C):
+    # the radix sort's tiles hold 2,048 keys, the scan's 2,048 values: counts
+    # around them, column indices around one digit, an unsorted input
+    R = max(2 * n // C, 3)
+    case = _random_case(R, C, min(n, R * C), 97)
+    case.d_row, case.d_col, case.d_val = (_dev(a) for a in graphgen.shuffled(case.crow, case.ccol, case.cval, 98))
+    for fmt in ("csr", "csc", "coo"):
+        check_layout(case, fmt)
+
+
 @pytest.mark.parametrize("merge", ["0", "1"])
 def test_block_count_kernels_agree(monkeypatch, merge):
     # the 16x16 block count (features, BSR sizing) has an LDS-bitmap kernel and
