@@ -293,6 +293,16 @@ typedef struct {
 
 int gs_ctx_stats(gs_ctx c, gs_select_stats *out);
 
+/* Weight gradient of a GNN layer's dense transformation: out = H^T . G, a x b
+ * row-major (leading dimension b), H [dev] n x a with leading dimension ldh,
+ * G [dev] n x b with leading dimension ldg, fp32 products and sums on the matrix
+ * cores.  a, b at most 4096.  work [dev] holds at least the bytes that
+ * gs_weight_grad_workspace reports.  Deterministic, asynchronous on s, no
+ * allocation. */
+int gs_weight_grad_workspace(int64_t n, int64_t a, int64_t b, uint64_t *bytes);
+int gs_weight_grad(const float *H, int64_t ldh, const float *G, int64_t ldg, int64_t n, int64_t a, int64_t b,
+                   float *out, void *work, uint64_t work_bytes, gs_stream s);
+
 /* Thread-local description of the last error (never NULL). */
 const char *gs_last_error(void);
 

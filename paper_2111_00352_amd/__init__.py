@@ -132,6 +132,8 @@ def lib() -> ctypes.CDLL:
         "gs_select": (c_int, [_p, _u64, P(_Coo), _i64, _p, P(_i32)]),
         "gs_select_and_run": (c_int, [_p, _u64, P(_Coo), _p, _i64, _p, _i64, _i64, _p, P(_i32)]),
         "gs_ctx_stats": (c_int, [_p, P(_SelStats)]),
+        "gs_weight_grad_workspace": (c_int, [_i64, _i64, _i64, P(_u64)]),
+        "gs_weight_grad": (c_int, [_p, _i64, _p, _i64, _i64, _i64, _i64, _p, _p, _u64, _p]),
         "gs_last_error": (ctypes.c_char_p, []),
         "gs_abi_version": (c_int, []),
     }
@@ -351,6 +353,22 @@ def build_format(row, col, val, shape, fmt: str = "csr", bsr_block: int = 16,
         e.bytes_required = need.value
         raise e
     return Matrix(h.value)
+
+
+def weight_grad(H: torch.Tensor, G: torch.Tensor, stream=None) -> torch.Tensor:
+    """H^T G for tall H (n x a) and G (n x b) on the matrix cores (gs_weight_grad)."""
+    _check_dense(H, "H")
+    _check_dense(G, "G")
+    if H.shape[0] != G.shape[0]:
+        raise ValueError("H and G must have the same number of rows")
+    n, a, b = H.shape[0], H.shape[1], G.shape[1]
+    need = _u64()
+    _check(lib().gs_weight_grad_workspace(n, a, b, ctypes.byref(need)))
+    out = torch.empty((a, b), dtype=torch.float32, device=H.device)
+    work = torch.empty(need.value // 4, dtype=torch.float32, device=H.device)
+    _check(lib().gs_weight_grad(H.data_ptr(), H.stride(0), G.data_ptr(), G.stride(0), n, a, b, out.data_ptr(),
+                                work.data_ptr(), need.value, _stream(stream)))
+    return out
 
 
 def _features_dict(out: _Features) -> dict:

@@ -30,6 +30,7 @@ import time
 
 import torch
 
+import paper_2111_00352_amd as gs
 from paper_2111_00352_amd import SelectContext
 
 
@@ -74,11 +75,31 @@ def aggregate(Z: torch.Tensor, adj: Adjacency) -> torch.Tensor:
     return _Aggregate.apply(Z, adj)
 
 
+def _native_weight_grad(H: torch.Tensor, G: torch.Tensor) -> bool:
+    """Whether H^T G can run as one library call: plain fp32 tensors of the
+    current device whose product nothing records."""
+    for t in (H, G):
+        if (type(t) not in (torch.Tensor, torch.nn.Parameter) or not t.is_cuda or t.dtype != torch.float32
+                or t.dim() != 2 or t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.shape[1] == 0
+                or t.device.index != torch.cuda.current_device()
+                or (torch.is_grad_enabled() and t.requires_grad) or torch._C._functorch.is_functorch_wrapped_tensor(t)):
+            return False
+    if (torch.compiler.is_compiling() or torch.is_autocast_enabled() or torch.autograd.forward_ad._current_level >= 0
+            or H.shape[0] != G.shape[0] or H.shape[0] >= 1 << 31):
+        return False
+    return -(-H.shape[1] // 128) * -(-G.shape[1] // 128) <= 16
+
+
 def weight_grad(H: torch.Tensor, G: torch.Tensor, rows_per_chunk: int = 2048) -> torch.Tensor:
     """H^T G for tall H (n x a) and G (n x b): the n-long reduction is split
-    over row chunks (one batched product, then a sum over the chunks), which
-    keeps the GPU busy where a single a x b product with an n-long inner
-    dimension would not."""
+    over row chunks, which keeps the GPU busy where a single a x b product
+    with an n-long inner dimension would not.  fp32 operands on the GPU go to
+    the library's kernel (at n = 100,000, 128 x 128 it takes 50 us against
+    141 us for the batched product below, whose operand has to be transposed
+    first); others, wide products, and calls that autograd or a transform
+    records, to PyTorch."""
+    if _native_weight_grad(H, G):
+        return gs.weight_grad(H, G)
     n = H.shape[0]
     k = n // rows_per_chunk
     if k < 2:

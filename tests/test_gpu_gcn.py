@@ -151,3 +151,33 @@ def test_gcn_graph_replays_match_eager(mode):
         ctx.close()
     assert out[True][0] == out[False][0]
     assert np.array_equal(out[True][1], out[False][1]) and np.array_equal(out[True][2], out[False][2])
+
+
+@pytest.mark.parametrize("n", [1, 31, 64, 65, 1000, 20_003])
+@pytest.mark.parametrize("a,b", [(1, 1), (32, 33), (33, 32), (64, 64), (65, 31), (31, 65), (128, 128), (64, 128),
+                                 (128, 40), (20, 128), (129, 5), (200, 300)])
+def test_weight_grad_product(n, a, b):
+    # H^T G on the matrix cores around its tiles (32, 64, 128 columns), stages
+    # (32 rows) and chunks, with operands cut out of wider tensors at 4-byte
+    # offsets.  A sum of n products is at most n / 256 + 256 roundings deep:
+    # one chunk's rows, then the chunks.
+    rng = np.random.default_rng(n * 7 + a + b)
+    H = rng.standard_normal((n, a)).astype(np.float32)
+    G = rng.standard_normal((n, b)).astype(np.float32)
+    wide = torch.full((n, a + b + 3), float("nan"), device="cuda")
+    wide[:, 1:1 + a] = torch.from_numpy(H)
+    wide[:, 2 + a:2 + a + b] = torch.from_numpy(G)
+    got = gcn.weight_grad(wide[:, 1:1 + a], wide[:, 2 + a:2 + a + b]).cpu().numpy()
+    want = H.astype(np.float64).T @ G.astype(np.float64)
+    mag = np.abs(H).astype(np.float64).T @ np.abs(G).astype(np.float64)
+    assert got.shape == (a, b)
+    assert np.all(np.abs(got - want) <= (n / 256 + 256) * 2.0**-24 * mag + 1e-30)
+
+
+def test_weight_grad_leaves_recorded_products_to_pytorch():
+    H = torch.randn(5000, 24, device="cuda", requires_grad=True)
+    G = torch.randn(5000, 12, device="cuda")
+    gcn.weight_grad(H, G).sum().backward()
+    torch.testing.assert_close(H.grad, G.sum(1, keepdim=True).expand(-1, 24))
+    assert gcn.weight_grad(H.detach().double(), G.double()).dtype == torch.float64
+    assert gcn.weight_grad(H.detach().cpu(), G.cpu()).device.type == "cpu"
