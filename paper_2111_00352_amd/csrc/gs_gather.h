@@ -35,13 +35,16 @@ template <> struct Quad<double> {
     typedef d4 type;
 };
 
-// Lane t's value of entry J of the group's batch (J a compile-time lane).
-// Groups of 16 lanes and more hold the same batch of 16 entries in every DPP
-// row of 16 lanes, so one row_newbcast serves them; smaller groups hold a
-// batch of G entries.  No LDS round trip, unlike a shuffle.
-template <int J, int G> __device__ __forceinline__ int bcast_entry(int v)
+// Lane t's value of entry j0 + J of the group's batch.  A group of a whole wave
+// holds 64 entries and reads one into a scalar register; groups of 16 and 32
+// lanes hold the same batch of 16 entries in every DPP row of 16 lanes, so one
+// row_newbcast serves them; smaller groups hold a batch of G entries (j0 is 0
+// for all but whole waves).  No LDS round trip, unlike a shuffle.
+template <int J, int G> __device__ __forceinline__ int bcast_entry(int v, int j0 = 0)
 {
-    if constexpr (G == 4) {
+    if constexpr (G == 64) {
+        return __builtin_amdgcn_readlane(v, j0 + J);
+    } else if constexpr (G == 4) {
         return __builtin_amdgcn_update_dpp(0, v, J * 0x55, 0xf, 0xf, true);  // quad_perm: lane J of each quad
     } else if constexpr (G == 8) {
         const int lo = __builtin_amdgcn_update_dpp(0, v, 0x150 + J, 0xf, 0xf, true);
@@ -52,7 +55,7 @@ template <int J, int G> __device__ __forceinline__ int bcast_entry(int v)
 }
 
 // Entries per batch of a group of G lanes.
-template <int G> constexpr int kEntryBatch = G < 16 ? G : 16;
+template <int G> constexpr int kEntryBatch = G == 64 ? 64 : G < 16 ? G : 16;
 
 // Column quads of a lane: quad q starts at column c0 + 4 G q, the last one
 // of a width that is no multiple of 4 moved back to end at column F (the
@@ -118,24 +121,24 @@ __device__ __forceinline__ const float *x_at(const float *X, uint32_t lo, uint32
 // whose lane set `cold` are gathered non-temporally.
 template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, class Q, class A>
 __device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
-                                            const Q &cols, A *acc)
+                                            const Q &cols, A *acc, int j0 = 0)
 {
     f4u x[B][NQ];
     float vv[B];
     [&]<int... U>(std::integer_sequence<int, U...>) {
         (
             [&] {
-                const uint32_t lo = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo);
+                const uint32_t lo = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo, j0);
                 uint32_t hi = 0;
-                if constexpr (OFF == kOff64) hi = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi);
-                vv[U] = __int_as_float(bcast_entry<J0 + U, G>(__float_as_int(v)));
+                if constexpr (OFF == kOff64) hi = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi, j0);
+                vv[U] = __int_as_float(bcast_entry<J0 + U, G>(__float_as_int(v), j0));
                 int c = 0;
-                if constexpr (CLS) c = bcast_entry<J0 + U, G>(cold);
+                if constexpr (CLS) c = bcast_entry<J0 + U, G>(cold, j0);
                 if (MASKED) {
 #pragma unroll
                     for (int q = 0; q < NQ; q++) x[U][q] = f4u{0.f, 0.f, 0.f, 0.f};
                 }
-                if (!MASKED || J0 + U < t) {
+                if (!MASKED || j0 + J0 + U < t) {
                     if (CLS && c) {
                         // (the empty asm statements keep the compiler from merging the two branches' loads
                         // into one that has lost the non-temporal hint)
@@ -168,7 +171,15 @@ template <int J0, int U, int NQ, int G, int OFF, bool CLS, class Q, class A>
 __device__ __forceinline__ void gather_entries_of(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
                                                   const Q &cols, A *acc)
 {
-    if constexpr (J0 < kEntryBatch<G>) {
+    if constexpr (G == 64) {
+        const int n = __builtin_amdgcn_readfirstlane(t);  // one row to the wave
+        int j = 0;
+        for (; j + U <= n; j += U) gather_step<0, U, NQ, G, false, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
+        if (U > 1 && j < n && n - j <= U / 2)
+            gather_step<0, (U > 1 ? U / 2 : 1), NQ, G, true, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
+        else if (j < n)
+            gather_step<0, U, NQ, G, true, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
+    } else if constexpr (J0 < kEntryBatch<G>) {
         if (t >= J0 + U) {
             gather_step<J0, U, NQ, G, false, OFF, CLS>(ref, v, cold, t, X, cols, acc);
             gather_entries_of<J0 + U, U, NQ, G, OFF, CLS>(ref, v, cold, t, X, cols, acc);

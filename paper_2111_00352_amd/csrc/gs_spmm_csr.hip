@@ -40,7 +40,7 @@ constexpr int kBlock = 256;
 constexpr int kWinCands = 4;
 
 // The group's next batch of entries: [k, k + n) of the entry arrays, one per
-// lane (every 16 lanes of a wider group load the same 16).  Lanes past the
+// lane (every 16 lanes of a group of 32 load the same 16).  Lanes past the
 // last entry hold a valid column and the value -0.
 template <int G, int OFF, bool CLS> struct Batch {
     int c;
@@ -101,7 +101,10 @@ __device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, con
 //
 // GROUPED: the plan's group tier is active, so items may be rows of up to the
 // group limit, folded every kChainFold entries (compiled out otherwise).
-template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A>
+//
+// DEEP: 16 X rows in flight per lane group instead of 8, for small matrices
+// with long rows, whose time is the longest rows' chain of round trips.
+template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A, bool DEEP = false>
 __global__ __launch_bounds__(kBlock) void k_csr_rows(
     int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
     const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
@@ -111,8 +114,8 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
     constexpr int EB = kEntryBatch<G>;
-        // 8 float4 loads in flight per lane (4 where registers or L2 lines are short: fp64 sums, class gathers)
-    constexpr int U0 = CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
+    // 8 float4 loads in flight per lane (4 where registers or L2 lines are short: fp64 sums, class gathers)
+    constexpr int U0 = DEEP ? 16 : CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
     constexpr int U = U0 < EB ? U0 : EB;
     typedef typename Quad<A>::type A4;
     __shared__ A4 part[GPB][G * NQ];
@@ -126,14 +129,16 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     for (; t < n_long; t += gridDim.x) {
         const int64_t row = long_rows[t];
         const int64_t s = rp[row], e = rp[row + 1];
+        // pieces of at most `chunk` entries, shorter where that gives every group one
+        const int even = (int)((e - s + GPB - 1) / GPB + 15) / 16 * 16, piece = even < chunk ? even : chunk;
         A acc[CPL];
 #pragma unroll
         for (int i = 0; i < CPL; i++) acc[i] = 0;
-        for (int64_t cs = s + (int64_t)g * chunk; cs < e; cs += (int64_t)GPB * chunk) {
+        for (int64_t cs = s + (int64_t)g * piece; cs < e; cs += (int64_t)GPB * piece) {
             A part_acc[CPL];
 #pragma unroll
             for (int i = 0; i < CPL; i++) part_acc[i] = 0;
-            gather_span<NQ, G, U, OFF, CLS>(col, val, (int)cs, e - cs < chunk ? (int)(e - cs) : chunk, zlast, X, ldx,
+            gather_span<NQ, G, U, OFF, CLS>(col, val, (int)cs, e - cs < piece ? (int)(e - cs) : piece, zlast, X, ldx,
                                             cols, lane, hot_cls, part_acc);
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] += part_acc[i];
@@ -992,7 +997,14 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         float *work = n_huge ? (float *)work_for(m, fixed, (size_t)m.n_long_chunks * F * 4, s) : nullptr;
         auto rows = [&](auto cls_t, auto grp_t, const int32_t *cols) {
             constexpr bool CL = decltype(cls_t)::value, GR = decltype(grp_t)::value;
-            const auto fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float>;
+            auto fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float>;
+            // Measured with 16 rows in flight: power-law graphs of 90,000
+            // entries (F = 64) 12.4 -> 10.7 us and of 263,000 (F = 256) 42.9 ->
+            // 37.2, of 10^6 (F = 128) 61.1 -> 62.9; a 2,048-node random graph
+            // without long rows 5.1 -> 5.9.
+            if constexpr (CPL == 4 && !CL && !GR && OFF == kOff32)
+                if (m.csr_sorted && m.n_long_rows > 0 && m.Z <= (1 << 19))
+                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, true>;
             dim3 grid(rows_grid((const void *)fn, tiles, slices, CL ? 16 : m.csr_sorted ? 4 : 8), (unsigned)slices);
             fn<<<grid, kBlock, CL ? kClassLds : 0, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
                                        m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
