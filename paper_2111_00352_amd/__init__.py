@@ -164,14 +164,19 @@ def _install_torch_allocator(reinstall: bool = False):
             _check(lib().gs_set_allocator(ctypes.byref(_alloc_keep[0])))
         return
 
+    # (what torch.cuda.caching_allocator_alloc / _delete call for the current
+    # device, without their device switch: a first call makes some fifty of these)
+    raw_alloc = torch._C._cuda_cudaCachingAllocator_raw_alloc
+    raw_delete = torch._C._cuda_cudaCachingAllocator_raw_delete
+
     def _alloc(nbytes, stream, _ctx):
         try:
-            return torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+            return raw_alloc(nbytes, stream or 0)
         except Exception:  # out of memory -> the library reports GS_ERR_OOM
             return None
 
     def _free(ptr, _stream, _ctx):
-        torch.cuda.caching_allocator_delete(int(ptr))
+        raw_delete(ptr)
 
     a = _Allocator(_ALLOC_FN(_alloc), _FREE_FN(_free), None)
     _check(lib().gs_set_allocator(ctypes.byref(a)))
@@ -212,7 +217,7 @@ def set_allocator(alloc=None, free=None):
 
 def _stream(stream=None) -> int:
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
     return int(stream.cuda_stream if hasattr(stream, "cuda_stream") else stream)
 
 
@@ -220,14 +225,19 @@ def _ptr(t: torch.Tensor | None) -> int | None:
     return None if t is None or t.numel() == 0 else t.data_ptr()
 
 
-def _coo_struct(row, col, val, shape):
-    for t, dt in ((row, torch.int32), (col, torch.int32), (val, torch.float32)):
-        if not t.is_cuda or t.dtype != dt or not t.is_contiguous() or t.dim() != 1:
-            raise ValueError("row/col must be contiguous CUDA int32, val contiguous CUDA float32")
-    if not (row.numel() == col.numel() == val.numel()):
+def _coo_struct(row, col, val, shape, into=None):
+    """The gs_coo of the triplets (written to `into` if given)."""
+    if not (row.is_cuda and col.is_cuda and val.is_cuda and row.dtype == torch.int32 and col.dtype == torch.int32
+            and val.dtype == torch.float32 and row.dim() == 1 and col.dim() == 1 and val.dim() == 1
+            and row.is_contiguous() and col.is_contiguous() and val.is_contiguous()):
+        raise ValueError("row/col must be contiguous CUDA int32, val contiguous CUDA float32")
+    n = row.numel()
+    if not (n == col.numel() == val.numel()):
         raise ValueError("row, col and val must have the same length")
-    R, C = int(shape[0]), int(shape[1])
-    return _Coo(R, C, row.numel(), _ptr(row), _ptr(col), _ptr(val))
+    A = _Coo() if into is None else into
+    A.n_rows, A.n_cols, A.nnz = int(shape[0]), int(shape[1]), n
+    A.row, A.col, A.val = (row.data_ptr(), col.data_ptr(), val.data_ptr()) if n else (None, None, None)
+    return A
 
 
 def _opts(bsr_block=16, assume_canonical=False, max_bytes=None):
@@ -276,12 +286,14 @@ class Matrix:
             raise ValueError(f"X has {X.shape[0]} rows, A has {C} columns")
         F = X.shape[1]
         if out is None:
-            out = torch.empty((R, F), dtype=torch.float32, device=X.device)
-        _check_dense(out, "out")
-        if out.shape[0] != R or out.shape[1] != F:
-            raise ValueError("out has the wrong shape")
-        _check(lib().gs_spmm(self._h, _ptr(X), X.stride(0), _ptr(out), out.stride(0), F,
-                             _stream(stream)))
+            out = X.new_empty((R, F))
+        else:
+            _check_dense(out, "out")
+            if out.shape[0] != R or out.shape[1] != F:
+                raise ValueError("out has the wrong shape")
+        rc = lib().gs_spmm(self._h, _ptr(X), X.stride(0), _ptr(out), out.stride(0), F, _stream(stream))
+        if rc:
+            _check(rc)
         return out
 
     def spmm_noalloc(self, X: torch.Tensor, out: torch.Tensor, stream=None) -> torch.Tensor:
@@ -413,6 +425,11 @@ class SelectContext:
         _check(lib().gs_ctx_create(ctypes.byref(o), ctypes.byref(h)))
         self._h = h
         self._keep = {}
+        # the arguments of run(), written anew by every call (a context is not
+        # thread-safe): making them costs more than filling them in
+        self._coo, self._chosen = _Coo(), _i32()
+        self._coo_ref, self._chosen_ref = ctypes.byref(self._coo), ctypes.byref(self._chosen)
+        self._run = lib().gs_select_and_run
 
     def close(self):
         if self._h:
@@ -429,17 +446,17 @@ class SelectContext:
             out: torch.Tensor | None = None, stream=None):
         """Y = A.X in the selected format; returns (Y, format name)."""
         _check_dense(X, "X")
-        A = _coo_struct(row, col, val, shape)
-        R = int(shape[0])
+        _coo_struct(row, col, val, shape, self._coo)
         F = X.shape[1]
         if out is None:
-            out = torch.empty((R, F), dtype=torch.float32, device=X.device)
-        _check_dense(out, "out")
-        chosen = _i32()
-        _check(lib().gs_select_and_run(self._h, int(key), ctypes.byref(A), _ptr(X), X.stride(0),
-                                       _ptr(out), out.stride(0), F, _stream(stream),
-                                       ctypes.byref(chosen)))
-        return out, FORMAT_NAMES[chosen.value]
+            out = X.new_empty((int(shape[0]), F))
+        else:
+            _check_dense(out, "out")
+        rc = self._run(self._h, int(key), self._coo_ref, _ptr(X), X.stride(0), _ptr(out), out.stride(0), F,
+                       _stream(stream), self._chosen_ref)
+        if rc:
+            _check(rc)
+        return out, FORMAT_NAMES[self._chosen.value]
 
     def select(self, key: int, row, col, val, shape, F: int, stream=None) -> str:
         A = _coo_struct(row, col, val, shape)

@@ -15,7 +15,6 @@
 //              goes to left, else right; node 0 is the root)
 // Version 2 writes every real as a hexadecimal literal and leaves as
 // "L value", internal nodes as "feat thr left right".
-#include <cctype>
 #include <climits>
 #include <cmath>
 #include <cstdlib>
@@ -61,12 +60,26 @@ tree 4 3
 
 namespace {
 
+// Value of each hexadecimal digit, -1 for every other character.
+struct HexDigits {
+    signed char value[256];
+    constexpr HexDigits() : value()
+    {
+        for (int c = 0; c < 256; c++)
+            value[c] = (signed char)(c >= '0' && c <= '9'   ? c - '0'
+                                     : c >= 'a' && c <= 'f' ? c - 'a' + 10
+                                     : c >= 'A' && c <= 'F' ? c - 'A' + 10
+                                                            : -1);
+    }
+};
+constexpr HexDigits kHex;
+
 // Whitespace-separated tokens of the model text.  Numbers are read with
 // strtod / strtol (the conversions the C library defines; a double rounds
 // correctly) and must fill their whole token.
 struct Tokens {
     const char *p;
-    static bool space(char c) { return c == ' ' || c == '\n' || c == '\t' || c == '\r' || c == '\v' || c == '\f'; }
+    static bool space(char c) { return c == ' ' || (c >= '\t' && c <= '\r'); }
     bool word(const char *&s, const char *&e)
     {
         while (*p && space(*p)) p++;
@@ -74,6 +87,14 @@ struct Tokens {
         s = p;
         while (*p && !space(*p)) p++;
         e = p;
+        return true;
+    }
+    // Consumes a token that is the single character c.
+    bool is_char(char c)
+    {
+        while (*p && space(*p)) p++;
+        if (*p != c || (p[1] && !space(p[1]))) return false;
+        p++;
         return true;
     }
     bool is(const char *w)
@@ -94,56 +115,63 @@ struct Tokens {
     // without a general decimal conversion.  At most 53 significant bits.
     bool hexnum(double &v)
     {
-        const char *s, *e;
-        if (!word(s, e)) return false;
-        const char *p = s;
+        while (*p && space(*p)) p++;
         const bool neg = *p == '-';
         if (*p == '-' || *p == '+') p++;
-        if (e - p < 4 || p[0] != '0' || (p[1] != 'x' && p[1] != 'X')) return false;
+        if (p[0] != '0' || (p[1] != 'x' && p[1] != 'X')) return false;
         p += 2;
         uint64_t m = 0;
-        int frac = 0, nd = 0;
-        bool dot = false;
-        for (; p < e && *p != 'p' && *p != 'P'; p++) {
-            if (*p == '.') {
-                if (dot) return false;
-                dot = true;
-                continue;
-            }
-            const int d = std::isdigit((unsigned char)*p) ? *p - '0'
-                          : (*p >= 'a' && *p <= 'f') ? *p - 'a' + 10
-                          : (*p >= 'A' && *p <= 'F') ? *p - 'A' + 10
-                                                     : -1;
-            if (d < 0 || nd == 15) return false;
-            m = m * 16 + (uint64_t)d;
-            nd++;
-            if (dot) frac++;
+        int nd = 0, frac = 0;
+        auto digits = [&] {  // a run of hexadecimal digits
+            const char *const from = p;
+            for (int d; (d = kHex.value[(unsigned char)*p]) >= 0; p++) m = m << 4 | (uint64_t)d;
+            return (int)(p - from);
+        };
+        const char *const first = p;
+        nd = digits();
+        if (*p == '.') {
+            p++;
+            frac = digits();
+            nd += frac;
         }
+        if (nd > 15 || p - first > 16 || (*p != 'p' && *p != 'P')) return false;
+        p++;
         long long ex;
-        if (nd == 0 || p == e || (m >> 53) != 0 || !integer(p + 1, e, -1100, 1100, ex)) return false;
-        v = std::ldexp((double)m, (int)(ex - 4 * frac));
+        if (nd == 0 || (m >> 53) != 0 || !integer(-1100, 1100, ex)) return false;
+        // m is exact in a double, so one product with a power of two rounds as ldexp does
+        const int k = (int)(ex - 4 * frac);
+        if (k >= -1022 && k <= 1023) {
+            const uint64_t bits = (uint64_t)(k + 1023) << 52;
+            double scale;
+            std::memcpy(&scale, &bits, sizeof scale);
+            v = (double)m * scale;
+        } else {
+            v = std::ldexp((double)m, k);
+        }
         if (neg) v = -v;
         return true;
     }
-    // A decimal integer filling [s, e), within the int range.
-    static bool integer(const char *s, const char *e, long long lo, long long hi, long long &x)
+    // A decimal integer of at most 11 characters that ends its token, within
+    // [lo, hi], from the current character on.
+    bool integer(long long lo, long long hi, long long &x)
     {
-        const bool neg = s < e && *s == '-';
-        if (s < e && (*s == '-' || *s == '+')) s++;
-        if (s == e || e - s > 11) return false;
+        const bool neg = *p == '-';
+        if (*p == '-' || *p == '+') p++;
+        const char *const digits = p;
         x = 0;
-        for (; s < e; s++) {
-            if (*s < '0' || *s > '9') return false;
-            x = x * 10 + (*s - '0');
+        for (; *p >= '0' && *p <= '9'; p++) {
+            if (p - digits == 11) return false;
+            x = x * 10 + (*p - '0');
         }
+        if (p == digits || (*p && !space(*p))) return false;
         if (neg) x = -x;
         return x >= lo && x <= hi;
     }
     bool num(int &v)
     {
-        const char *s, *e;
         long long x;
-        if (!word(s, e) || !integer(s, e, INT_MIN, INT_MAX, x)) return false;
+        while (*p && space(*p)) p++;
+        if (!integer(INT_MIN, INT_MAX, x)) return false;
         v = (int)x;
         return true;
     }
@@ -206,12 +234,10 @@ void parse(const std::string &text, Model &m)
             if (ver == 1) {
                 ok = in.num(n.feat) && in.num(n.thr) && in.num(n.left) && in.num(n.right) && in.num(n.value);
             } else {
-                const char *save = in.p;
-                if (in.is("L")) {
+                if (in.is_char('L')) {
                     n = Node{-1, 0.0, 0, 0, 0.0};
                     ok = in.hexnum(n.value);
                 } else {
-                    in.p = save;
                     n.value = 0.0;
                     ok = in.num(n.feat) && n.feat >= 0 && in.hexnum(n.thr) && in.num(n.left) && in.num(n.right);
                 }

@@ -273,10 +273,13 @@ int gs_ctx_create(const gs_selector_opts *o, gs_ctx *out)
                 if (r.model_path) {
                     std::FILE *f = std::fopen(r.model_path, "rb");
                     if (!f) fail(GS_ERR_MODEL, "cannot open model file %s", r.model_path);
-                    text.clear();
-                    char buf[1 << 16];
-                    size_t n;
-                    while ((n = std::fread(buf, 1, sizeof buf, f)) > 0) text.append(buf, n);
+                    text.resize(1 << 18);  // (the shipped model is 160 kB: one read)
+                    size_t n, have = 0;
+                    while ((n = std::fread(text.data() + have, 1, text.size() - have, f)) > 0) {
+                        have += n;
+                        if (have == text.size()) text.resize(2 * have);
+                    }
+                    text.resize(have);
                     const bool bad = std::ferror(f) != 0;
                     std::fclose(f);
                     if (bad) fail(GS_ERR_MODEL, "cannot read model file %s", r.model_path);
