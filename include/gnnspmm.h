@@ -139,14 +139,12 @@ int gs_convert(gs_matrix A, int fmt, const gs_build_opts *opts, gs_stream s, gs_
  * otherwise).  X and Y must not overlap.  fp32 in and out; products and sums in fp32
  * (fused multiply-add), with every sequential chain kept short enough that
  * |Y - A.X| <= 1e-5 (|A|.|X|) + 1e-6 elementwise.  Deterministic: the same
- * inputs give bit-identical Y.  CSC is the exception: its columns scatter
- * into the rows of Y, so the products (exact in fp64) are added with fp64
- * atomics in a workspace and rounded to fp32 once; the order of the fp64
- * additions varies, which can change an fp32 result only where an fp64
- * sum sits on an fp32 rounding boundary.  Fully asynchronous on s; the
+ * inputs give bit-identical Y.  CSC sums its (in fp64 exact) products in fp64
+ * and rounds once; its handle keeps the matrix by rows beside its arrays for
+ * that.  Fully asynchronous on s; the
  * first call with a larger F than before may allocate a workspace (in
- * stream order).  That workspace (partial sums of split rows, COO carries,
- * the CSC accumulator) belongs to the handle: SpMM calls on one handle must
+ * stream order), a COO handle's first call its row pointers.  That workspace
+ * (partial sums of split rows) belongs to the handle: SpMM calls on one handle must
  * not overlap in time (issue them on one stream or order them); different
  * handles are independent. */
 int gs_spmm(gs_matrix A, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
@@ -156,7 +154,7 @@ int gs_spmm(gs_matrix A, const float *X, int64_t ldx, float *Y, int64_t ldy, int
  * capture, tight serving loops, harnesses that forbid allocation): gs_spmm
  * with the same arguments and the same result, bit for bit, that never calls
  * the allocator.  The F-dependent workspace that gs_spmm keeps in the handle
- * (partial sums of split CSR rows, the CSC fp64 accumulator) comes instead
+ * (partial sums of split CSR and CSC rows) comes instead
  * from a fixed array of GS_NOALLOC_SCRATCH_BYTES in device memory, one per
  * device, reserved when the library's code is loaded on that device and held
  * until the process ends.  Every call on one device shares that device's

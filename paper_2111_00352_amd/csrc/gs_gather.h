@@ -62,6 +62,7 @@ template <int G> constexpr int kEntryBatch = G == 64 ? 64 : G < 16 ? G : 16;
 // lanes that overlap then compute and store the same sums twice), quads past
 // the width folded onto it and not stored.
 template <int NQ, int G, bool FULL> struct Quads {
+    static constexpr bool kFull = FULL;
     int c0;               // (F is at most 2^24)
     int col[FULL ? 1 : NQ];
     bool live[FULL ? 1 : NQ];
@@ -103,8 +104,8 @@ template <int OFF> struct RowRef {
     }
 };
 
-// Address of quad q of the lane in the X row of entry J.
-template <int J, int G, int OFF, class Q>
+// Address of quad q of the lane in the X row at (hi, lo).
+template <int OFF, class Q>
 __device__ __forceinline__ const float *x_at(const float *X, uint32_t lo, uint32_t hi, const Q &cols, int q)
 {
     const char *b = reinterpret_cast<const char *>(X);
@@ -125,38 +126,50 @@ __device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int
 {
     f4u x[B][NQ];
     float vv[B];
+    uint32_t lo[B], hi[B];
+    int c[B];
     [&]<int... U>(std::integer_sequence<int, U...>) {
         (
             [&] {
-                const uint32_t lo = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo, j0);
-                uint32_t hi = 0;
-                if constexpr (OFF == kOff64) hi = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi, j0);
+                lo[U] = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo, j0);
+                hi[U] = 0;
+                if constexpr (OFF == kOff64) hi[U] = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi, j0);
                 vv[U] = __int_as_float(bcast_entry<J0 + U, G>(__float_as_int(v), j0));
-                int c = 0;
-                if constexpr (CLS) c = bcast_entry<J0 + U, G>(cold, j0);
-                if (MASKED) {
-#pragma unroll
-                    for (int q = 0; q < NQ; q++) x[U][q] = f4u{0.f, 0.f, 0.f, 0.f};
-                }
-                if (!MASKED || j0 + J0 + U < t) {
-                    if (CLS && c) {
-                        // (the empty asm statements keep the compiler from merging the two branches' loads
-                        // into one that has lost the non-temporal hint)
-                        asm volatile("");
-#pragma unroll
-                        for (int q = 0; q < NQ; q++)
-                            x[U][q] = __builtin_nontemporal_load(
-                                reinterpret_cast<const f4u *>(x_at<J0 + U, G, OFF>(X, lo, hi, cols, q)));
-                        asm volatile("");
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < NQ; q++)
-                            x[U][q] = *reinterpret_cast<const f4u *>(x_at<J0 + U, G, OFF>(X, lo, hi, cols, q));
-                    }
-                }
+                c[U] = 0;
+                if constexpr (CLS) c[U] = bcast_entry<J0 + U, G>(cold, j0);
             }(),
             ...);
     }(std::make_integer_sequence<int, B>{});
+#pragma unroll
+    for (int u = 0; u < B; u++)
+#pragma unroll
+        for (int q = 0; q < NQ; q++)
+            x[u][q] = MASKED ? f4u{0.f, 0.f, 0.f, 0.f} : __builtin_nondeterministic_value(x[u][q]);
+    // (lanes past the width load nothing: dead lanes cost data return, 12% at
+    // F = 156)
+    auto load = [&](int q) {
+#pragma unroll
+        for (int u = 0; u < B; u++) {
+            if (MASKED && j0 + J0 + u >= t) continue;
+            const f4u *p = reinterpret_cast<const f4u *>(x_at<OFF>(X, lo[u], hi[u], cols, q));
+            if (CLS && c[u]) {
+                // (the empty asm statements keep the compiler from merging the two branches' loads
+                // into one that has lost the non-temporal hint)
+                asm volatile("");
+                x[u][q] = __builtin_nontemporal_load(p);
+                asm volatile("");
+            } else {
+                x[u][q] = *p;
+            }
+        }
+    };
+#pragma unroll
+    for (int q = 0; q < NQ; q++) {
+        if constexpr (Q::kFull)
+            load(q);
+        else if (cols.ok(q))
+            load(q);
+    }
 #pragma unroll
     for (int u = 0; u < B; u++)
 #pragma unroll
@@ -238,9 +251,15 @@ __device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m, con
             for (int q = 0; q < NQ; q++) x[u][q] = f4u{0.f, 0.f, 0.f, 0.f};
             if (j + u >= m) v[u] = -0.0f;
         }
+        if (!MASKED) {
+#pragma unroll
+            for (int q = 0; q < NQ; q++) x[u][q] = __builtin_nondeterministic_value(x[u][q]);
+        }
         if (!MASKED || j + u < m) {
 #pragma unroll
-            for (int q = 0; q < NQ; q++) x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
+            for (int q = 0; q < NQ; q++)
+                if (Q::kFull || cols.ok(q))
+                    x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
         }
     }
     // FENCE: every load of the batch is issued before the first use.  Where
@@ -283,7 +302,11 @@ __device__ __forceinline__ void window_batch(int cj, float vj, int j, int m, con
         } else {
             const float *xp = X + (int64_t)cu * ldx;
 #pragma unroll
-            for (int q = 0; q < NQ; q++) x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
+            for (int q = 0; q < NQ; q++) {
+                x[u][q] = __builtin_nondeterministic_value(x[u][q]);
+                if (Q::kFull || cols.ok(q))
+                    x[u][q] = *reinterpret_cast<const f4u *>(xp + cols.base(q) + cols.step(q));
+            }
         }
     }
 #pragma unroll

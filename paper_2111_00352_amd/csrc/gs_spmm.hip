@@ -1,19 +1,20 @@
 // SpMM Y = A.X for each storage format (the aggregation of a GNN layer,
 // Sec. 2.1; formats of Sec. 2.2).  fp32 in and out, fused multiply-add.
 //
-// Shared layout of every kernel: a "row group" of G lanes (G in {8,16,32,64},
+// This file: the generic kernels (CSR, ELL and DIA of fewer than four columns;
+// BSR of any block size and width) and the per-format entry points.
+//
+// Shared layout of the kernels here: a "row group" of G lanes (G in {8,16,32,64},
 // always inside one 64-wide wavefront) owns one output row slice of G*VEC
 // columns, lane l holding columns l*VEC .. l*VEC+VEC-1 as one vector; X rows
-// are gathered with one VEC-wide load per lane, so a group reads G*VEC*4
-// contiguous bytes of an X row per nonzero (256 B at F = 64 up to 1 KiB at
-// F = 256).  grid.y walks F in slices of G*VEC columns when F is wider.
-// Index/value streams are read once and are loaded cooperatively by the
-// group (one entry per lane) and broadcast with cross-lane shuffles.
+// are gathered with one VEC-wide load per lane.  grid.y walks F in slices of
+// G*VEC columns when F is wider.  Index/value streams are read once and are
+// loaded cooperatively by the group (one entry per lane) and broadcast with
+// cross-lane shuffles.
 //
-// Every sequential fp32 chain is bounded (row chunks of at most 256 terms,
-// four interleaved accumulators), which keeps the rounding error far below
-// 1e-5 |A||X|; partial sums of split rows are combined in a fixed order, so
-// results are deterministic.
+// Every sequential fp32 chain is bounded (at most 128 terms), which keeps the
+// rounding error far below 1e-5 |A||X|; partial sums of split rows are combined
+// in a fixed order, so results are deterministic.
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>

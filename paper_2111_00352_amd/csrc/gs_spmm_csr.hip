@@ -102,9 +102,10 @@ __device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, con
 // GROUPED: the plan's group tier is active, so items may be rows of up to the
 // group limit, folded every kChainFold entries (compiled out otherwise).
 //
-// DEEP: 16 X rows in flight per lane group instead of 8, for small matrices
-// with long rows, whose time is the longest rows' chain of round trips.
-template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A, bool DEEP = false>
+// DEPTH: X rows in flight per lane group where it is not the 8 of CPL = 4:
+// 16 for small matrices with long rows, whose time is the longest rows' chain
+// of round trips, 4 for large ones.
+template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A, int DEPTH = 0>
 __global__ __launch_bounds__(kBlock) void k_csr_rows(
     int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
     const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     constexpr int NQ = CPL / 4;
     constexpr int EB = kEntryBatch<G>;
     // 8 float4 loads in flight per lane (4 where registers or L2 lines are short: fp64 sums, class gathers)
-    constexpr int U0 = DEEP ? 16 : CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
+    constexpr int U0 = DEPTH ? DEPTH : CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
     constexpr int U = U0 < EB ? U0 : EB;
     typedef typename Quad<A>::type A4;
     __shared__ A4 part[GPB][G * NQ];
@@ -1002,11 +1003,23 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
             // entries (F = 64) 12.4 -> 10.7 us and of 263,000 (F = 256) 42.9 ->
             // 37.2, of 10^6 (F = 128) 61.1 -> 62.9; a 2,048-node random graph
             // without long rows 5.1 -> 5.9.
-            if constexpr (CPL == 4 && !CL && !GR && OFF == kOff32)
-                if (m.csr_sorted && m.n_long_rows > 0 && m.Z <= (1 << 19))
-                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, true>;
+            // Long rows in numbers: 4 rows in flight and 4 workgroups per CU, as
+            // for class gathers: with 8 and 7 the lines in flight exceed the
+            // L2s.  13,283 uniform rows of 373 entries at F = 156 261 -> 216 us,
+            // 15,000 of 300 at F = 128 173 -> 152, 9,000 of 720 at F = 64 108.7
+            // -> 106.6; slower below (3,302 rows of 165 at F = 176 30 -> 34, 23
+            // entries a row 90 -> 94, F = 32 143 -> 145).
+            bool few = CL;
+            if constexpr (CPL == 4 && !CL && !GR && OFF == kOff32) {
+                if (m.csr_sorted && m.n_long_rows > 0 && m.Z <= (1 << 19)) {
+                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, 16>;
+                } else if (m.Z >= 128 * m.R && F >= 64 && m.Z >= (1ll << 28) / F) {
+                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, 4>;
+                    few = true;
+                }
+            }
             dim3 grid(rows_grid((const void *)fn, tiles, slices, CL ? 16 : m.csr_sorted ? 4 : 8), (unsigned)slices);
-            fn<<<grid, kBlock, CL ? kClassLds : 0, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
+            fn<<<grid, kBlock, few ? kClassLds : 0, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
                                        m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
                                        cols ? cols : m.row_ptr.as<int32_t>(),
                                        m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),

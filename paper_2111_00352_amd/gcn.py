@@ -13,9 +13,8 @@ per adjacency key, the format predicted per call since the feature width F is
 one of the predictor's inputs, converted at most once per key).  A^T is a
 second key built from the same triplets with rows and columns exchanged, or
 the same key when the caller declares A symmetric (GCN-normalised adjacencies
-are).  The dense products H W and their gradients are PyTorch fp32 matmuls
-(the weight gradient H^T G, an n-long reduction, split over row chunks);
-ReLU and the loss are PyTorch element-wise operations.
+are).  The dense products H W and G W^T are PyTorch fp32 matmuls, the weight
+gradient H^T G (an n-long reduction) is the library's matrix-core kernel; ReLU and the loss are PyTorch element-wise operations.
 
 Command line (end-to-end timing of one workload):
     python -m paper_2111_00352_amd.gcn --config 2 --epochs 10

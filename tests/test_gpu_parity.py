@@ -280,6 +280,15 @@ def test_csr_group_tier(monkeypatch, group_row, sort):
         check_spmm(case, case.build(fmt), graphgen.features_x(case.C, 64, 99, "normal"))
 
 
+@pytest.mark.parametrize("F", [250, 256])
+def test_csr_many_long_rows_few_in_flight(F):
+    # 2^28 gathered floats in rows of 128 entries and more on average: the row
+    # kernel's variant with 4 X rows in flight (full and ragged widths)
+    case = _uniform_long_rows(2600, 6000, 150, 700, 93)
+    assert case.crow.size * F >= 1 << 28
+    check_spmm(case, case.build("csr"), graphgen.features_x(case.C, F, 94, "normal"))
+
+
 @pytest.mark.parametrize("cpl", ["", "4", "16"])
 @pytest.mark.parametrize("ranges", ["", "1", "3", "50", "997"])
 def test_coo_ranges_split_rows(monkeypatch, ranges, cpl):
