@@ -120,14 +120,15 @@ int gs_set_allocator(const gs_allocator *a);
  *   BSR  b = bsr_block; block_ptr[ceil(n_rows/b)+1]; block_col[nb] ascending per
  *        block row; block_val[nb*b*b], A[r,c] at blk*b*b + (r%b)*b + c%b,
  *        every other slot +0.0f (the matrix is zero-padded to whole blocks)
- * opts may be NULL (defaults).  Synchronises s once (sizes are needed on the
- * host).  On GS_ERR_INFEASIBLE *bytes_required (if non-NULL) holds the bytes
+ * opts may be NULL (defaults).  Synchronises s where sizes are needed on the
+ * host, but may return before the last kernels have run.  On GS_ERR_INFEASIBLE *bytes_required (if non-NULL) holds the bytes
  * the format would need; on success it holds the bytes allocated. */
 int gs_build_format(const gs_coo *A, int fmt, const gs_build_opts *opts, gs_stream s,
                     gs_matrix *out, uint64_t *bytes_required);
 
 /* Converts an already built matrix into another format without re-checking
- * it.  Same layouts, options and errors as gs_build_format. */
+ * it.  Same layouts, options and errors as gs_build_format.  A may still be read
+ * on s when the call returns. */
 int gs_convert(gs_matrix A, int fmt, const gs_build_opts *opts, gs_stream s, gs_matrix *out,
                uint64_t *bytes_required);
 
@@ -199,10 +200,10 @@ int gs_get_array(gs_matrix A, int which, const void **dev_ptr, uint64_t *bytes);
 int gs_copy_array(gs_matrix A, int which, void *dst, uint64_t dst_bytes, gs_stream s);
 
 /* Frees A's device arrays and workspace through the hooks that allocated
- * them, in the order of the stream A was built on.  When A was last read on
- * another stream (gs_spmm, gs_spmm_noalloc, gs_to_coo, gs_copy_array), the
- * call first waits for that work to finish, so no later allocation on the
- * build stream can reuse the memory under it.  Work captured into a graph
+ * them, in the order of the stream A was built on.  When A was read on
+ * other streams (gs_spmm, gs_spmm_noalloc, gs_to_coo, gs_convert, gs_copy_array),
+ * the call first waits for the last such work on each of them, so no later
+ * allocation on the build stream can reuse the memory under it.  Work captured into a graph
  * is not tracked: destroy A only after the graph's last replay.  NULL is
  * ignored. */
 void gs_destroy(gs_matrix A);

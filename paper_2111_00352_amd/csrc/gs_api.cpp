@@ -67,6 +67,7 @@ void run_spmm(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s, const WorkArea *fixed)
 {
     if (m.R == 0) return;
+    const NoteUse used{m, s};
     switch (m.fmt) {
     case GS_CSR: spmm_csr(m, X, ldx, Y, ldy, F, s, fixed); break;
     case GS_COO: spmm_coo(m, X, ldx, Y, ldy, F, s, fixed); break;
@@ -76,7 +77,6 @@ void run_spmm(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
     case GS_CSC: spmm_csc(m, X, ldx, Y, ldy, F, s, fixed); break;
     default: fail(GS_ERR_INVALID_ARG, "corrupt matrix handle");
     }
-    note_use(m, s);
 }
 
 }  // namespace gs
@@ -118,6 +118,7 @@ int gs_convert(gs_matrix A, int fmt, const gs_build_opts *opts, gs_stream stream
         if (fmt < 0 || fmt >= GS_NUM_FORMATS) fail(GS_ERR_INVALID_ARG, "unknown format %d", fmt);
         const gs_build_opts o = resolve_opts(opts);
         hipStream_t s = (hipStream_t)stream;
+        const NoteUse used{*A, s};  // (a conversion may return before it has read A)
         if (A->fmt == GS_CSR) {
             *out = convert_from_csr(*A, fmt, o.bsr_block, o.max_bytes, s, bytes_required);
             return;
@@ -147,8 +148,8 @@ int gs_to_coo(gs_matrix A, int32_t *row, int32_t *col, float *val, gs_stream str
     return guarded([&] {
         if (!A) fail(GS_ERR_INVALID_ARG, "null matrix handle");
         if (A->Z > 0 && (!row || !col || !val)) fail(GS_ERR_INVALID_ARG, "null output array");
+        const NoteUse used{*A, (hipStream_t)stream};
         to_coo(*A, row, col, val, (hipStream_t)stream);
-        note_use(*A, (hipStream_t)stream);
     });
 }
 
@@ -176,6 +177,7 @@ int gs_matrix_features(gs_matrix A, gs_stream stream, gs_features *out)
     return guarded([&] {
         if (!A || !out) fail(GS_ERR_INVALID_ARG, "null argument");
         hipStream_t s = (hipStream_t)stream;
+        const NoteUse used{*A, s};
         if (A->fmt == GS_CSR) {
             features_from_csr(*A, s, out);
             return;

@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <mutex>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/gnnspmm.h"
@@ -89,6 +91,20 @@ struct DevBuf {
 
 struct WorkArea;
 
+// An event after the last call on each stream (calls that only read a handle
+// may come from several threads at once).
+class StreamUses {
+public:
+    // Records s, which is left out while it is `home` and no other stream was recorded.
+    void record(hipStream_t s, hipStream_t home) noexcept;
+    // Waits for the recorded work.
+    void wait() noexcept;
+
+private:
+    std::mutex mu_;
+    std::vector<std::pair<hipStream_t, hipEvent_t>> last_;
+};
+
 // ------------------------------------------------------------ matrix handle
 
 }  // namespace gs
@@ -158,24 +174,20 @@ struct gs_matrix_ {
 
     uint64_t device_bytes = 0;
 
-    // Work that reads the handle's arrays on a stream other than `stream`
-    // (an SpMM, to_coo or an array copy): an event recorded after the last
-    // such call, waited for before the arrays are freed (they are freed in
-    // `stream` order, which does not cover other streams).
-    // Once there was one, calls on `stream` are recorded too: plans and
-    // workspaces may have been allocated on the other stream.
-    hipEvent_t last_foreign = nullptr;
-    bool foreign = false;
+    // Work that reads the handle's arrays on a stream other than `stream` (an
+    // SpMM, to_coo, a conversion or an array copy): per stream an event
+    // recorded after its last such call, waited for before the arrays are
+    // freed (they are freed in `stream` order, which does not cover other
+    // streams).  Once there was one, calls on `stream` are recorded too: plans
+    // and workspaces may have been allocated on the other stream.
+    gs::StreamUses uses;
 
     gs_matrix_() = default;
     gs_matrix_(const gs_matrix_ &) = delete;
     gs_matrix_ &operator=(const gs_matrix_ &) = delete;
     ~gs_matrix_()
     {
-        if (last_foreign) {
-            (void)hipEventSynchronize(last_foreign);
-            (void)hipEventDestroy(last_foreign);
-        }
+        uses.wait();
         delete by_rows;
     }
 };
@@ -314,6 +326,8 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
 // Workgroups of 256 threads the device keeps resident at full occupancy
 // (compute units x 8), queried once.
 int resident_workgroups();
+// Whether s is being captured into a graph (or may not be asked, for a capture).
+bool is_capturing(hipStream_t s);
 int compute_units();
 // Workgroups of `threads` threads of a kernel (without dynamic LDS) that one
 // compute unit keeps resident, queried once per kernel.
@@ -352,10 +366,14 @@ struct WorkArea {
 // in stream order.
 void *work_for(gs_matrix_ &m, const WorkArea *fixed, size_t bytes, hipStream_t s);
 
-// Records that work reading m's arrays was enqueued on s (see
-// gs_matrix_::last_foreign); nothing when s is m's own stream or is being
-// captured into a graph (replays are ordered by the caller).
-void note_use(gs_matrix_ &m, hipStream_t s);
+// Records, when it goes out of scope, that work on m was enqueued on s (see
+// gs_matrix_::uses), also where an error ended the call halfway; nothing while
+// s is being captured into a graph (replays are ordered by the caller).
+struct NoteUse {
+    gs_matrix_ &m;
+    hipStream_t s;
+    ~NoteUse() { m.uses.record(s, m.stream); }
+};
 
 // Argument checks of gs_spmm (throws Error) and the format dispatch.
 void check_spmm_args(const gs_matrix_ *A, const float *X, int64_t ldx, const float *Y, int64_t ldy,

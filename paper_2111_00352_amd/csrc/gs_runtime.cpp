@@ -1,4 +1,5 @@
 // Error reporting, device allocation and matrix-handle plumbing of the C ABI.
+#include <algorithm>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
@@ -92,18 +93,41 @@ void *work_for(gs_matrix_ &m, const WorkArea *fixed, size_t bytes, hipStream_t s
     return m.work.p;
 }
 
-void note_use(gs_matrix_ &m, hipStream_t s)
+bool is_capturing(hipStream_t s)
 {
-    if (s != m.stream) m.foreign = true;
-    if (!m.foreign) return;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &cs) != hipSuccess) {  // e.g. the legacy stream during a capture
+    if (hipStreamIsCapturing(s, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();  // the legacy stream during a capture
+    return true;
+}
+
+void StreamUses::record(hipStream_t s, hipStream_t home) noexcept
+{
+    std::lock_guard<std::mutex> lock(mu_);
+    if ((s == home && last_.empty()) || is_capturing(s)) return;
+    auto it = std::find_if(last_.begin(), last_.end(), [s](const auto &u) { return u.first == s; });
+    try {
+        if (it == last_.end()) {
+            last_.reserve(last_.size() + 1);
+            hipEvent_t e;
+            GS_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+            last_.emplace_back(s, e);
+            it = last_.end() - 1;
+        }
+        GS_HIP(hipEventRecord(it->second, s));
+    } catch (...) {  // no event: wait here instead
         (void)hipGetLastError();
-        return;
+        (void)hipStreamSynchronize(s);
     }
-    if (cs != hipStreamCaptureStatusNone) return;
-    if (!m.last_foreign) GS_HIP(hipEventCreateWithFlags(&m.last_foreign, hipEventDisableTiming));
-    GS_HIP(hipEventRecord(m.last_foreign, s));
+}
+
+void StreamUses::wait() noexcept
+{
+    for (auto &u : last_) {
+        (void)hipEventSynchronize(u.second);
+        (void)hipEventDestroy(u.second);
+    }
+    last_.clear();
 }
 
 // Device properties, read once (thread-safe static initialisation; a failed
@@ -230,10 +254,9 @@ int gs_copy_array(gs_matrix A, int which, void *dst, uint64_t dst_bytes, gs_stre
         return GS_ERR_INVALID_ARG;
     }
     return guarded([&] {
-        if (bytes) {
-            GS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, (hipStream_t)s));
-            note_use(*A, (hipStream_t)s);
-        }
+        if (!bytes) return;
+        const NoteUse used{*A, (hipStream_t)s};
+        GS_HIP(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToDevice, (hipStream_t)s));
     });
 }
 

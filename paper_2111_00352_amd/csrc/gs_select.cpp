@@ -112,11 +112,13 @@ gs_matrix_ &ensure_built(gs_ctx_ &c, Entry &e, int fmt, hipStream_t s)
 {
     if (!e.built[fmt]) {
         const double t0 = now_s();
+        const NoteUse used{*e.built[GS_CSR], s};
         e.built[fmt] = convert_from_csr(*e.built[GS_CSR], fmt, c.opts.bsr_block, c.opts.max_bytes, s,
                                         nullptr);
         e.t_convert[fmt] = now_s() - t0;
     } else if (fmt == GS_CSR && !e.built[fmt]->csr_planned) {
         const double t0 = now_s();
+        const NoteUse used{*e.built[fmt], s};
         plan_csr(*e.built[fmt], s);
         e.t_convert[fmt] = now_s() - t0;
     }

@@ -637,6 +637,49 @@ def test_destroy_right_after_spmm_on_another_stream():
         del junk
 
 
+def _busy(stream):
+    # tens of milliseconds of work that later calls on the stream queue behind
+    with torch.cuda.stream(stream):
+        torch.cuda._sleep(50_000_000)
+
+
+@pytest.mark.parametrize("src", FMTS)
+@pytest.mark.parametrize("dst", FMTS)
+def test_destroy_waits_for_a_conversion_on_another_stream(src, dst):
+    # a handle converted on a second stream behind other work, then destroyed:
+    # whether or not the conversion waited for its copies, nothing of it is
+    # outstanding once the source's arrays go back to the allocator
+    case = _random_case(300, 310, 2500, 31)
+    m = case.build(src)
+    torch.cuda.synchronize()
+    s2 = torch.cuda.Stream()
+    _busy(s2)
+    with torch.cuda.stream(s2):
+        m2 = m.convert(dst)
+    m.close()
+    assert s2.query(), "destroyed under a conversion that still reads it"
+    r, c, v = (_host(t) for t in m2.to_coo())
+    assert (r == case.crow).all() and (c == case.ccol).all() and (_bits(v) == _bits(case.cval)).all()
+
+
+@pytest.mark.parametrize("fmt", ["csr", "coo", "csc"])
+def test_destroy_waits_for_every_stream_that_read(fmt):
+    # reads on two other streams, then an SpMM on the handle's own: the
+    # later record replaces neither of the earlier ones
+    case = _random_case(300, 310, 2500, 32)
+    m = case.build(fmt)
+    Xd = _dev(graphgen.features_x(case.C, 16, 33, "normal"))
+    torch.cuda.synchronize()
+    others = [torch.cuda.Stream() for _ in range(2)]
+    for s2 in others:
+        _busy(s2)
+        with torch.cuda.stream(s2):
+            m.to_coo()
+    m.spmm(Xd)
+    m.close()
+    assert all(s2.query() for s2 in others), "destroyed under a copy that still reads it"
+
+
 # -------------------------------------------------------------- conversion
 
 @pytest.mark.parametrize("src", FMTS)
