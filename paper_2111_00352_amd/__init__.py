@@ -368,18 +368,27 @@ def build_format(row, col, val, shape, fmt: str = "csr", bsr_block: int = 16,
 
 
 def weight_grad(H: torch.Tensor, G: torch.Tensor, stream=None) -> torch.Tensor:
-    """H^T G for tall H (n x a) and G (n x b) on the matrix cores (gs_weight_grad)."""
+    """H^T G for tall H (n x a) and G (n x b) on the matrix cores (gs_weight_grad).
+    The result and the workspace, which is given back on return, belong to `stream`."""
     _check_dense(H, "H")
     _check_dense(G, "G")
     if H.shape[0] != G.shape[0]:
         raise ValueError("H and G must have the same number of rows")
+    if H.device != G.device:
+        raise ValueError("H and G must be on the same device")
+    if stream is not None and _stream(stream) != _stream():
+        if not isinstance(stream, torch.cuda.Stream):
+            raw = _stream(stream)
+            stream = torch.cuda.ExternalStream(raw) if raw else torch.cuda.default_stream()
+        with torch.cuda.stream(stream):
+            return weight_grad(H, G)
     n, a, b = H.shape[0], H.shape[1], G.shape[1]
     need = _u64()
     _check(lib().gs_weight_grad_workspace(n, a, b, ctypes.byref(need)))
     out = torch.empty((a, b), dtype=torch.float32, device=H.device)
     work = torch.empty(need.value // 4, dtype=torch.float32, device=H.device)
     _check(lib().gs_weight_grad(H.data_ptr(), H.stride(0), G.data_ptr(), G.stride(0), n, a, b, out.data_ptr(),
-                                work.data_ptr(), need.value, _stream(stream)))
+                                work.data_ptr(), need.value, _stream()))
     return out
 
 

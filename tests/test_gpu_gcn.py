@@ -181,3 +181,22 @@ def test_weight_grad_leaves_recorded_products_to_pytorch():
     torch.testing.assert_close(H.grad, G.sum(1, keepdim=True).expand(-1, 24))
     assert gcn.weight_grad(H.detach().double(), G.double()).dtype == torch.float64
     assert gcn.weight_grad(H.detach().cpu(), G.cpu()).device.type == "cpu"
+
+
+@pytest.mark.parametrize("handle", [False, True])
+def test_weight_grad_on_another_stream_keeps_its_workspace(handle):
+    # called for a stream that is busy: what the call allocates belongs to that
+    # stream, so memory the current stream takes next is not what the kernels
+    # queued there will still write and read
+    H = torch.randn(5000, 64, device="cuda")
+    G = torch.randn(5000, 64, device="cuda")
+    want, mag = H.double().T @ G.double(), H.double().abs().T @ G.double().abs()
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side):
+        torch.cuda._sleep(50_000_000)
+    got = gs.weight_grad(H, G, stream=side.cuda_stream if handle else side)
+    taken = [torch.full((1 << k,), float("nan"), device="cuda") for k in range(8, 22) for _ in range(4)]
+    torch.cuda.synchronize()
+    assert all(bool(t.isnan().all()) for t in taken)
+    assert bool(((got.double() - want).abs() <= 256 * U * mag).all())  # sums of 64 rows, then 79 of them
