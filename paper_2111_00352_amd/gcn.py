@@ -28,6 +28,7 @@ import sys
 import time
 
 import torch
+from torch.utils._device import DeviceContext
 
 import paper_2111_00352_amd as gs
 from paper_2111_00352_amd import SelectContext
@@ -74,12 +75,23 @@ def aggregate(Z: torch.Tensor, adj: Adjacency) -> torch.Tensor:
     return _Aggregate.apply(Z, adj)
 
 
+def _recording() -> bool:
+    """Whether something watches PyTorch's own operations: a trace, a dispatch
+    mode, a function mode (other than the one that only sets a device)."""
+    if torch._C._get_tracing_state() is not None or torch._C._len_torch_dispatch_stack() > 0:
+        return True
+    return torch._C._len_torch_function_stack() > 0 and any(
+        type(m) is not DeviceContext for m in torch.overrides._get_current_function_mode_stack())
+
+
 def _native_weight_grad(H: torch.Tensor, G: torch.Tensor) -> bool:
     """Whether H^T G can run as one library call: plain fp32 tensors of the
     current device whose product nothing records."""
+    if _recording():
+        return False
     for t in (H, G):
         if (type(t) not in (torch.Tensor, torch.nn.Parameter) or not t.is_cuda or t.dtype != torch.float32
-                or t.dim() != 2 or t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.shape[1] == 0
+                or t.layout != torch.strided or t.is_neg() or t.dim() != 2 or t.stride(1) != 1 or t.stride(0) < t.shape[1] or t.shape[1] == 0
                 or t.device.index != torch.cuda.current_device()
                 or (torch.is_grad_enabled() and t.requires_grad) or torch._C._functorch.is_functorch_wrapped_tensor(t)):
             return False

@@ -174,6 +174,38 @@ def test_weight_grad_product(n, a, b):
     assert np.all(np.abs(got - want) <= (n / 256 + 256) * 2.0**-24 * mag + 1e-30)
 
 
+def test_weight_grad_leaves_watched_products_to_pytorch():
+    # a trace replays the product on other operands, a dispatch mode and a
+    # function mode see it, a negated view keeps its sign
+    from torch.overrides import TorchFunctionMode
+    from torch.utils.flop_counter import FlopCounterMode
+
+    class Seen(TorchFunctionMode):
+        n = 0
+
+        def __torch_function__(self, func, types, args=(), kwargs=None):
+            Seen.n += getattr(func, "__name__", "") in ("bmm", "matmul", "__matmul__")
+            return func(*args, **(kwargs or {}))
+
+    H, G, H2, G2 = (torch.randn(5000, k, device="cuda") for k in (24, 12, 24, 12))
+    prod = lambda h, g: h.double().T @ g.double()  # noqa: E731
+
+    def near(x, want):  # 5,000 products of normal values, of magnitude 3,200 in all, in any order
+        assert float((x.double() - want).abs().max()) <= 5000 * U * 3500
+
+    traced = torch.jit.trace(lambda h, g: gcn.weight_grad(h, g), (H, G), check_trace=False)
+    near(traced(H2, G2), prod(H2, G2))
+    with FlopCounterMode(display=False) as flops:
+        gcn.weight_grad(H, G)
+    assert flops.get_total_flops() > 0
+    with Seen():
+        gcn.weight_grad(H, G)
+    assert Seen.n > 0
+    near(gcn.weight_grad(torch._neg_view(H), G), -prod(H, G))
+    with torch.device("cuda"):  # (only sets a device: the library's kernel)
+        assert gcn._native_weight_grad(H, G)
+
+
 def test_weight_grad_leaves_recorded_products_to_pytorch():
     H = torch.randn(5000, 24, device="cuda", requires_grad=True)
     G = torch.randn(5000, 12, device="cuda")
