@@ -22,6 +22,9 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kRows = 32;  // rows of H and G per stage
+// Rows after which the running sums of a workgroup join their totals, so that
+// no chain grows with n (512 x 512 leaves a workgroup n / 32 rows).
+constexpr int kFoldRows = 1024;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Rows [r0, r0 + kRows) x columns [c0, c0 + W) of M (n x c, leading dimension
@@ -62,8 +65,8 @@ template <int W> __device__ __forceinline__ void store_stage(float *lds, const f
 // MT x NT (of the a x b product), four waves WM x WN x KS: a wave owns
 // MT / WM x NT / WN of the tile and every KS-th pair of rows, and writes its
 // sums as partial (x * KS + ks).  The next stage's rows are loaded while the
-// current one's are multiplied.
-template <int MT, int NT, int WM, int WN>
+// current one's are multiplied.  FOLD: per exceeds kFoldRows.
+template <int MT, int NT, int WM, int WN, bool FOLD>
 __global__ __launch_bounds__(kBlock) void k_tn_partial(const float *__restrict__ H, int64_t ldh,
                                                        const float *__restrict__ G, int64_t ldg, int64_t n, int a, int b,
                                                        int64_t per, float *__restrict__ part)
@@ -76,13 +79,23 @@ __global__ __launch_bounds__(kBlock) void k_tn_partial(const float *__restrict__
     const int nbt = (b + NT - 1) / NT;
     const int m0 = (blockIdx.y / nbt) * MT, n0 = (blockIdx.y % nbt) * NT;
     const int64_t r0 = (int64_t)blockIdx.x * per, r1 = r0 + per < n ? r0 + per : n;
-    f32x16 acc[TM][TN];
+    f32x16 acc[TM][TN], tot[FOLD ? TM : 1][FOLD ? TN : 1];
 #pragma unroll
     for (int i = 0; i < TM; i++)
 #pragma unroll
-        for (int j = 0; j < TN; j++)
+        for (int j = 0; j < TN; j++) {
+            acc[i][j] = f32x16{};
+            if constexpr (FOLD) tot[i][j] = f32x16{};
+        }
+    auto fold = [&] {
 #pragma unroll
-            for (int e = 0; e < 16; e++) acc[i][j][e] = 0.0f;
+        for (int i = 0; i < TM; i++)
+#pragma unroll
+            for (int j = 0; j < TN; j++) {
+                tot[FOLD ? i : 0][FOLD ? j : 0] += acc[i][j];
+                acc[i][j] = FOLD ? f32x16{} : acc[i][j];
+            }
+    };
     f4u hv[kRows * MT / 4 / kBlock], gv[kRows * NT / 4 / kBlock];
     load_stage<MT>(hv, H, ldh, r0, r1, m0, a);
     load_stage<NT>(gv, G, ldg, r0, r1, n0, b);
@@ -109,7 +122,10 @@ __global__ __launch_bounds__(kBlock) void k_tn_partial(const float *__restrict__
                 for (int j = 0; j < TN; j++)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
+        if constexpr (FOLD)
+            if ((r - r0) % kFoldRows == kFoldRows - kRows) fold();
     }
+    if constexpr (FOLD) fold();
     // accumulator layout: lane l, register e hold row 8 (e / 4) + 4 (l / 32) + e % 4, column l % 32
     float *out = part + ((int64_t)blockIdx.x * KS + ks) * a * b;
 #pragma unroll
@@ -120,7 +136,7 @@ __global__ __launch_bounds__(kBlock) void k_tn_partial(const float *__restrict__
             for (int e = 0; e < 16; e++) {
                 const int row = m0 + wm * (TM * 32) + 32 * i + 8 * (e / 4) + 4 * (lane / 32) + e % 4;
                 const int col = n0 + wn * (TN * 32) + 32 * j + lane % 32;
-                if (row < a && col < b) out[(int64_t)row * b + col] = acc[i][j][e];
+                if (row < a && col < b) out[(int64_t)row * b + col] = FOLD ? tot[FOLD ? i : 0][FOLD ? j : 0][e] : acc[i][j][e];
             }
 }
 
@@ -208,14 +224,21 @@ int gs_weight_grad(const float *H, int64_t ldh, const float *G, int64_t ldg, int
         const TnPlan p = tn_plan(n, a, b);
         const dim3 grid((unsigned)p.chunks, (unsigned)p.tiles);
         float *part = (float *)work;
-        auto go = [&](auto mt, auto nt, auto wm, auto wn) {
-            k_tn_partial<decltype(mt)::value, decltype(nt)::value, decltype(wm)::value, decltype(wn)::value>
+        auto go = [&](auto mt, auto nt, auto wm, auto wn, auto fold) {
+            k_tn_partial<decltype(mt)::value, decltype(nt)::value, decltype(wm)::value, decltype(wn)::value,
+                         decltype(fold)::value>
                 <<<grid, kBlock, 0, s>>>(H, ldh, G, ldg, n, (int)a, (int)b, p.per, part);
         };
-#define GS_TN(M, N, WM, WN)                                                                                    \
-    if (p.mt == M && p.nt == N)                                                                                \
-        go(std::integral_constant<int, M>{}, std::integral_constant<int, N>{}, std::integral_constant<int, WM>{}, \
-           std::integral_constant<int, WN>{});
+        auto tiled = [&](auto mt, auto nt, auto wm, auto wn) {
+            if (p.mt != decltype(mt)::value || p.nt != decltype(nt)::value) return;
+            if (p.per > kFoldRows)
+                go(mt, nt, wm, wn, std::true_type{});
+            else
+                go(mt, nt, wm, wn, std::false_type{});
+        };
+#define GS_TN(M, N, WM, WN)                                                                                       \
+    tiled(std::integral_constant<int, M>{}, std::integral_constant<int, N>{}, std::integral_constant<int, WM>{}, \
+          std::integral_constant<int, WN>{});
         GS_TN(128, 128, 2, 2) GS_TN(128, 64, 2, 2) GS_TN(64, 128, 2, 2) GS_TN(64, 64, 2, 2)
         GS_TN(128, 32, 4, 1) GS_TN(32, 128, 1, 4) GS_TN(64, 32, 2, 1) GS_TN(32, 64, 1, 2) GS_TN(32, 32, 1, 1)
 #undef GS_TN

@@ -159,8 +159,9 @@ def test_gcn_graph_replays_match_eager(mode):
 def test_weight_grad_product(n, a, b):
     # H^T G on the matrix cores around its tiles (32, 64, 128 columns), stages
     # (32 rows) and chunks, with operands cut out of wider tensors at 4-byte
-    # offsets.  A sum of n products is at most n / 256 + 256 roundings deep:
-    # one chunk's rows, then the chunks.
+    # offsets.  A workgroup sums at most 256 rows here (20,003 rows in 85
+    # chunks, two stages rounded up), and the reduction adds every sixteenth
+    # partial of at most 1,256 and then sixteen: within n / 256 + 256 roundings.
     rng = np.random.default_rng(n * 7 + a + b)
     H = rng.standard_normal((n, a)).astype(np.float32)
     G = rng.standard_normal((n, b)).astype(np.float32)
@@ -213,6 +214,21 @@ def test_weight_grad_leaves_recorded_products_to_pytorch():
     torch.testing.assert_close(H.grad, G.sum(1, keepdim=True).expand(-1, 24))
     assert gcn.weight_grad(H.detach().double(), G.double()).dtype == torch.float64
     assert gcn.weight_grad(H.detach().cpu(), G.cpu()).device.type == "cpu"
+
+
+@pytest.mark.parametrize("a,b", [(512, 512), (512, 480), (32, 64), (100, 128)])
+def test_weight_grad_chains_do_not_grow_with_n(a, b):
+    # a workgroup's sums are folded every 1,024 rows.  All products are
+    # 1 + 2^-12: a sum of 1,024 is exact, while one chain loses the 2^-12 of
+    # every product once it is past 8,192 (at 16 tiles it would hold 18,750 rows,
+    # an error of 1.4e-4).  Depth: at most 1,024 rows and 19 folds with 32
+    # partials to a slice (32 x 64: 256 and 18 with 128), four levels.
+    n = 600_000 if a * b > 1 << 17 else 9_000_000
+    H = torch.ones(n, a, device="cuda")
+    G = torch.full((n, b), 1 + 2.0**-12, device="cuda")
+    want = n * (1 + 2.0**-12)
+    got = gcn.weight_grad(H, G).double()
+    assert float((got / want - 1).abs().max()) <= (1024 + 19 + 32 + 4) * U
 
 
 @pytest.mark.parametrize("handle", [False, True])
