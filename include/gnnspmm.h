@@ -143,10 +143,10 @@ int gs_convert(gs_matrix A, int fmt, const gs_build_opts *opts, gs_stream s, gs_
  * inputs give bit-identical Y.  CSC sums its (in fp64 exact) products in fp64
  * and rounds once; its handle keeps the matrix by rows beside its arrays for
  * that.  Fully asynchronous on s; the
- * first call with a larger F than before may allocate a workspace (in
- * stream order), a COO handle's first call its row pointers.  That workspace
- * (partial sums of split rows) belongs to the handle: SpMM calls on one handle must
- * not overlap in time (issue them on one stream or order them); different
+ * first call with a larger F than before may allocate (in stream order) a
+ * workspace (partial sums of split rows) and, outside a graph capture, a copy
+ * of the column indices tagged for gathers by class, which belong to the
+ * handle: SpMM calls on one handle must not overlap in time (issue them on one stream or order them); different
  * handles are independent. */
 int gs_spmm(gs_matrix A, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
             gs_stream s);

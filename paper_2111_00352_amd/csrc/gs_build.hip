@@ -858,13 +858,6 @@ void canonicalize(const gs_coo &A, bool assume_canonical, hipStream_t s, CanonCO
     if (f & kFlagDup) fail(GS_ERR_DUPLICATE, "COO holds duplicate (row, col) entries");
 }
 
-void row_pointers(gs_matrix_ &m, hipStream_t s)
-{
-    m.row_ptr.alloc((size_t)(m.R + 1) * 4, s);
-    k_row_ptr<<<elem_grid(ceil_div(m.Z, 4) + 1), kTB, 0, s>>>(m.row.as<int32_t>(), m.Z, m.R, m.row_ptr.as<int32_t>());
-    GS_LAUNCH_CHECK();
-}
-
 gs_matrix_ *csr_from_canon(CanonCOO &&c, hipStream_t s, bool plan)
 {
     gs_matrix_ *m = new gs_matrix_();
@@ -1053,7 +1046,6 @@ gs_matrix_ *convert_from_csr(const gs_matrix_ &csr, int fmt, int bsr_block, uint
                 GS_LAUNCH_CHECK();
             }
             copy_or_make_plan(csr, *m, true, s);
-            m->row_ptr.reset();  // made again from the row indices by the first SpMM
             m->device_bytes = need;
             break;
         }

@@ -114,10 +114,9 @@ struct gs_matrix_ {
     int64_t R = 0, C = 0, Z = 0;
     hipStream_t stream = nullptr;  // stream the arrays were allocated on
 
-    // COO (row, col, val; row_ptr for its SpMM) and CSR (row_ptr, col, val)
-    // share col/val; CSC
-    // keeps its col_ptr / row indices / values in row_ptr / col / val (it is
-    // the CSR of the transpose).
+    // COO (row, col, val; row_ptr and the row plan for its SpMM), CSR (row_ptr,
+    // col, val), CSC (col_ptr in row_ptr, row indices in col, val: it is the
+    // CSR of the transpose).
     gs::DevBuf row, row_ptr, col, val;
     // ELL
     int64_t K = 0;
@@ -251,9 +250,6 @@ void canonicalize(const gs_coo &A, bool assume_canonical, hipStream_t s, CanonCO
 // plan = false leaves the SpMM work plan to the first use of the handle
 // (feature extraction reads only row_ptr / col).
 gs_matrix_ *csr_from_canon(CanonCOO &&c, hipStream_t s, bool plan = true);
-
-// Row pointers of a COO handle from its sorted row indices.
-void row_pointers(gs_matrix_ &m, hipStream_t s);
 
 // Builds format fmt from a CSR handle (not consumed).
 gs_matrix_ *convert_from_csr(const gs_matrix_ &csr, int fmt, int bsr_block, uint64_t max_bytes,

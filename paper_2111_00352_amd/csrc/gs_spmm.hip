@@ -414,8 +414,7 @@ void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 
 // COO: the entries are in row order, so their column and value arrays are
 // those of the CSR form and the row kernel reads them as they are, by the row
-// plan that the handle keeps beside them and row pointers made at the first
-// SpMM.  (Equal ranges
+// pointers and the row plan that the handle keeps beside them.  (Equal ranges
 // of entries with a segmented sum, the schedule this replaces, took 43.8 us on
 // the power-law graph at F = 64 against 34.3 us, 255 against 185 us on the
 // block graph and 3.5 against 3.0 ms on the 2M-row graph: cut rows went through
@@ -424,7 +423,6 @@ void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s, const WorkArea *fixed)
 {
     if (fixed) fail(GS_ERR_UNSUPPORTED, "COO handles are not supported without allocation");
-    if (!m.row_ptr.p) row_pointers(m, s);
     spmm_csr(m, X, ldx, Y, ldy, F, s, fixed);
 }
 

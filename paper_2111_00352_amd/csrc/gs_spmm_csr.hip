@@ -957,8 +957,8 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
             if (cum > budget) hot_cls = c < 15 ? c + 1 : 15;
         }
         if (hot_cls && !m.csr_colf.p) {
-            if (fixed) {
-                hot_cls = 0;  // no allocation allowed: plain gathers
+            if (fixed || is_capturing(s)) {
+                hot_cls = 0;  // no allocation allowed, or the copy would be made by the first replay: plain gathers
             } else {          // first use: the class-tagged column copy
                 m.csr_colf.alloc((size_t)m.Z * 4, s);
                 k_tag_cols<<<plan_grid(ceil_div(m.Z, 16)), kBlock, 0, s>>>(

@@ -538,7 +538,7 @@ def test_allocation_failure_is_reported_and_recovers():
     # GS_ERR_OOM and leave no half-made buffer behind, so once allocation
     # works again the same handle builds its workspace and computes correctly
     gs._require_gpu()
-    case = _random_case(3000, 2800, 60000, 71)
+    case = Case(3000, 2800, *graphgen.dense_rows_coo(3000, 2800, [5, 1700], seed=71, base_nnz=60000))
     m = case.build("coo")
     X = graphgen.features_x(case.C, 64, 72, "normal")
     Xd = _dev(X)
@@ -556,7 +556,7 @@ def test_allocation_failure_is_reported_and_recovers():
     assert gs.lib().gs_set_allocator(ctypes.byref(hooks)) == 0
     m2 = None
     try:
-        with pytest.raises(gs.GnnSpmmError) as e1:  # COO range bounds and carry slots
+        with pytest.raises(gs.GnnSpmmError) as e1:  # partial sums of the dense rows' chunks
             m.spmm(Xd)
         with pytest.raises(gs.GnnSpmmError) as e2:  # a whole build
             case.build("csr")
@@ -678,6 +678,35 @@ def test_destroy_waits_for_every_stream_that_read(fmt):
     m.spmm(Xd)
     m.close()
     assert all(s2.query() for s2 in others), "destroyed under a copy that still reads it"
+
+
+@pytest.mark.parametrize("fmt,classes", [("coo", False), ("coo", True), ("csr", True), ("csc", False)])
+def test_first_spmm_inside_a_capture(monkeypatch, fmt, classes):
+    # nothing that a handle keeps may be left to the first replay: an eager
+    # call between capture and replay, and every replay, give what a handle
+    # that was never captured gives, bit for bit
+    monkeypatch.setenv("GS_CSR_HOTCOLD", "on" if classes else "off")
+    monkeypatch.setenv("GS_CSR_HOT_KB", "1")
+    monkeypatch.setenv("GS_CSR_SORT", "2")
+    case = Case(700, 5000, *graphgen.dense_rows_coo(700, 5000, [0, 3, 350, 699], seed=35, base_nnz=8000))
+    Xd = _dev(graphgen.features_x(case.C, 64, 36, "normal"))
+    X2 = _dev(graphgen.features_x(case.C, 64, 37, "normal"))
+    plain = case.build(fmt)
+    want, want2 = _bits(_host(plain.spmm(Xd))), _bits(_host(plain.spmm(X2)))
+    m = case.build(fmt)
+    Xs, out = Xd.clone(), torch.empty((case.R, 64), device=DEV)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        m.spmm(Xs, out=out)
+    assert (_bits(_host(m.spmm(Xd))) == want).all()
+    for x, w in ((Xd, want), (X2, want2), (Xd, want)):
+        Xs.copy_(x)
+        out.fill_(7.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (_bits(_host(out)) == w).all()
+        assert (_bits(_host(m.spmm(X2))) == want2).all()
 
 
 # -------------------------------------------------------------- conversion
