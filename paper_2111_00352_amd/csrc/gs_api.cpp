@@ -81,6 +81,9 @@ void run_spmm(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 
 }  // namespace gs
 
+// The CSR form that a handle holds, if any.
+static gs_matrix_ *rows_of(gs_matrix_ &m) { return m.fmt == GS_CSR ? &m : m.fmt == GS_CSC ? m.by_rows : nullptr; }
+
 extern "C" {
 
 int gs_build_format(const gs_coo *A, int fmt, const gs_build_opts *opts, gs_stream stream,
@@ -119,8 +122,8 @@ int gs_convert(gs_matrix A, int fmt, const gs_build_opts *opts, gs_stream stream
         const gs_build_opts o = resolve_opts(opts);
         hipStream_t s = (hipStream_t)stream;
         const NoteUse used{*A, s};  // (a conversion may return before it has read A)
-        if (A->fmt == GS_CSR) {
-            *out = convert_from_csr(*A, fmt, o.bsr_block, o.max_bytes, s, bytes_required);
+        if (gs_matrix_ *rows = rows_of(*A)) {
+            *out = convert_from_csr(*rows, fmt, o.bsr_block, o.max_bytes, s, bytes_required);
             return;
         }
         gs_matrix_ *csr = csr_from_any(*A, s);
@@ -178,8 +181,8 @@ int gs_matrix_features(gs_matrix A, gs_stream stream, gs_features *out)
         if (!A || !out) fail(GS_ERR_INVALID_ARG, "null argument");
         hipStream_t s = (hipStream_t)stream;
         const NoteUse used{*A, s};
-        if (A->fmt == GS_CSR) {
-            features_from_csr(*A, s, out);
+        if (gs_matrix_ *rows = rows_of(*A)) {
+            features_from_csr(*rows, s, out);
             return;
         }
         gs_matrix_ *csr = csr_from_any(*A, s);

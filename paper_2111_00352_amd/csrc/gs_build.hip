@@ -957,13 +957,17 @@ void copy_or_make_plan(const gs_matrix_ &csr, gs_matrix_ &m, bool gathers, hipSt
     copy_buf(m.csr_items, csr.csr_items, s);
     copy_buf(m.long_rows, csr.long_rows, s);
     copy_buf(m.long_first, csr.long_first, s);
-    if (gathers) {
-        copy_buf(m.col_cls, csr.col_cls, s);
-        std::copy(csr.col_class_cols, csr.col_class_cols + 16, m.col_class_cols);
-        m.win_counted = csr.win_counted;
-        std::copy(csr.win_entries, csr.win_entries + 8, m.win_entries);
-    }
     m.csr_planned = true;
+    if (!gathers) return;
+    if (!csr.gathers_planned) {  // the row form behind a CSC handle
+        plan_gathers(m, s);
+        return;
+    }
+    copy_buf(m.col_cls, csr.col_cls, s);
+    std::copy(csr.col_class_cols, csr.col_class_cols + 16, m.col_class_cols);
+    m.win_counted = csr.win_counted;
+    std::copy(csr.win_entries, csr.win_entries + 8, m.win_entries);
+    m.gathers_planned = true;
 }
 
 // A planned copy of a CSR handle (gathers: as for plan_csr).
@@ -1239,8 +1243,6 @@ void to_coo(const gs_matrix_ &m, int32_t *row, int32_t *col, float *val, hipStre
 
 gs_matrix_ *csr_from_any(const gs_matrix_ &m, hipStream_t s)
 {
-    if (m.fmt == GS_CSR) return convert_from_csr(m, GS_CSR, 0, ~0ull, s, nullptr);
-    if (m.fmt == GS_CSC) return convert_from_csr(*m.by_rows, GS_CSR, 0, ~0ull, s, nullptr);
     CanonCOO c;
     c.R = m.R;
     c.C = m.C;

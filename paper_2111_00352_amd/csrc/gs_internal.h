@@ -154,6 +154,7 @@ struct gs_matrix_ {
     bool csr_sorted = false; // items ordered by decreasing length
     bool csr_grouped = false; // group tier: short items may be rows of up to kCsrGroupRow entries
     bool csr_planned = false; // plan_csr has run (a CSR built only for its features has no plan)
+    bool gathers_planned = false; // ... with the reference classes and windows below
     // CSR: column indices tagged with their column's reference class (bit
     // length of its entry count) in bits 27..30 (made by the first SpMM that
     // gathers by class), each column's class, and the number of columns in
@@ -300,6 +301,8 @@ void spmm_csc(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 // gathers = false leaves out what only spmm_csr uses (reference classes and
 // row windows).
 void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers = true);
+// Adds to a row plan what only spmm_csr uses (synchronises s).
+void plan_gathers(gs_matrix_ &m, hipStream_t s);
 // Entries inside their row tile's window for every candidate tile (T = 32,
 // 64, 128, 256 rows, halo 0 / 1) of the matrix with CSR arrays rp, col, into
 // m.win_entries (synchronises s).

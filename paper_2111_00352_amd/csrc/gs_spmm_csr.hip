@@ -752,6 +752,56 @@ static bool enqueue_col_classes(gs_matrix_ &m, int32_t *hist, hipStream_t s)
     return true;
 }
 
+namespace {
+
+// What the host needs of a plan, read back in one copy: the item counts at the
+// tier boundaries, the columns of each class, the window counts.
+struct PlanBack {
+    int32_t off[4];
+    int32_t cls[16];
+    unsigned long long win[2 * kWinCands];
+};
+
+struct Gathers {
+    bool classes = false, windows = false;
+};
+
+Gathers enqueue_gathers(gs_matrix_ &m, PlanBack *back, hipStream_t s)
+{
+    const char *no_win = std::getenv("GS_CSR_WINDOW");
+    Gathers have;
+    have.classes = enqueue_col_classes(m, back->cls, s);
+    have.windows = !(no_win && std::string(no_win) == "off") && !m.csr_sorted && !m.csr_grouped &&
+                   m.n_long_rows == 0 && m.Z > 0;
+    if (have.windows) enqueue_window_counts(m, m.row_ptr.as<int32_t>(), m.col.as<int32_t>(), back->win, s);
+    return have;
+}
+
+void take_gathers(gs_matrix_ &m, Gathers have, const PlanBack &back)
+{
+    if (have.classes) std::copy(back.cls, back.cls + 16, m.col_class_cols);
+    if (have.windows) {
+        std::copy(back.win, back.win + 2 * kWinCands, m.win_entries);
+        m.win_counted = true;
+    }
+    m.gathers_planned = true;
+}
+
+}  // namespace
+
+void plan_gathers(gs_matrix_ &m, hipStream_t s)
+{
+    PlanBack back = {};
+    DevBuf d_back;
+    d_back.alloc(sizeof back, s);
+    const Gathers have = enqueue_gathers(m, d_back.as<PlanBack>(), s);
+    if (have.classes || have.windows) {
+        GS_HIP(hipMemcpyAsync(&back, d_back.p, sizeof back, hipMemcpyDeviceToHost, s));
+        GS_HIP(hipStreamSynchronize(s));
+    }
+    take_gathers(m, have, back);
+}
+
 void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
 {
     const int thr = env_int("GS_CSR_LONG_ROW", kCsrLongRow);
@@ -815,16 +865,10 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
     m.n_medium_rows = n_long - n_huge;
     m.n_short = R - n_long;
 
-    // what the host needs of the plan, read back in one copy: the item counts
-    // at the tier boundaries, the columns of each class, the window counts
-    struct Back {
-        int32_t off[4];
-        int32_t cls[16];
-        unsigned long long win[2 * kWinCands];
-    } back = {};
+    PlanBack back = {};
     DevBuf d_back;
     d_back.alloc(sizeof back, s);
-    Back *db = d_back.as<Back>();
+    PlanBack *db = d_back.as<PlanBack>();
     DevBuf ka, kb, pa, pb, cnt;
     uint32_t *perm = nullptr;
     if (R > 0) {
@@ -851,11 +895,7 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
         k_pick3<<<1, kWave, 0, s>>>(cnt.as<int32_t>(), m.n_medium_rows, n_long, R, db->off);
         GS_HIP(hipGetLastError());
     }
-    const char *no_win = std::getenv("GS_CSR_WINDOW");
-    const bool classes = gathers && enqueue_col_classes(m, db->cls, s);
-    const bool windows = gathers && !(no_win && std::string(no_win) == "off") && !m.csr_sorted && !m.csr_grouped &&
-                         m.n_long_rows == 0 && m.Z > 0;
-    if (windows) enqueue_window_counts(m, rp, m.col.as<int32_t>(), db->win, s);
+    const Gathers have = gathers ? enqueue_gathers(m, db, s) : Gathers{};
     if (R > 0) {
         GS_HIP(hipMemcpyAsync(&back, d_back.p, sizeof back, hipMemcpyDeviceToHost, s));
         GS_HIP(hipStreamSynchronize(s));
@@ -863,11 +903,7 @@ void plan_csr(gs_matrix_ &m, hipStream_t s, bool gathers)
     m.n_medium_chunks = back.off[0];
     m.n_long_chunks = back.off[1];
     m.n_items = back.off[2];
-    if (classes) std::copy(back.cls, back.cls + 16, m.col_class_cols);
-    if (windows) {
-        std::copy(back.win, back.win + 2 * kWinCands, m.win_entries);
-        m.win_counted = true;
-    }
+    if (gathers) take_gathers(m, have, back);
     m.csr_items.alloc((size_t)m.n_items * sizeof(int4), s);
     m.long_rows.alloc((size_t)n_long * 4, s);
     m.long_first.alloc((size_t)(n_long + 1) * 4, s);

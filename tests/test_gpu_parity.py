@@ -725,6 +725,28 @@ def test_convert_between_formats(src):
     assert f["f"] == fo.tolist()
 
 
+@pytest.mark.parametrize("dst", ["csr", "coo"])
+def test_rows_made_from_csc_gather_by_class(monkeypatch, dst):
+    # the row form behind a CSC handle has no reference classes; CSR and COO
+    # made from it do, like those built directly: their first SpMM allocates
+    # the tagged copy of the columns, and the results agree bit for bit
+    monkeypatch.setenv("GS_CSR_HOTCOLD", "on")
+    monkeypatch.setenv("GS_CSR_HOT_KB", "1")
+    case = _random_case(523, 411, 6000, 11)
+    Xd = _dev(graphgen.features_x(case.C, 64, 12, "normal"))
+    out = torch.empty((case.R, 64), device=DEV)
+    src = case.build("csc")
+    ys, made = [], []
+    for m in (case.build(dst), src.convert(dst)):
+        n0 = torch.cuda.memory_stats()["allocation.all.allocated"]
+        ys.append(_bits(_host(m.spmm(Xd, out=out))))
+        made.append(torch.cuda.memory_stats()["allocation.all.allocated"] - n0)
+    assert made == [1, 1]
+    assert (ys[0] == ys[1]).all()
+    ints, fo = oracle.features(case.R, case.C, case.crow, case.ccol)
+    assert src.features()["f"] == fo.tolist()
+
+
 @pytest.mark.parametrize("cpl", [4, 8, 16])
 @pytest.mark.parametrize("sort", [1, 2])
 @pytest.mark.parametrize("F", [64, 128, 256])
