@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
     const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
     const float *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t F, A *__restrict__ work,
-    int hot_cls, int natural)
+    int hot_cls)
 {
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
@@ -122,11 +122,12 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     __shared__ A4 part[GPB][G * NQ];
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
     const Quads<NQ, G, FULL> cols((int64_t)blockIdx.y * (G * CPL), lane, F);
-    // natural row order: each XCD takes neighbouring rows, which share X rows
-    const int64_t wg = natural ? xcd_tile(blockIdx.x, gridDim.x) : blockIdx.x;
 
-    // long rows first, a workgroup each
-    int64_t t = wg;
+    // long rows first, a workgroup each.  (Tiles in launch order: giving each
+    // XCD neighbouring rows, so that they share X rows in its L2, made a mesh
+    // of 512 x 512 slower (F = 128 77 against 59 us) and 140,001 rows of 20
+    // entries (F = 128 168 against 131).)
+    int64_t t = blockIdx.x;
     for (; t < n_long; t += gridDim.x) {
         const int64_t row = long_rows[t];
         const int64_t s = rp[row], e = rp[row + 1];
@@ -205,10 +206,16 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] = tot[i] + acc[i];
         }
-        if (d.w < 0)
+        // (the empty asm statements keep the compiler from merging the branches'
+        // stores into ones that have lost the non-temporal hint: a 512 x 512
+        // mesh at F = 128 took 65 us against 59)
+        if (d.w < 0) {
+            asm volatile("");
             store_quads_stream<NQ>(Y + (int64_t)d.x * ldy, cols, acc);
-        else  // a chunk of a huge row: its partial sum, added later in slot order
+            asm volatile("");
+        } else {  // a chunk of a huge row: its partial sum, added later in slot order
             store_quads<NQ>(work + (int64_t)d.w * F, cols, acc);
+        }
         it += stride;
         if (it >= n_items) break;
         d = dn;
@@ -1059,8 +1066,7 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
                                        m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
                                        cols ? cols : m.row_ptr.as<int32_t>(),
                                        m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),
-                                       (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls,
-                                       m.csr_sorted ? 0 : 1);
+                                       (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls);
             GS_HIP(hipGetLastError());
         };
         bool done = false;
@@ -1144,8 +1150,7 @@ void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         if (!tiles) return;
         dim3 grid(rows_grid((const void *)fn, tiles, slices, m.csr_sorted ? 4 : 8), (unsigned)slices);
         fn<<<grid, kBlock, 0, s>>>(n_wg, m.long_rows.as<int32_t>(), rp, m.csr_chunk, m.n_items - skip, items + skip, col,
-                                   val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0,
-                                   m.csr_sorted ? 0 : 1);
+                                   val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0);
         GS_HIP(hipGetLastError());
         if (n_huge) {
             dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
