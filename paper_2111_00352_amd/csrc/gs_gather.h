@@ -54,8 +54,10 @@ template <int J, int G> __device__ __forceinline__ int bcast_entry(int v, int j0
     }
 }
 
-// Entries per batch of a group of G lanes.
-template <int G> constexpr int kEntryBatch = G == 64 ? 64 : G < 16 ? G : 16;
+// Entries per register of a group of G lanes, and per batch of NB registers
+// (NB = 2 for groups of 32 lanes only).
+template <int G> constexpr int kEntryReg = G == 64 ? 64 : G < 16 ? G : 16;
+template <int G, int NB> constexpr int kEntryBatch = NB * kEntryReg<G>;
 
 // Column quads of a lane: quad q starts at column c0 + 4 G q, the last one
 // of a width that is no multiple of 4 moved back to end at column F (the
@@ -115,14 +117,15 @@ __device__ __forceinline__ const float *x_at(const float *X, uint32_t lo, uint32
         return reinterpret_cast<const float *>(b + (((uint64_t)hi << 32) | lo)) + (int64_t)cols.base(q) + cols.step(q);
 }
 
-// Entries J0 .. J0+B-1 of the group's batch (ref, v: one entry per lane): B
-// X rows requested back to back, then B multiply-adds into acc.  MASKED:
-// entries past the t-th gather nothing (a dead gather costs as much as a live
-// one) and add -0 * 0 = -0, which leaves every sum as it is.  CLS: entries
-// whose lane set `cold` are gathered non-temporally.
-template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, class Q, class A>
-__device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
-                                            const Q &cols, A *acc, int j0 = 0)
+// Entries J0 .. J0+B-1 of the group's batch (ref, v: one entry per lane and
+// register): B X rows requested back to back, then B multiply-adds, entry j
+// into the sums j % NA.  MASKED: entries past the t-th gather nothing (a dead
+// gather costs as much as a live one) and add -0 * 0 = -0, which leaves every
+// sum as it is.  CLS: entries whose lane set `cold` are gathered
+// non-temporally.
+template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, int NA, class Q, class A>
+__device__ __forceinline__ void gather_step(const RowRef<OFF> *ref, const float *v, const int *cold, int t,
+                                            const float *X, const Q &cols, A *acc, int j0 = 0)
 {
     f4u x[B][NQ];
     float vv[B];
@@ -131,12 +134,13 @@ __device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int
     [&]<int... U>(std::integer_sequence<int, U...>) {
         (
             [&] {
-                lo[U] = (uint32_t)bcast_entry<J0 + U, G>((int)ref.lo, j0);
+                constexpr int E = (J0 + U) % kEntryReg<G>, R = (J0 + U) / kEntryReg<G>;
+                lo[U] = (uint32_t)bcast_entry<E, G>((int)ref[R].lo, j0);
                 hi[U] = 0;
-                if constexpr (OFF == kOff64) hi[U] = (uint32_t)bcast_entry<J0 + U, G>((int)ref.hi, j0);
-                vv[U] = __int_as_float(bcast_entry<J0 + U, G>(__float_as_int(v), j0));
+                if constexpr (OFF == kOff64) hi[U] = (uint32_t)bcast_entry<E, G>((int)ref[R].hi, j0);
+                vv[U] = __int_as_float(bcast_entry<E, G>(__float_as_int(v[R]), j0));
                 c[U] = 0;
-                if constexpr (CLS) c[U] = bcast_entry<J0 + U, G>(cold, j0);
+                if constexpr (CLS) c[U] = bcast_entry<E, G>(cold[R], j0);
             }(),
             ...);
     }(std::make_integer_sequence<int, B>{});
@@ -175,32 +179,48 @@ __device__ __forceinline__ void gather_step(const RowRef<OFF> &ref, float v, int
 #pragma unroll
         for (int q = 0; q < NQ; q++)
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                acc[4 * q + i] = __builtin_elementwise_fma((A)vv[u], (A)x[u][q][i], acc[4 * q + i]);
+            for (int i = 0; i < 4; i++) {
+                A &a = acc[((J0 + u) % NA * NQ + q) * 4 + i];
+                a = __builtin_elementwise_fma((A)vv[u], (A)x[u][q][i], a);
+            }
 }
 
-// The first t (1 .. kEntryBatch<G>) entries of the group's batch, U at a time.
-template <int J0, int U, int NQ, int G, int OFF, bool CLS, class Q, class A>
-__device__ __forceinline__ void gather_entries_of(const RowRef<OFF> &ref, float v, int cold, int t, const float *X,
-                                                  const Q &cols, A *acc)
+// Adds the NA sums of N elements each, pairwise, into the first.
+template <int NA, int N, class A> __device__ __forceinline__ void add_sums(A *acc)
 {
+#pragma unroll
+    for (int w = 1; w < NA; w <<= 1)
+#pragma unroll
+        for (int k = 0; k < NA; k += 2 * w)
+#pragma unroll
+            for (int i = 0; i < N; i++) acc[k * N + i] += acc[(k + w) * N + i];
+}
+
+// The first t (1 .. kEntryBatch<G, NB>) entries of the group's batch, U at a
+// time (U a multiple of NA), a last half batch where it still holds every sum.
+template <int J0, int U, int NQ, int G, int NB, int OFF, bool CLS, int NA, class Q, class A>
+__device__ __forceinline__ void gather_entries_of(const RowRef<OFF> *ref, const float *v, const int *cold, int t,
+                                                  const float *X, const Q &cols, A *acc)
+{
+    static_assert(U % NA == 0, "entry j belongs to the sums j % NA");
+    constexpr int H = U / 2 >= NA && U > 1 ? U / 2 : U;
     if constexpr (G == 64) {
         const int n = __builtin_amdgcn_readfirstlane(t);  // one row to the wave
         int j = 0;
-        for (; j + U <= n; j += U) gather_step<0, U, NQ, G, false, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
-        if (U > 1 && j < n && n - j <= U / 2)
-            gather_step<0, (U > 1 ? U / 2 : 1), NQ, G, true, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
+        for (; j + U <= n; j += U) gather_step<0, U, NQ, G, false, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
+        if (H < U && j < n && n - j <= H)
+            gather_step<0, H, NQ, G, true, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
         else if (j < n)
-            gather_step<0, U, NQ, G, true, OFF, CLS>(ref, v, cold, n, X, cols, acc, j);
-    } else if constexpr (J0 < kEntryBatch<G>) {
+            gather_step<0, U, NQ, G, true, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
+    } else if constexpr (J0 < kEntryBatch<G, NB>) {
         if (t >= J0 + U) {
-            gather_step<J0, U, NQ, G, false, OFF, CLS>(ref, v, cold, t, X, cols, acc);
-            gather_entries_of<J0 + U, U, NQ, G, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+            gather_step<J0, U, NQ, G, false, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
+            gather_entries_of<J0 + U, U, NQ, G, NB, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
         } else if (t > J0) {
-            if (U > 1 && t - J0 <= U / 2)
-                gather_step<J0, (U > 1 ? U / 2 : 1), NQ, G, true, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+            if (H < U && t - J0 <= H)
+                gather_step<J0, H, NQ, G, true, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
             else
-                gather_step<J0, U, NQ, G, true, OFF, CLS>(ref, v, cold, t, X, cols, acc);
+                gather_step<J0, U, NQ, G, true, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
         }
     }
 }

@@ -328,9 +328,9 @@ int resident_workgroups();
 // Whether s is being captured into a graph (or may not be asked, for a capture).
 bool is_capturing(hipStream_t s);
 int compute_units();
-// Workgroups of `threads` threads of a kernel (without dynamic LDS) that one
-// compute unit keeps resident, queried once per kernel.
-int resident_blocks(const void *fn, int threads);
+// Workgroups of `threads` threads and `lds` bytes of dynamic LDS of a kernel
+// that one compute unit keeps resident, queried once.
+int resident_blocks(const void *fn, int threads, size_t lds);
 // LDS bytes one workgroup may use (the device's limit), queried once.
 int64_t max_lds_bytes();
 

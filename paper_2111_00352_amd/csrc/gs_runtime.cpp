@@ -6,7 +6,7 @@
 #include <map>
 #include <mutex>
 #include <new>
-#include <utility>
+#include <tuple>
 
 #include "gs_internal.h"
 
@@ -145,16 +145,16 @@ int compute_units()
 
 int resident_workgroups() { return compute_units() * 8; }
 
-int resident_blocks(const void *fn, int threads)
+int resident_blocks(const void *fn, int threads, size_t lds)
 {
     static std::mutex mu;
-    static std::map<std::pair<const void *, int>, int> cache;
+    static std::map<std::tuple<const void *, int, size_t>, int> cache;
     std::lock_guard<std::mutex> lock(mu);
-    const auto key = std::make_pair(fn, threads);
+    const auto key = std::make_tuple(fn, threads, lds);
     auto it = cache.find(key);
     if (it != cache.end()) return it->second;
     int n = 0;
-    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, 0));
+    GS_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds));
     return cache[key] = n > 0 ? n : 1;
 }
 

@@ -40,55 +40,77 @@ constexpr int kBlock = 256;
 constexpr int kWinCands = 4;
 
 // The group's next batch of entries: [k, k + n) of the entry arrays, one per
-// lane (every 16 lanes of a group of 32 load the same 16).  Lanes past the
-// last entry hold a valid column and the value -0.
-template <int G, int OFF, bool CLS> struct Batch {
-    int c;
-    float v;
+// lane and register (every 16 lanes of a group of 32 load the same 16).  Lanes
+// past the last entry hold a valid column and the value -0.
+template <int G, int NB, int OFF, bool CLS> struct Batch {
+    int c[NB];
+    float v[NB];
     // (zlast: the matrix's last entry, read in the place of an empty row's)
     __device__ __forceinline__ void load(const int32_t *__restrict__ col, const float *__restrict__ val, int k, int n,
                                          int zlast, int lane)
     {
-        constexpr int EB = kEntryBatch<G>;
-        const int e = lane % EB;
-        int i = k + (e < n ? e : n > 0 ? n - 1 : 0);
-        i = i < zlast ? i : zlast;
-        c = ld_stream(col + i);
-        v = ld_stream(val + i);
-        if (e >= n) v = -0.0f;
+#pragma unroll
+        for (int r = 0; r < NB; r++) {
+            const int e = lane % kEntryReg<G> + r * kEntryReg<G>;
+            int i = k + (e < n ? e : n > 0 ? n - 1 : 0);
+            i = i < zlast ? i : zlast;
+            c[r] = ld_stream(col + i);
+            v[r] = ld_stream(val + i);
+            if (e >= n) v[r] = -0.0f;
+        }
     }
-    __device__ __forceinline__ void refs(int64_t ldx, int hot_cls, RowRef<OFF> &ref, int &cold) const
+    __device__ __forceinline__ void refs(int64_t ldx, int hot_cls, RowRef<OFF> *ref, int *cold) const
     {
-        ref.set(CLS ? (c & kColMask) : c, ldx);
-        cold = CLS ? (c >> kColClassShift) < hot_cls : 0;
+#pragma unroll
+        for (int r = 0; r < NB; r++) {
+            ref[r].set(CLS ? (c[r] & kColMask) : c[r], ldx);
+            cold[r] = CLS ? (c[r] >> kColClassShift) < hot_cls : 0;
+        }
     }
 };
 
 // Accumulates the n entries from k0 on into acc, the next batch's
 // entries requested while the current one's X rows are gathered.
-template <int NQ, int G, int U, int OFF, bool CLS, class Q, class A>
+template <int NQ, int G, int NB, int U, int OFF, bool CLS, int NA, class Q, class A>
 __device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, const float *__restrict__ val, int k0,
                                             int n, int zlast, const float *__restrict__ X, int64_t ldx, const Q &cols,
                                             int lane, int hot_cls, A *acc)
 {
-    constexpr int EB = kEntryBatch<G>;
-    Batch<G, OFF, CLS> b;
+    constexpr int EB = kEntryBatch<G, NB>;
+    Batch<G, NB, OFF, CLS> b;
     b.load(col, val, k0, n < EB ? n : EB, zlast, lane);
     for (int kb = 0; kb < n; kb += EB) {
         const int left = n - kb;
-        RowRef<OFF> ref;
-        int cold;
+        RowRef<OFF> ref[NB];
+        int cold[NB];
         b.refs(ldx, hot_cls, ref, cold);
-        const float v = b.v;
+        float v[NB];
+#pragma unroll
+        for (int r = 0; r < NB; r++) v[r] = b.v[r];
         const int nl = left > EB ? left - EB : 0;
         b.load(col, val, k0 + kb + (left > EB ? EB : 0), nl < EB ? nl : EB, zlast, lane);
-        gather_entries_of<0, U, NQ, G, OFF, CLS>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
+        gather_entries_of<0, U, NQ, G, NB, OFF, CLS, NA>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
     }
 }
 
-// A: the accumulator type (double: the products are summed exactly enough
-// that one rounding to fp32 is the only one that matters).
-//
+// What a row kernel is compiled for, beside its lane shape:
+//  A        the accumulator type (double: the products are summed exactly
+//           enough that one rounding to fp32 is the only one that matters)
+//  CLS      columns carry their reference class
+//  GROUPED  the plan's group tier is active, so items may be rows of up to the
+//           group limit, folded every kChainFold entries
+//  DEPTH    X rows in flight per lane group where it is not 8 of CPL = 4 (8
+//           float4 loads a lane; 4 where registers or L2 lines are short: fp64
+//           sums, class gathers)
+//  NA       sums per column, entry j going to sum j % NA (fp32 chains of a
+//           quarter or half the length)
+//  NB       registers of entries per batch
+template <class A_, bool CLS_, bool GROUPED_, int DEPTH_ = 0, int NA_ = 1, int NB_ = 1> struct RowVariant {
+    typedef A_ A;
+    static constexpr bool CLS = CLS_, GROUPED = GROUPED_;
+    static constexpr int DEPTH = DEPTH_, NA = NA_, NB = NB_;
+};
+
 // Bound by the L2 fills of the gathered X rows (7.3 TB/s) where X exceeds the
 // L2s, by the L2's gather rate (16 TB/s) where it does not, and on small
 // matrices by the chain item -> entries -> X rows: a lane group runs its items
@@ -99,24 +121,20 @@ __device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, con
 // (F = 256) 199 -> 185, a 30,011 x 100,003 block of 450,000 entries at F = 47
 // 23.1 -> 20.3.
 //
-// GROUPED: the plan's group tier is active, so items may be rows of up to the
-// group limit, folded every kChainFold entries (compiled out otherwise).
-//
-// DEPTH: X rows in flight per lane group where it is not the 8 of CPL = 4:
-// 16 for small matrices with long rows, whose time is the longest rows' chain
-// of round trips, 4 for large ones.
-template <int CPL, int G, bool FULL, int OFF, bool CLS, bool GROUPED, class A, int DEPTH = 0>
+template <int CPL, int G, bool FULL, int OFF, class V>
 __global__ __launch_bounds__(kBlock) void k_csr_rows(
     int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
     const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
-    const float *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t F, A *__restrict__ work,
-    int hot_cls)
+    const float *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t F,
+    typename V::A *__restrict__ work, int hot_cls)
 {
+    typedef typename V::A A;
+    constexpr bool CLS = V::CLS, GROUPED = V::GROUPED;
+    constexpr int NA = V::NA, NB = V::NB;
     constexpr int GPB = kBlock / G;
     constexpr int NQ = CPL / 4;
-    constexpr int EB = kEntryBatch<G>;
-    // 8 float4 loads in flight per lane (4 where registers or L2 lines are short: fp64 sums, class gathers)
-    constexpr int U0 = DEPTH ? DEPTH : CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
+    constexpr int EB = kEntryBatch<G, NB>;
+    constexpr int U0 = V::DEPTH ? V::DEPTH : CLS || sizeof(A) == 8 ? 4 : 32 / CPL > 0 ? 32 / CPL : 1;
     constexpr int U = U0 < EB ? U0 : EB;
     typedef typename Quad<A>::type A4;
     __shared__ A4 part[GPB][G * NQ];
@@ -137,11 +155,12 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
 #pragma unroll
         for (int i = 0; i < CPL; i++) acc[i] = 0;
         for (int64_t cs = s + (int64_t)g * piece; cs < e; cs += (int64_t)GPB * piece) {
-            A part_acc[CPL];
+            A part_acc[NA * CPL];
 #pragma unroll
-            for (int i = 0; i < CPL; i++) part_acc[i] = 0;
-            gather_span<NQ, G, U, OFF, CLS>(col, val, (int)cs, e - cs < piece ? (int)(e - cs) : piece, zlast, X, ldx,
-                                            cols, lane, hot_cls, part_acc);
+            for (int i = 0; i < NA * CPL; i++) part_acc[i] = 0;
+            gather_span<NQ, G, NB, U, OFF, CLS, NA>(col, val, (int)cs, e - cs < piece ? (int)(e - cs) : piece, zlast, X,
+                                                    ldx, cols, lane, hot_cls, part_acc);
+            add_sums<NA, CPL>(part_acc);
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] += part_acc[i];
         }
@@ -163,19 +182,22 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
         __syncthreads();  // part[] is reused by the next long row
     }
 
-    // items: the tiles after the long rows, GPB items each
+    // items: the tiles after the long rows, GPB items each.  The next item and
+    // its first entries are requested without a test, where there is none the
+    // last ones again: tests in the inner loop cost more than they save (3,302
+    // rows of 165 entries at F = 64 15.9 against 17.4 us).
     const int64_t stride = (int64_t)gridDim.x * GPB;
     int64_t it = (t - n_long) * GPB + g;
     if (it >= n_items) return;
     const int64_t last = n_items - 1;
     int4 d = items[it];
     int4 dn = items[it + stride < last ? it + stride : last];
-    Batch<G, OFF, CLS> b;
+    Batch<G, NB, OFF, CLS> b;
     b.load(col, val, d.y, d.z < EB ? d.z : EB, zlast, lane);
     while (true) {
-        A acc[CPL], tot[GROUPED ? CPL : 1];
+        A acc[NA * CPL], tot[GROUPED ? CPL : 1];
 #pragma unroll
-        for (int i = 0; i < CPL; i++) acc[i] = 0;
+        for (int i = 0; i < NA * CPL; i++) acc[i] = 0;
         if constexpr (GROUPED) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) tot[i] = 0;
@@ -183,25 +205,28 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
         for (int kb = 0;; kb += EB) {
             const int left = d.z - kb;
             const bool more = left > EB;
-            RowRef<OFF> ref;
-            int cold;
+            RowRef<OFF> ref[NB];
+            int cold[NB];
             b.refs(ldx, hot_cls, ref, cold);
-            const float v = b.v;
+            float v[NB];
+#pragma unroll
+            for (int r = 0; r < NB; r++) v[r] = b.v[r];
             // the next batch: of this row, or the next item's first
             const int nk = more ? d.y + kb + EB : dn.y, nn = more ? left - EB : dn.z;
             b.load(col, val, nk, nn < EB ? nn : EB, zlast, lane);
-            gather_entries_of<0, U, NQ, G, OFF, CLS>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
+            gather_entries_of<0, U, NQ, G, NB, OFF, CLS, NA>(ref, v, cold, left < EB ? left : EB, X, cols, acc);
             if constexpr (GROUPED) {
                 if ((kb + EB) % kChainFold == 0) {
+                    add_sums<NA, CPL>(acc);
 #pragma unroll
-                    for (int i = 0; i < CPL; i++) {
-                        tot[i] += acc[i];
-                        acc[i] = 0;
-                    }
+                    for (int i = 0; i < CPL; i++) tot[i] += acc[i];
+#pragma unroll
+                    for (int i = 0; i < NA * CPL; i++) acc[i] = 0;
                 }
             }
             if (!more) break;
         }
+        add_sums<NA, CPL>(acc);
         if constexpr (GROUPED) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] = tot[i] + acc[i];
@@ -933,14 +958,21 @@ namespace {
 // them, and any width with 64-bit offsets (X of 4 GiB and more).
 enum { kModeFull = 0, kModeAny = 1, kModeWide = 2 };
 
-// Dynamic LDS of the class gathers, which keep 4 X rows in flight per lane
-// group instead of 8 and, through this LDS, 4 workgroups per CU instead of 6.
-// Their X exceeds every cache and the kernel runs at the rate of the L2
-// fills (7.3 TB/s), so what counts is the L2 hit rate, and every row in flight
-// takes 512 B of a 4 MiB L2: 8 rows and 6 workgroups measured 3078 us on the
-// 2M-row graph, 4 rows 3005, 4 rows and 4 workgroups 2969 (2 rows 3059; 3
-// workgroups 3004).
-constexpr size_t kClassLds = 32000;
+// Dynamic LDS of row kernels that shall leave 4 workgroups on a CU (and keep 4
+// X rows in flight per lane group instead of 8).  Their X exceeds the caches
+// and they run at the rate of the L2 fills (7.3 TB/s), so what counts is the L2
+// hit rate, and every row in flight takes its lines of a 4 MiB L2.  Class
+// gathers of the group tier (2M-row graph, F = 128): 8 rows 2966 us, 4 rows
+// 2970, 4 rows and 4 workgroups 2910.  Class gathers otherwise run 4 rows
+// without it (10^6 rows of 7 entries, F = 128: 479 us, with it 506, 8 rows 489;
+// 150,000 rows of 17 139, 150, 142; of 5 at F = 200 100, 136, 110).
+constexpr size_t kFewLds = 32000;
+
+// Entries a row on average from which groups of 32 lanes take 32 at a time, in
+// two registers (30,000 uniform rows at F = 128, 16 against 32 at a time: of 12
+// entries 24.5 and 24.8 us, of 15 36.3 and 34.9, of 24 43.1 and 42.0, of 48
+// 80.4 and 78.3; 9,000 of 720 185 and 164).
+constexpr int64_t kFillRow = 14;
 
 // Every byte offset into X stays below 4 GiB.
 bool fits_off32(int64_t C, int64_t ldx, int64_t F)
@@ -954,11 +986,12 @@ bool fits_off32(int64_t C, int64_t ldx, int64_t F)
 // launch unbalanced (items are dealt out statically): 1 / 2 / 4 / 8 rounds
 // measured 68.1 / 61.7 / 60.2 / 61.1 us on the power-law graph, 137 / 163 /
 // 108 / 107 on a 9,000-row uniform matrix (8% dense, F = 64), 190 (2) / 187 /
-// 185 on the block graph and, gathering by class, 2969 (8) / 2955 (16) on the
-// 2M-row graph.
-unsigned rows_grid(const void *fn, int64_t tiles, int64_t slices, int rounds)
+// 185 on the block graph; gathering by class 4 / 8 / 16 took 485 / 480 / 479 on
+// 10^6 rows of 7 entries and 140 / 139 / 141 on 150,000 of 17, and on the
+// 2M-row graph (4 resident) 14 / 28 / 56 took 3051 / 2910 / 2913.
+unsigned rows_grid(const void *fn, size_t lds, int64_t tiles, int64_t slices, int rounds)
 {
-    const int64_t cap = (int64_t)resident_blocks(fn, kBlock) * compute_units() * env_int("GS_WG_MULT", rounds);
+    const int64_t cap = (int64_t)resident_blocks(fn, kBlock, lds) * compute_units() * env_int("GS_WG_MULT", rounds);
     return (unsigned)std::max<int64_t>(1, std::min(tiles, cap / slices));
 }
 
@@ -972,10 +1005,12 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     // columns per lane (wide groups, 8 X rows in flight per lane) is best or
     // near it, except in natural row order for very short rows (fewer than 8
     // entries on average) and for wide X (F >= 256) with rows under 64
-    // entries, where 16 columns per lane -- more rows per wave -- wins.
-    const bool many_rows_per_wave =
-        !m.csr_sorted && (m.Z < 8 * m.R || (F >= 256 && m.Z < 64 * m.R));
-    int cpl = env_int("GS_CSR_CPL", many_rows_per_wave ? 16 : 4);
+    // entries, where more columns per lane -- more rows per wave -- win: 16, or
+    // 8 for short rows at F <= 64 (mesh 33.8 us, with 16 37.8 and with 4 38.0;
+    // 30,000 rows of 6 10.6, 11.7, 10.8; mesh at F = 128 62.7, 60.2, 70.3).
+    const bool short_rows = !m.csr_sorted && m.Z < 8 * m.R;
+    const bool many_rows_per_wave = short_rows || (!m.csr_sorted && F >= 256 && m.Z < 64 * m.R);
+    int cpl = env_int("GS_CSR_CPL", !many_rows_per_wave ? 4 : F <= 64 ? 8 : 16);
     if (cpl != 4 && cpl != 8 && cpl != 16) cpl = 16;
     while (cpl > 4 && F < 4 * (int64_t)cpl) cpl /= 2;  // at least 4 lanes per group
     const int64_t lanes = ceil_div(F, cpl);
@@ -1039,52 +1074,55 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         const int64_t tiles = m.n_medium_rows + ceil_div(n_group_items, GPB);
         if (!tiles) return;
         float *work = n_huge ? (float *)work_for(m, fixed, (size_t)m.n_long_chunks * F * 4, s) : nullptr;
-        auto rows = [&](auto cls_t, auto grp_t, const int32_t *cols) {
-            constexpr bool CL = decltype(cls_t)::value, GR = decltype(grp_t)::value;
-            auto fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float>;
-            // Measured with 16 rows in flight: power-law graphs of 90,000
-            // entries (F = 64) 12.4 -> 10.7 us and of 263,000 (F = 256) 42.9 ->
-            // 37.2, of 10^6 (F = 128) 61.1 -> 62.9; a 2,048-node random graph
-            // without long rows 5.1 -> 5.9.
-            // Long rows in numbers: 4 rows in flight and 4 workgroups per CU, as
-            // for class gathers: with 8 and 7 the lines in flight exceed the
-            // L2s.  13,283 uniform rows of 373 entries at F = 156 261 -> 216 us,
-            // 15,000 of 300 at F = 128 173 -> 152, 9,000 of 720 at F = 64 108.7
-            // -> 106.6; slower below (3,302 rows of 165 at F = 176 30 -> 34, 23
-            // entries a row 90 -> 94, F = 32 143 -> 145).
-            bool few = CL;
-            if constexpr (CPL == 4 && !CL && !GR && OFF == kOff32) {
-                if (m.csr_sorted && m.n_long_rows > 0 && m.Z <= (1 << 19)) {
-                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, 16>;
-                } else if (m.Z >= 128 * m.R && F >= 64 && m.Z >= (1ll << 28) / F) {
-                    fn = k_csr_rows<CPL, G, FU, OFF, CL, GR, float, 4>;
-                    few = true;
-                }
-            }
-            dim3 grid(rows_grid((const void *)fn, tiles, slices, CL ? 16 : m.csr_sorted ? 4 : 8), (unsigned)slices);
-            fn<<<grid, kBlock, few ? kClassLds : 0, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
-                                       m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
-                                       cols ? cols : m.row_ptr.as<int32_t>(),
-                                       m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),
-                                       (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls);
+        auto rows = [&](auto v_t, const int32_t *cols, int rounds, size_t lds = 0) {
+            auto fn = k_csr_rows<CPL, G, FU, OFF, decltype(v_t)>;
+            dim3 grid(rows_grid((const void *)fn, lds, tiles, slices, rounds), (unsigned)slices);
+            fn<<<grid, kBlock, lds, s>>>(m.n_medium_rows, m.long_rows.as<int32_t>(), m.row_ptr.as<int32_t>(),
+                                         m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
+                                         cols ? cols : m.row_ptr.as<int32_t>(),
+                                         m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),
+                                         (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls);
             GS_HIP(hipGetLastError());
         };
-        bool done = false;
-        if constexpr (CPL == 4) {  // reference classes: only the length-sorted lane shape
-            if (hot_cls) {
-                if (m.csr_grouped)
-                    rows(std::true_type{}, std::true_type{}, m.csr_colf.as<int32_t>());
-                else
-                    rows(std::true_type{}, std::false_type{}, m.csr_colf.as<int32_t>());
-                done = true;
+        auto pick = [&](auto na_t) {
+            constexpr int NA = decltype(na_t)::value;
+            constexpr int NB = G == 32 ? 2 : 1;  // (of long rows)
+            const int32_t *col = m.col.as<int32_t>();
+            const int rounds = m.csr_sorted ? 4 : 8;
+            if constexpr (CPL == 4) {
+                if (hot_cls) {  // reference classes: only the length-sorted lane shape
+                    const int32_t *tagged = m.csr_colf.as<int32_t>();
+                    if (m.csr_grouped) return rows(RowVariant<float, true, true, 0, NA, NB>{}, tagged, 32, kFewLds);
+                    return rows(RowVariant<float, true, false, 0, NA, NB>{}, tagged, 8);
+                }
             }
-        }
-        if (!done) {
-            if (m.csr_grouped)
-                rows(std::false_type{}, std::true_type{}, m.col.as<int32_t>());
-            else
-                rows(std::false_type{}, std::false_type{}, m.col.as<int32_t>());
-        }
+            if (m.csr_grouped) return rows(RowVariant<float, false, true, 0, NA, NB>{}, col, rounds);
+            if constexpr (CPL == 4 && OFF == kOff32) {
+                // Small skewed matrices, whose time is the longest rows' chain of
+                // round trips: 16 rows in flight.  Power-law graphs of 11 entries
+                // a row, 16 against 8: 275,000 entries 15.5 and 16.8 us (F = 64),
+                // 19.5 and 20.7 (128); 385,000 19.8 and 21.5, 26.4 and 26.5;
+                // 495,000 21.0 and 21.8, 30.1 and 28.8; 660,000 24.2 and 24.9,
+                // 38.2 and 36.7; without long rows slower (2,048 nodes 5.9, 5.1).
+                if (m.csr_sorted && m.n_long_rows > 0 && m.Z <= (F <= 64 ? 1 << 19 : 3 << 17))
+                    return rows(RowVariant<float, false, false, 16, NA>{}, col, rounds);
+                // Long rows in numbers: 4 rows in flight and 4 workgroups per CU.
+                // Against 8: 9,000 rows of 720 entries, X of 30,000 rows (7 to 18
+                // MiB) 131 -> 114 us at F = 64, 334 -> 274 at 128, 498 -> 398 at
+                // 156, X of 1,500 105.1 -> 103.7, 168 -> 155, 244 -> 235 (200);
+                // 15,000 rows of 300 162 -> 136 at 128, 348 -> 253 at 200; up to 3%
+                // slower near an X of 3.5 MiB (15,000 of 300 at F = 64, 13,283 of 375
+                // at 156) and below this line (3,302 rows of 165 at F = 176 30 -> 34,
+                // F = 32 143 -> 145).
+                if (m.Z >= 128 * m.R && F >= 64 && m.Z >= (1ll << 28) / F)
+                    return rows(RowVariant<float, false, false, 4, NA, NB>{}, col, 2 * rounds, kFewLds);
+            }
+            if constexpr (G == 32) {
+                if (m.Z >= kFillRow * m.R) return rows(RowVariant<float, false, false, 0, NA, NB>{}, col, rounds);
+            }
+            rows(RowVariant<float, false, false, 0, NA>{}, col, rounds);
+        };
+        pick(std::integral_constant<int, 1>{});
         if (n_huge) {
             dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
             k_csr_combine<CPL, G, float><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>() + m.n_medium_rows,
@@ -1145,10 +1183,11 @@ void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     double *work = n_huge ? (double *)work_for(m, fixed, need, s) : nullptr;
     auto launch = [&](auto g_t, auto mode_t) {
         constexpr int G = decltype(g_t)::value, M = decltype(mode_t)::value, GPB = kBlock / G;
-        const auto fn = k_csr_rows<4, G, M == kModeFull, M == kModeWide ? kOff64 : kOff32, false, false, double>;
+        const auto fn =
+            k_csr_rows<4, G, M == kModeFull, M == kModeWide ? kOff64 : kOff32, RowVariant<double, false, false>>;
         const int64_t tiles = n_wg + ceil_div(m.n_items - skip, GPB);
         if (!tiles) return;
-        dim3 grid(rows_grid((const void *)fn, tiles, slices, m.csr_sorted ? 4 : 8), (unsigned)slices);
+        dim3 grid(rows_grid((const void *)fn, 0, tiles, slices, m.csr_sorted ? 4 : 8), (unsigned)slices);
         fn<<<grid, kBlock, 0, s>>>(n_wg, m.long_rows.as<int32_t>(), rp, m.csr_chunk, m.n_items - skip, items + skip, col,
                                    val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0);
         GS_HIP(hipGetLastError());

@@ -289,6 +289,16 @@ def test_csr_many_long_rows_few_in_flight(F):
     check_spmm(case, case.build("csr"), graphgen.features_x(case.C, F, 94, "normal"))
 
 
+@pytest.mark.parametrize("n", [13, 14, 31, 32, 33, 64, 65])
+@pytest.mark.parametrize("F", [67, 100, 128])
+def test_csr_two_registers_of_entries(n, F):
+    # groups of 32 lanes around the average row length from which they hold 32
+    # entries in two registers (14), rows of 0 to 2 n entries with n of them
+    # on average: batches that end in either register, empty rows, a hub
+    case = _uniform_long_rows(400, 3000, 0, 2 * n, 400 + n, hubs=(7,) if n == 33 else ())
+    check_spmm(case, case.build("csr"), graphgen.features_x(case.C, F, 401, "normal"))
+
+
 @pytest.mark.parametrize("cpl", ["", "4", "16"])
 @pytest.mark.parametrize("ranges", ["", "1", "3", "50", "997"])
 def test_coo_ranges_split_rows(monkeypatch, ranges, cpl):
