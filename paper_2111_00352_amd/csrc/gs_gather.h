@@ -118,12 +118,13 @@ __device__ __forceinline__ const float *x_at(const float *X, uint32_t lo, uint32
 }
 
 // Entries J0 .. J0+B-1 of the group's batch (ref, v: one entry per lane and
-// register): B X rows requested back to back, then B multiply-adds, entry j
-// into the sums j % NA.  MASKED: entries past the t-th gather nothing (a dead
-// gather costs as much as a live one) and add -0 * 0 = -0, which leaves every
-// sum as it is.  CLS: entries whose lane set `cold` are gathered
-// non-temporally.
-template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, int NA, class Q, class A>
+// register): B X rows requested back to back, then B multiply-adds into acc:
+// one chain (NA = 1), or a chain for every four entries, which joins two sums in
+// turn (NA = 2; ODD: the first of them the second sum).  MASKED: entries past the
+// t-th gather nothing (a dead gather costs as much as a live one) and add
+// -0 * 0 = -0, which leaves every sum as it is.  CLS: entries whose lane set
+// `cold` are gathered non-temporally.
+template <int J0, int B, int NQ, int G, bool MASKED, int OFF, bool CLS, int NA, bool ODD, class Q, class A>
 __device__ __forceinline__ void gather_step(const RowRef<OFF> *ref, const float *v, const int *cold, int t,
                                             const float *X, const Q &cols, A *acc, int j0 = 0)
 {
@@ -174,15 +175,32 @@ __device__ __forceinline__ void gather_step(const RowRef<OFF> *ref, const float 
         else if (cols.ok(q))
             load(q);
     }
+    if constexpr (NA == 1) {
 #pragma unroll
-    for (int u = 0; u < B; u++)
+        for (int u = 0; u < B; u++)
 #pragma unroll
-        for (int q = 0; q < NQ; q++)
+            for (int q = 0; q < NQ; q++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                A &a = acc[((J0 + u) % NA * NQ + q) * 4 + i];
-                a = __builtin_elementwise_fma((A)vv[u], (A)x[u][q][i], a);
-            }
+                for (int i = 0; i < 4; i++)
+                    acc[4 * q + i] = __builtin_elementwise_fma((A)vv[u], (A)x[u][q][i], acc[4 * q + i]);
+    } else {
+        static_assert(NA == 2 && B % 4 == 0 && J0 % 4 == 0, "whole chains of four");
+#pragma unroll
+        for (int u = 0; u < B; u += 4)
+#pragma unroll
+            for (int q = 0; q < NQ; q++)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const A a = (A)vv[u] * (A)x[u][q][i];
+                    const A b = __builtin_elementwise_fma((A)vv[u + 1], (A)x[u + 1][q][i], a);
+                    const A c = __builtin_elementwise_fma((A)vv[u + 2], (A)x[u + 2][q][i], b);
+                    acc[(((J0 + u) / 4 + ODD) % 2 * NQ + q) * 4 + i] +=
+                        __builtin_elementwise_fma((A)vv[u + 3], (A)x[u + 3][q][i], c);
+                }
+        // (keeps the compiler from merging the ends of steps that add to
+        // different sums, which would put the sums into scratch memory)
+        asm volatile("" ::"n"(((J0 * 64 + B) * 2 + MASKED) * 2 + ODD));
+    }
 }
 
 // Adds the NA sums of N elements each, pairwise, into the first.
@@ -197,30 +215,51 @@ template <int NA, int N, class A> __device__ __forceinline__ void add_sums(A *ac
 }
 
 // The first t (1 .. kEntryBatch<G, NB>) entries of the group's batch, U at a
-// time (U a multiple of NA), a last half batch where it still holds every sum.
+// time, a last half batch where that still holds whole chains.
 template <int J0, int U, int NQ, int G, int NB, int OFF, bool CLS, int NA, class Q, class A>
 __device__ __forceinline__ void gather_entries_of(const RowRef<OFF> *ref, const float *v, const int *cold, int t,
                                                   const float *X, const Q &cols, A *acc)
 {
-    static_assert(U % NA == 0, "entry j belongs to the sums j % NA");
-    constexpr int H = U / 2 >= NA && U > 1 ? U / 2 : U;
+    constexpr int H = U / 2 >= (NA == 2 ? 4 : 1) ? U / 2 : U;
     if constexpr (G == 64) {
+        constexpr bool PAIR = NA == 2 && U == 4;  // two steps, one for each sum
         const int n = __builtin_amdgcn_readfirstlane(t);  // one row to the wave
         int j = 0;
-        for (; j + U <= n; j += U) gather_step<0, U, NQ, G, false, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
+        if constexpr (PAIR) {
+            for (; j + 2 * U <= n; j += 2 * U) {
+                gather_step<0, U, NQ, G, false, OFF, CLS, NA, false>(ref, v, cold, n, X, cols, acc, j);
+                gather_step<0, U, NQ, G, false, OFF, CLS, NA, true>(ref, v, cold, n, X, cols, acc, j + U);
+            }
+            if (j + U < n) {
+                gather_step<0, U, NQ, G, false, OFF, CLS, NA, false>(ref, v, cold, n, X, cols, acc, j);
+                gather_step<0, U, NQ, G, true, OFF, CLS, NA, true>(ref, v, cold, n, X, cols, acc, j + U);
+                return;
+            }
+        } else {
+            for (; j + U <= n; j += U)
+                gather_step<0, U, NQ, G, false, OFF, CLS, NA, false>(ref, v, cold, n, X, cols, acc, j);
+        }
         if (H < U && j < n && n - j <= H)
-            gather_step<0, H, NQ, G, true, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
+            gather_step<0, H, NQ, G, true, OFF, CLS, NA, false>(ref, v, cold, n, X, cols, acc, j);
         else if (j < n)
-            gather_step<0, U, NQ, G, true, OFF, CLS, NA>(ref, v, cold, n, X, cols, acc, j);
+            gather_step<0, U, NQ, G, true, OFF, CLS, NA, false>(ref, v, cold, n, X, cols, acc, j);
     } else if constexpr (J0 < kEntryBatch<G, NB>) {
         if (t >= J0 + U) {
-            gather_step<J0, U, NQ, G, false, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
+            gather_step<J0, U, NQ, G, false, OFF, CLS, NA, false>(ref, v, cold, t, X, cols, acc);
             gather_entries_of<J0 + U, U, NQ, G, NB, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
         } else if (t > J0) {
             if (H < U && t - J0 <= H)
-                gather_step<J0, H, NQ, G, true, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
+                gather_step<J0, H, NQ, G, true, OFF, CLS, NA, false>(ref, v, cold, t, X, cols, acc);
             else
-                gather_step<J0, U, NQ, G, true, OFF, CLS, NA>(ref, v, cold, t, X, cols, acc);
+                gather_step<J0, U, NQ, G, true, OFF, CLS, NA, false>(ref, v, cold, t, X, cols, acc);
+        }
+        if constexpr (NA == 2 && J0 == 0 && kEntryBatch<G, NB> == 4) {  // a batch is one chain: the other sum is next
+#pragma unroll
+            for (int i = 0; i < 4 * NQ; i++) {
+                const A a = acc[i];
+                acc[i] = acc[4 * NQ + i];
+                acc[4 * NQ + i] = a;
+            }
         }
     }
 }
@@ -254,8 +293,9 @@ __device__ __forceinline__ void store_quads(A *p, const Q &cols, const A *acc)
 // B X-row loads issued back to back, then B fused multiply-adds.  MASKED
 // batches may run past the last entry m: those slots gather nothing (on a
 // 512 x 512 mesh one dead gather a row made the DIA kernel 7% slower) and add
-// -0 * 0 = -0, which leaves every sum as it is.
-template <int B, int NQ, int G, bool MASKED, bool FENCE = false, class Q>
+// -0 * 0 = -0, which leaves every sum as it is.  Entry u of the batch goes to
+// the sums u % NA.
+template <int B, int NQ, int G, bool MASKED, int NA, bool FENCE = false, class Q>
 __device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m, const float *__restrict__ X, int64_t ldx,
                                              const Q &cols, float *acc)
 {
@@ -292,7 +332,27 @@ __device__ __forceinline__ void gather_batch(int cj, float vj, int j, int m, con
 #pragma unroll
         for (int q = 0; q < NQ; q++)
 #pragma unroll
-            for (int i = 0; i < 4; i++) acc[4 * q + i] = __builtin_fmaf(v[u], x[u][q][i], acc[4 * q + i]);
+            for (int i = 0; i < 4; i++) {
+                float &a = acc[(u % NA * NQ + q) * 4 + i];
+                a = __builtin_fmaf(v[u], x[u][q][i], a);
+            }
+}
+
+// The first m entries of the group's index batch, U at a time (U a multiple of
+// NA), a last half batch where it still holds every sum.
+template <int U, int NQ, int G, int NA, bool FENCE, class Q>
+__device__ __forceinline__ void gather_batches(int cj, float vj, int m, const float *__restrict__ X, int64_t ldx,
+                                               const Q &cols, float *acc)
+{
+    static_assert(U % NA == 0, "entry j belongs to the sums j % NA");
+    constexpr int H = U / 2 >= NA && U > 1 ? U / 2 : U;
+    int j = 0;
+    for (; j + U <= m; j += U) gather_batch<U, NQ, G, false, NA, FENCE>(cj, vj, j, m, X, ldx, cols, acc);
+    if (j >= m) return;
+    if (H < U && m - j <= H)
+        gather_batch<H, NQ, G, true, NA, FENCE>(cj, vj, j, m, X, ldx, cols, acc);
+    else
+        gather_batch<U, NQ, G, true, NA, FENCE>(cj, vj, j, m, X, ldx, cols, acc);
 }
 
 // One batch of B entries j .. j+B-1 of the group's index batch in a row

@@ -102,8 +102,7 @@ __device__ __forceinline__ void gather_span(const int32_t *__restrict__ col, con
 //  DEPTH    X rows in flight per lane group where it is not 8 of CPL = 4 (8
 //           float4 loads a lane; 4 where registers or L2 lines are short: fp64
 //           sums, class gathers)
-//  NA       sums per column, entry j going to sum j % NA (fp32 chains of a
-//           quarter or half the length)
+//  NA       2: chains of four entries that join two sums in turn, 1: one chain
 //  NB       registers of entries per batch
 template <class A_, bool CLS_, bool GROUPED_, int DEPTH_ = 0, int NA_ = 1, int NB_ = 1> struct RowVariant {
     typedef A_ A;
@@ -1010,14 +1009,29 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     // 30,000 rows of 6 10.6, 11.7, 10.8; mesh at F = 128 62.7, 60.2, 70.3).
     const bool short_rows = !m.csr_sorted && m.Z < 8 * m.R;
     const bool many_rows_per_wave = short_rows || (!m.csr_sorted && F >= 256 && m.Z < 64 * m.R);
-    int cpl = env_int("GS_CSR_CPL", !many_rows_per_wave ? 4 : F <= 64 ? 8 : 16);
+    // Chains of four entries, joining two sums in turn, where the operands are no
+    // 16-byte quads (F, strides or addresses) and on COO handles: the kernels
+    // that served those before this one summed in four chains, or in pieces of
+    // a few dozen entries, and one chain of up to 128 has up to 70% more error.
+    // Rows of under 4 entries have least error in one chain, which rounds each
+    // product with its addition.  At most 8 columns per lane hold them.
+    // Error (2-norm, against 64 bits) and time of the earlier kernels, of one
+    // chain, of fours: 30,011 rows of 15 at F = 47 5.6e-8 23.8 us, 7.4e-8 21.1,
+    // 5.6e-8 21.0; 140,001 of 20 at F = 33 5.9e-8 86.9, 8.4e-8 52.1, 5.9e-8 52.6;
+    // power-law graph of 10^6 entries, COO, F = 64 3.3e-8 43.8, 3.5e-8 33.6,
+    // 3.1e-8 33.9; four sums, entry j going to sum j % 4, 3.3e-8 35.0.
+    auto quads = [](const void *p, int64_t ld) { return (uintptr_t)p % 16 == 0 && ld % 4 == 0; };
+    const bool odd = F % 4 || !quads(X, ldx) || !quads(Y, ldy);
+    const bool fours = (odd || (m.fmt == GS_COO && !many_rows_per_wave)) && (m.csr_sorted || m.Z >= 4 * m.R);
+    int cpl = m.csr_grouped ? 4 : env_int("GS_CSR_CPL", !many_rows_per_wave ? 4 : F <= 64 || fours ? 8 : 16);
+    if (fours) cpl = std::min(cpl, 8);
     if (cpl != 4 && cpl != 8 && cpl != 16) cpl = 16;
     while (cpl > 4 && F < 4 * (int64_t)cpl) cpl /= 2;  // at least 4 lanes per group
     const int64_t lanes = ceil_div(F, cpl);
     const int g = lanes <= 4 ? 4 : lanes <= 8 ? 8 : lanes <= 16 ? 16 : lanes <= 32 ? 32 : 64;
     const int64_t slices = ceil_div(F, (int64_t)g * cpl);
     const bool full = (F % ((int64_t)g * cpl)) == 0;
-    const int mode = !fits_off32(m.C, ldx, F) ? kModeWide : full ? kModeFull : kModeAny;
+    const int mode = !fits_off32(m.C, ldx, F) ? kModeWide : full && !(fours && (odd || cpl > 4)) ? kModeFull : kModeAny;
     // Reference classes: the rows of the most referenced columns, whole
     // classes of them up to GS_CSR_HOT_KB (64 MiB) at this width, are
     // gathered with plain loads, every other row non-temporally, so that
@@ -1052,7 +1066,7 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     // 128 KiB) measured 193 / 280 / 480 us against 209 us without staging
     // (with today's plain kernel both take 203 us there).
     int win_T = 0, win_h = 0;
-    if (m.n_long_rows == 0 && !m.csr_grouped) pick_window(m, (int64_t)g * cpl * 4, win_T, win_h);
+    if (m.n_long_rows == 0 && !m.csr_grouped && !fours) pick_window(m, (int64_t)g * cpl * 4, win_T, win_h);
     auto launch = [&](auto cpl_t, auto g_t, auto mode_t) {
         constexpr int CPL = decltype(cpl_t)::value, G = decltype(g_t)::value, M = decltype(mode_t)::value;
         constexpr bool FU = M == kModeFull;
@@ -1096,8 +1110,10 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
                     return rows(RowVariant<float, true, false, 0, NA, NB>{}, tagged, 8);
                 }
             }
-            if (m.csr_grouped) return rows(RowVariant<float, false, true, 0, NA, NB>{}, col, rounds);
-            if constexpr (CPL == 4 && OFF == kOff32) {
+            if constexpr (CPL == 4) {
+                if (m.csr_grouped) return rows(RowVariant<float, false, true, 0, NA, NB>{}, col, rounds);
+            }
+            if constexpr (CPL == 4 && G >= 16 && OFF == kOff32) {
                 // Small skewed matrices, whose time is the longest rows' chain of
                 // round trips: 16 rows in flight.  Power-law graphs of 11 entries
                 // a row, 16 against 8: 275,000 entries 15.5 and 16.8 us (F = 64),
@@ -1122,7 +1138,14 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
             }
             rows(RowVariant<float, false, false, 0, NA>{}, col, rounds);
         };
-        pick(std::integral_constant<int, 1>{});
+        if constexpr (CPL == 4 || (CPL == 8 && M != kModeFull)) {
+            if (fours)
+                pick(std::integral_constant<int, 2>{});
+            else
+                pick(std::integral_constant<int, 1>{});
+        } else {
+            pick(std::integral_constant<int, 1>{});
+        }
         if (n_huge) {
             dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
             k_csr_combine<CPL, G, float><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>() + m.n_medium_rows,

@@ -27,7 +27,8 @@ constexpr int kBlock = 256;
 
 // FOLD: rows may hold more than kChainFold slots; their running sum is then
 // added into a total every kChainFold slots (compiled out otherwise).
-template <int CPL, int G, bool FULL, bool FOLD>
+// NA: sums per column, entry j going to sum j % NA.
+template <int CPL, int G, bool FULL, bool FOLD, int NA>
 __global__ __launch_bounds__(kBlock) void k_ell_fast(int64_t R, int64_t K,
                                                      const int32_t *__restrict__ ec,
                                                      const float *__restrict__ ev,
@@ -46,9 +47,9 @@ __global__ __launch_bounds__(kBlock) void k_ell_fast(int64_t R, int64_t K,
     for (int64_t tile = xcd_tile(blockIdx.x, gridDim.x); tile < tiles; tile += gridDim.x) {
         const int64_t row = tile * GPB + g;
         if (row >= R) break;
-        float acc[CPL], tot[FOLD ? CPL : 1];
+        float acc[NA * CPL], tot[FOLD ? CPL : 1];
 #pragma unroll
-        for (int i = 0; i < CPL; i++) acc[i] = 0.0f;
+        for (int i = 0; i < NA * CPL; i++) acc[i] = 0.0f;
         if constexpr (FOLD) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) tot[i] = 0.0f;
@@ -68,30 +69,25 @@ __global__ __launch_bounds__(kBlock) void k_ell_fast(int64_t R, int64_t K,
             }
             const int m = __popcll((__ballot(cj >= 0) >> gbase) & gmask);
             if (cj < 0) cj = 0;  // padding lanes gather row 0 and are masked
-            int j = 0;
-            for (; j + U <= m; j += U) gather_batch<U, NQ, G, false, FOLD>(cj, vj, j, m, X, ldx, cols, acc);
-            if (j < m) {
-                if (U > 1 && m - j <= U / 2)
-                    gather_batch<(U > 1 ? U / 2 : 1), NQ, G, true, FOLD>(cj, vj, j, m, X, ldx, cols, acc);
-                else
-                    gather_batch<U, NQ, G, true, FOLD>(cj, vj, j, m, X, ldx, cols, acc);
-            }
+            gather_batches<U, NQ, G, NA, FOLD>(cj, vj, m, X, ldx, cols, acc);
             if (m < G) {  // padding reached: the row has no more slots
                 more = false;
                 break;
             }
           }
           if constexpr (FOLD) {
+            add_sums<NA, CPL>(acc);
 #pragma unroll
-            for (int i = 0; i < CPL; i++) {
-                tot[i] += acc[i];
-                acc[i] = 0.0f;
-            }
+            for (int i = 0; i < CPL; i++) tot[i] += acc[i];
+#pragma unroll
+            for (int i = 0; i < NA * CPL; i++) acc[i] = 0.0f;
           }
         }
         if constexpr (FOLD) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] = tot[i];
+        } else {
+            add_sums<NA, CPL>(acc);
         }
         store_quads_stream<NQ>(Y + row * ldy, cols, acc);
     }
@@ -154,8 +150,9 @@ __global__ __launch_bounds__(kBlock) void k_ell_window(int64_t R, int64_t C, int
 }
 
 // FOLD: more than kChainFold diagonals (the running sum of a row is added
-// into a total every kChainFold diagonals; compiled out otherwise).
-template <int CPL, int G, bool FULL, bool FOLD>
+// into a total every kChainFold diagonals; compiled out otherwise).  NA: sums
+// per column, the j-th stored diagonal of a batch going to sum j % NA.
+template <int CPL, int G, bool FULL, bool FOLD, int NA>
 __global__ __launch_bounds__(kBlock) void k_dia_fast(int64_t R, int64_t C, int64_t ND,
                                                      const int32_t *__restrict__ offsets,
                                                      const float *__restrict__ data,
@@ -174,20 +171,20 @@ __global__ __launch_bounds__(kBlock) void k_dia_fast(int64_t R, int64_t C, int64
     for (int64_t tile = xcd_tile(blockIdx.x, gridDim.x); tile < tiles; tile += gridDim.x) {
         const int64_t row = tile * GPB + g;
         if (row >= R) break;
-        float acc[CPL], tot[FOLD ? CPL : 1];
+        float acc[NA * CPL], tot[FOLD ? CPL : 1];
 #pragma unroll
-        for (int i = 0; i < CPL; i++) acc[i] = 0.0f;
+        for (int i = 0; i < NA * CPL; i++) acc[i] = 0.0f;
         if constexpr (FOLD) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) tot[i] = 0.0f;
         }
         for (int64_t db = 0; db < ND; db += G) {
             if (FOLD && db > 0 && db % kChainFold == 0) {  // fold the running chain every kChainFold diagonals
+                add_sums<NA, CPL>(acc);
 #pragma unroll
-                for (int i = 0; i < CPL; i++) {
-                    tot[i] += acc[i];
-                    acc[i] = 0.0f;
-                }
+                for (int i = 0; i < CPL; i++) tot[i] += acc[i];
+#pragma unroll
+                for (int i = 0; i < NA * CPL; i++) acc[i] = 0.0f;
             }
             int cj = 0;
             float vj = 0.0f;
@@ -207,15 +204,9 @@ __global__ __launch_bounds__(kBlock) void k_dia_fast(int64_t R, int64_t C, int64
             const int pick = bits ? __ffsll((unsigned long long)bits) - 1 : 0;
             const int cc = __shfl(cj, pick, G);
             const float vv = __shfl(vj, pick, G);
-            int j = 0;
-            for (; j + U <= m; j += U) gather_batch<U, NQ, G, false, FOLD>(cc, vv, j, m, X, ldx, cols, acc);
-            if (j < m) {
-                if (U > 1 && m - j <= U / 2)
-                    gather_batch<(U > 1 ? U / 2 : 1), NQ, G, true, FOLD>(cc, vv, j, m, X, ldx, cols, acc);
-                else
-                    gather_batch<U, NQ, G, true, FOLD>(cc, vv, j, m, X, ldx, cols, acc);
-            }
+            gather_batches<U, NQ, G, NA, FOLD>(cc, vv, m, X, ldx, cols, acc);
         }
+        add_sums<NA, CPL>(acc);
         if constexpr (FOLD) {
 #pragma unroll
             for (int i = 0; i < CPL; i++) acc[i] += tot[i];
@@ -236,13 +227,19 @@ struct FastShape {
     int cpl, g;
     int64_t slices;
     bool full;
+    bool odd;  // the operands are no 16-byte quads
 };
 
 // Lane shape for natural-order kernels: 8 or 16 columns per lane (more rows
-// per wave), a group never wider than 64 lanes.
-bool fast_shape(int64_t F, FastShape &sh)
+// per wave), a group never wider than 64 lanes.  Operands that are no 16-byte
+// quads (F, strides or addresses) are summed in two chains, as the kernels that
+// took them before these did (error of a 512 x 512 mesh at F = 47 4.35e-8, in
+// one chain 4.38e-8).
+bool fast_shape(const float *X, int64_t ldx, const float *Y, int64_t ldy, int64_t F, FastShape &sh)
 {
     if (F < 4) return false;
+    auto quads = [](const void *p, int64_t ld) { return (uintptr_t)p % 16 == 0 && ld % 4 == 0; };
+    sh.odd = F % 4 || !quads(X, ldx) || !quads(Y, ldy);
     // measured: 8 columns per lane is best up to F = 128, 16 beyond
     int cpl = env_int("GS_FAST_CPL", F <= 128 ? 8 : 16);
     if (cpl != 4 && cpl != 8 && cpl != 16) cpl = 16;
@@ -252,7 +249,7 @@ bool fast_shape(int64_t F, FastShape &sh)
     sh.cpl = cpl;
     sh.g = g;
     sh.slices = ceil_div(F, (int64_t)g * cpl);
-    sh.full = F % ((int64_t)g * cpl) == 0;
+    sh.full = F % ((int64_t)g * cpl) == 0 && !sh.odd;
     return true;
 }
 
@@ -274,6 +271,22 @@ bool dispatch_fast(const FastShape &sh, Fn &&fn)
     return false;
 }
 
+// go(fold, sums): whether chains are folded, and two chains for odd operands
+// (which are never FULL).
+template <bool FULL, class Go> void by_sums(bool fold, bool odd, Go &&go)
+{
+    auto with = [&](auto na_t) {
+        if (fold)
+            go(std::true_type{}, na_t);
+        else
+            go(std::false_type{}, na_t);
+    };
+    if constexpr (!FULL) {
+        if (odd) return with(std::integral_constant<int, 2>{});
+    }
+    with(std::integral_constant<int, 1>{});
+}
+
 // Measured on the mesh and block workloads: 8 resident-workgroup multiples
 // (about one row tile per workgroup) beat a tighter persistent grid.
 unsigned persistent_grid(int64_t tiles, int64_t slices)
@@ -289,12 +302,12 @@ bool spmm_ell_fast(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
                    hipStream_t s)
 {
     FastShape sh;
-    if (!fast_shape(F, sh)) return false;
+    if (!fast_shape(X, ldx, Y, ldy, F, sh)) return false;
     return dispatch_fast(sh, [&](auto c_t, auto g_t, auto f_t) {
         constexpr int CPL = decltype(c_t)::value, G = decltype(g_t)::value;
         constexpr bool FU = decltype(f_t)::value;
         int T = 0, h = 0;
-        if (m.K <= kChainFold && pick_window(m, (int64_t)G * CPL * 4, T, h)) {
+        if (m.K <= kChainFold && !sh.odd && pick_window(m, (int64_t)G * CPL * 4, T, h)) {
             const int64_t ntiles = ceil_div(m.R, T);
             const size_t lds = (size_t)(T + 2 * h) * G * CPL * 4;
             dim3 grid(persistent_grid(ntiles, sh.slices), (unsigned)sh.slices);
@@ -306,12 +319,11 @@ bool spmm_ell_fast(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         }
         const int64_t tiles = ceil_div(m.R, kBlock / G);
         dim3 grid(persistent_grid(tiles, sh.slices), (unsigned)sh.slices);
-        if (m.K > kChainFold)
-            k_ell_fast<CPL, G, FU, true><<<grid, kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(),
-                                                                  m.ell_val.as<float>(), X, ldx, Y, ldy, F);
-        else
-            k_ell_fast<CPL, G, FU, false><<<grid, kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(),
-                                                                   m.ell_val.as<float>(), X, ldx, Y, ldy, F);
+        auto go = [&](auto fold_t, auto na_t) {
+            k_ell_fast<CPL, G, FU, decltype(fold_t)::value, decltype(na_t)::value><<<grid, kBlock, 0, s>>>(
+                m.R, m.K, m.ell_col.as<int32_t>(), m.ell_val.as<float>(), X, ldx, Y, ldy, F);
+        };
+        by_sums<FU>(m.K > kChainFold, sh.odd, go);
         GS_HIP(hipGetLastError());
     });
 }
@@ -320,18 +332,17 @@ bool spmm_dia_fast(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
                    hipStream_t s)
 {
     FastShape sh;
-    if (!fast_shape(F, sh)) return false;
+    if (!fast_shape(X, ldx, Y, ldy, F, sh)) return false;
     return dispatch_fast(sh, [&](auto c_t, auto g_t, auto f_t) {
         constexpr int CPL = decltype(c_t)::value, G = decltype(g_t)::value;
         constexpr bool FU = decltype(f_t)::value;
         const int64_t tiles = ceil_div(m.R, kBlock / G);
         dim3 grid(persistent_grid(tiles, sh.slices), (unsigned)sh.slices);
-        if (m.ND > kChainFold)
-            k_dia_fast<CPL, G, FU, true><<<grid, kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(),
-                                                                  m.dia.as<float>(), X, ldx, Y, ldy, F);
-        else
-            k_dia_fast<CPL, G, FU, false><<<grid, kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(),
-                                                                   m.dia.as<float>(), X, ldx, Y, ldy, F);
+        auto go = [&](auto fold_t, auto na_t) {
+            k_dia_fast<CPL, G, FU, decltype(fold_t)::value, decltype(na_t)::value><<<grid, kBlock, 0, s>>>(
+                m.R, m.C, m.ND, m.offsets.as<int32_t>(), m.dia.as<float>(), X, ldx, Y, ldy, F);
+        };
+        by_sums<FU>(m.ND > kChainFold, sh.odd, go);
         GS_HIP(hipGetLastError());
     });
 }
