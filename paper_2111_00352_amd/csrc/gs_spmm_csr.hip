@@ -1039,10 +1039,14 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
     // Measured on the 2M-row power-law graph at F = 128 (52M entries, rows
     // of columns with at least 64 entries hot): 3426 -> 3126 us; budgets of
     // 4 / 32 / 128 / 256 MiB gave 4185 / 3286 / 3231 / 3306 us.  Not used
-    // when the rows of every referenced column fit the budget.
+    // when the rows of every referenced column fit the budget, nor (its gathers
+    // keep 4 rows in flight) for rows of under 6 entries on an X of up to 4
+    // budgets: 150,000 rows of 3 at F = 128 51.9 us, without 48.2, of 5 61.3,
+    // 59.5; of 17 138.4, 144.7; 10^6 rows of 7 478, 497.
     int hot_cls = 0;
-    if (m.col_cls.p && cpl == 4) {
-        const int64_t budget = (int64_t)env_int("GS_CSR_HOT_KB", 65536) * 1024 / (F * 4);
+    const int64_t hot_kb = env_int("GS_CSR_HOT_KB", 65536);
+    if (m.col_cls.p && cpl == 4 && (m.Z >= 6 * m.R || m.C * F * 4 > hot_kb * 4096)) {
+        const int64_t budget = hot_kb * 1024 / (F * 4);
         int64_t cum = 0;
         for (int c = 15; c >= 1 && !hot_cls; c--) {
             cum += m.col_class_cols[c];
