@@ -226,6 +226,24 @@ def test_spmm_any_width_and_alignment(fmt, F):
         assert (got[:, :3 - off] == 7.0).all() and (got[:, 3 - off + F:] == 7.0).all(), "wrote outside Y"
 
 
+@pytest.mark.parametrize("F", [16, 48, 64, 256, 320])
+def test_bsr16_remainder_rows(F):
+    # 16 x 16 blocks too sparse for the matrix cores run as rows: full batches
+    # and tails of every length (rows of 0..40 entries, a hub), one slice and
+    # four slices of columns to a workgroup.  X rows that no entry references
+    # hold NaN.
+    case = _uniform_long_rows(230, 2300, 0, 40, 60 + F, hubs=(3,))
+    keep = ~((case.crow == 3) & (case.ccol >= 2100))
+    case = Case(case.R, case.C, case.crow[keep], case.ccol[keep], case.cval[keep])
+    used = np.zeros(case.C, bool)
+    used[case.ccol] = True
+    X = graphgen.features_x(case.C, F, 62, "normal")
+    Yref, M = oracle.spmm(case.R, case.rp, case.ccol, case.cval, X)
+    X[~used] = np.nan
+    ok, worst = oracle.check_spmm(_host(case.build("bsr").spmm(_dev(X))), Yref, M)
+    assert ok, worst
+
+
 def _chained_sums(case, X, chains):
     # A.X in fp32 with `chains` running sums per row and column, entry k of a row
     # in chain k % chains (a remainder in the first), added pairwise at the end
