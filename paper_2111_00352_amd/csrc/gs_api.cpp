@@ -96,6 +96,13 @@ int gs_build_format(const gs_coo *A, int fmt, const gs_build_opts *opts, gs_stre
         check_coo(A);
         const gs_build_opts o = resolve_opts(opts);
         hipStream_t s = (hipStream_t)stream;
+        if (fmt == GS_COO) {
+            CanonCOO c;
+            canonicalize(*A, o.assume_canonical != 0, s, c);
+            *out = coo_from_canon(std::move(c), s);
+            if (bytes_required) *bytes_required = (*out)->device_bytes;
+            return;
+        }
         gs_matrix_ *csr = build_csr(A, o, s, fmt == GS_CSR);
         if (fmt == GS_CSR) {
             if (bytes_required) *bytes_required = csr->device_bytes;

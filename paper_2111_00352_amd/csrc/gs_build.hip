@@ -882,6 +882,15 @@ gs_matrix_ *csr_from_canon(CanonCOO &&c, hipStream_t s, bool plan)
     return m;
 }
 
+gs_matrix_ *coo_from_canon(CanonCOO &&c, hipStream_t s)
+{
+    gs_matrix_ *m = csr_from_canon(std::move(c), s, true);
+    m->fmt = GS_COO;
+    m->row = std::move(c.row);
+    m->device_bytes = format_bytes(GS_COO, m->R, m->C, m->Z, 0, 0, 0, 0);
+    return m;
+}
+
 uint64_t format_bytes(int fmt, int64_t R, int64_t C, int64_t Z, int64_t K, int64_t ND, int64_t nb,
                       int b)
 {

@@ -252,6 +252,10 @@ void canonicalize(const gs_coo &A, bool assume_canonical, hipStream_t s, CanonCO
 // (feature extraction reads only row_ptr / col).
 gs_matrix_ *csr_from_canon(CanonCOO &&c, hipStream_t s, bool plan = true);
 
+// Builds a COO handle from canonical COO (takes ownership of its arrays), whose
+// row pointers and row plan are those of CSR.
+gs_matrix_ *coo_from_canon(CanonCOO &&c, hipStream_t s);
+
 // Builds format fmt from a CSR handle (not consumed).
 gs_matrix_ *convert_from_csr(const gs_matrix_ &csr, int fmt, int bsr_block, uint64_t max_bytes,
                              hipStream_t s, uint64_t *bytes_required);
