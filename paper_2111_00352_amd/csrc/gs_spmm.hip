@@ -352,7 +352,11 @@ struct Shape {
     int64_t fslices;  // grid.y
 };
 
-// Four columns per lane from F = 4 on (any alignment, see Quads), one below.
+// Lanes of a group of the kernels for fewer than four columns (CSR, ELL, DIA),
+// one column per lane.
+constexpr int kNarrow = 8;
+
+// BSR: four columns per lane from F = 4 on (any alignment, see Quads), one below.
 Shape pick_shape(int64_t F)
 {
     const int vec = F >= 4 ? 4 : 1;
@@ -391,25 +395,19 @@ void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
         plan_csr(m, s);
     }
     if (spmm_csr_vec4(m, X, ldx, Y, ldy, F, s, fixed)) return;
-    const Shape sh = pick_shape(F);
+    // fewer than four columns
+    constexpr int GPB = kBlock / kNarrow;
     float *work = m.n_long_chunks ? (float *)work_for(m, fixed, (size_t)m.n_long_chunks * F * 4, s) : nullptr;
-    dispatch(sh, [&]<int VEC, int G>() {
-        constexpr int GPB = kBlock / G;
-        if (m.n_items) {
-            dim3 grid(u32_grid(ceil_div(m.n_items, GPB)), (unsigned)sh.fslices);
-            k_csr_items_generic<VEC, G><<<grid, kBlock, 0, s>>>(
-                m.n_items, m.csr_items.as<int4>(), m.col.as<int32_t>(), m.val.as<float>(), X, ldx, Y,
-                ldy, F, work);
-            GS_HIP(hipGetLastError());
-        }
-        if (m.n_long_rows) {
-            dim3 g2(u32_grid(ceil_div(m.n_long_rows, GPB)), (unsigned)sh.fslices);
-            k_csr_combine<VEC, G><<<g2, kBlock, 0, s>>>(m.long_rows.as<int32_t>(),
-                                                        m.long_first.as<int32_t>(), m.n_long_rows,
-                                                        work, Y, ldy, F);
-            GS_HIP(hipGetLastError());
-        }
-    });
+    if (m.n_items) {
+        k_csr_items_generic<1, kNarrow><<<u32_grid(ceil_div(m.n_items, GPB)), kBlock, 0, s>>>(
+            m.n_items, m.csr_items.as<int4>(), m.col.as<int32_t>(), m.val.as<float>(), X, ldx, Y, ldy, F, work);
+        GS_HIP(hipGetLastError());
+    }
+    if (m.n_long_rows) {
+        k_csr_combine<1, kNarrow><<<u32_grid(ceil_div(m.n_long_rows, GPB)), kBlock, 0, s>>>(
+            m.long_rows.as<int32_t>(), m.long_first.as<int32_t>(), m.n_long_rows, work, Y, ldy, F);
+        GS_HIP(hipGetLastError());
+    }
 }
 
 // COO: the entries are in row order, so their column and value arrays are
@@ -442,32 +440,18 @@ void spmm_ell(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
               hipStream_t s)
 {
     if (spmm_ell_fast(m, X, ldx, Y, ldy, F, s)) return;
-    const Shape sh = pick_shape(F);
-    dispatch(sh, [&]<int VEC, int G>() {
-        constexpr int GPB = kBlock / G;
-        const int64_t tiles = ceil_div(m.R, GPB);
-        if (!tiles) return;
-        dim3 grid(u32_grid(tiles), (unsigned)sh.fslices);
-        k_ell<VEC, G><<<grid, kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(), m.ell_val.as<float>(),
-                                              X, ldx, Y, ldy, F, tiles);
-        GS_HIP(hipGetLastError());
-    });
+    const int64_t tiles = ceil_div(m.R, kBlock / kNarrow);  // fewer than four columns
+    k_ell<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(), m.ell_val.as<float>(), X, ldx, Y, ldy, F, tiles);
+    GS_HIP(hipGetLastError());
 }
 
 void spmm_dia(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s)
 {
     if (spmm_dia_fast(m, X, ldx, Y, ldy, F, s)) return;
-    const Shape sh = pick_shape(F);
-    dispatch(sh, [&]<int VEC, int G>() {
-        constexpr int GPB = kBlock / G;
-        const int64_t tiles = ceil_div(m.R, GPB);
-        if (!tiles) return;
-        dim3 grid(u32_grid(tiles), (unsigned)sh.fslices);
-        k_dia<VEC, G><<<grid, kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(), m.dia.as<float>(),
-                                              X, ldx, Y, ldy, F, tiles);
-        GS_HIP(hipGetLastError());
-    });
+    const int64_t tiles = ceil_div(m.R, kBlock / kNarrow);  // fewer than four columns
+    k_dia<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(), m.dia.as<float>(), X, ldx, Y, ldy, F, tiles);
+    GS_HIP(hipGetLastError());
 }
 
 void spmm_bsr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
