@@ -162,8 +162,10 @@ int gs_spmm(gs_matrix A, const float *X, int64_t ldx, float *Y, int64_t ldy, int
  * array and leaves it in an undefined state: calls that may overlap in time
  * on one device (other streams, other threads) race, so order them.
  * Supported for CSR, ELL, DIA, BSR and CSC handles built by gs_build_format
- * or gs_convert.  Errors: GS_ERR_UNSUPPORTED for a COO handle (its range
- * tables are built, and allocated, per launch shape on first use) and when
+ * or gs_convert.  Where the partial sums of a CSC handle's long rows exceed the
+ * array, a workgroup sums each of those rows instead, in another order in fp64,
+ * which can change a result by one fp32 step where the sum sits on a rounding
+ * boundary.  Errors: GS_ERR_UNSUPPORTED for a COO handle and when
  * the workspace would exceed GS_NOALLOC_SCRATCH_BYTES (CSR: at most 4 * F
  * bytes per 128 entries of the rows longer than 128 entries, as many as the
  * row plan cuts into chunks; CSC: 8 * n_rows * F bytes); otherwise as
@@ -183,7 +185,12 @@ typedef struct {
     int32_t bsr_block;     /* b for BSR, else 0 */
     int64_t n_rows, n_cols, nnz;
     int64_t param;         /* ELL: K, DIA: N_diags, BSR: number of blocks, else 0 */
-    uint64_t device_bytes; /* bytes of the format's arrays (excluding workspaces) */
+    uint64_t device_bytes; /* bytes of the format's arrays, as in gs_build_format: the footprint of
+                              the format.  What a handle keeps beside them for its SpMM is not
+                              counted: workspaces, the row plan of CSR, COO and CSC (16 bytes a
+                              row and chunk) with COO's row pointers and tagged columns (4 bytes
+                              an entry, matrices gathered by class), BSR's remainder rows (8
+                              bytes an entry), CSC's row form (8 bytes an entry, 4 a row) */
 } gs_matrix_info;
 
 int gs_get_info(gs_matrix A, gs_matrix_info *info);

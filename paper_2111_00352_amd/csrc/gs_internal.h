@@ -322,7 +322,7 @@ bool pick_window(const gs_matrix_ &m, int64_t row_bytes, int &T, int &h);
 void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
                    hipStream_t s, const WorkArea *fixed = nullptr);
 
-// Vectorised CSR path; returns false when F / alignment do not allow it.
+// CSR and COO path of four columns and more; returns false for fewer.
 bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
                    hipStream_t s, const WorkArea *fixed = nullptr);
 
@@ -356,7 +356,7 @@ bool spmm_bsr16_mfma(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64
 void ensure_work(gs_matrix_ &m, size_t bytes, hipStream_t s);
 
 // Where an SpMM call takes its F-dependent workspace (partial sums of split
-// rows, the CSC accumulator): the handle's own buffer, grown through the
+// rows): the handle's own buffer, grown through the
 // allocator on demand (fixed == nullptr), or a fixed buffer of cap bytes that
 // is never grown.
 struct WorkArea {

@@ -1,5 +1,5 @@
 // The allocation-free SpMM entry point: gs_spmm whose F-dependent workspace
-// (partial sums of split CSR rows, the CSC fp64 accumulator) lives in a fixed
+// (partial sums of split CSR and CSC rows) lives in a fixed
 // device array instead of the handle's own buffer, so that the call never
 // reaches the allocator.
 //

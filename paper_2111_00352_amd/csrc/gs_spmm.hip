@@ -413,10 +413,11 @@ void spmm_csr(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 // COO: the entries are in row order, so their column and value arrays are
 // those of the CSR form and the row kernel reads them as they are, by the row
 // pointers and the row plan that the handle keeps beside them.  (Equal ranges
-// of entries with a segmented sum, the schedule this replaces, took 43.8 us on
-// the power-law graph at F = 64 against 34.3 us, 255 against 185 us on the
-// block graph and 3.5 against 3.0 ms on the 2M-row graph: cut rows went through
-// carry slots and a second launch.)
+// of entries with a segmented sum, the schedule this replaces, took 43.7 us on
+// the power-law graph at F = 64 against 33.7 us, 247 against 191 us on the
+// block graph and 3.41 against 2.89 ms on the 2M-row graph: cut rows went
+// through carry slots and a second launch.  The plan is made with the handle:
+// building the power-law graph takes 248 us, without it 167.)
 void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s, const WorkArea *fixed)
 {
@@ -427,8 +428,10 @@ void spmm_coo(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 // CSC: rows gathered from the handle's row form, the products summed in fp64
 // (they are exact there) and rounded once.  Scattering the columns into an
 // R x F fp64 accumulator with atomics, which this replaces, took 781 us on the
-// power-law graph at F = 64 (180 billion atomics a second) against 38 us.
-// Without allocation the accumulator's size, 8 R F bytes, remains the limit.
+// power-law graph at F = 64 (180 billion atomics a second) against 37 us.
+// Without allocation 8 R F bytes stay the limit that the interface states (they
+// were the accumulator's), though partial sums of long rows are all that is
+// kept now.
 void spmm_csc(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy, int64_t F,
               hipStream_t s, const WorkArea *fixed)
 {
@@ -441,7 +444,8 @@ void spmm_ell(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 {
     if (spmm_ell_fast(m, X, ldx, Y, ldy, F, s)) return;
     const int64_t tiles = ceil_div(m.R, kBlock / kNarrow);  // fewer than four columns
-    k_ell<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(), m.ell_val.as<float>(), X, ldx, Y, ldy, F, tiles);
+    k_ell<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.K, m.ell_col.as<int32_t>(), m.ell_val.as<float>(), X,
+                                                         ldx, Y, ldy, F, tiles);
     GS_HIP(hipGetLastError());
 }
 
@@ -450,7 +454,8 @@ void spmm_dia(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t ldy,
 {
     if (spmm_dia_fast(m, X, ldx, Y, ldy, F, s)) return;
     const int64_t tiles = ceil_div(m.R, kBlock / kNarrow);  // fewer than four columns
-    k_dia<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(), m.dia.as<float>(), X, ldx, Y, ldy, F, tiles);
+    k_dia<1, kNarrow><<<u32_grid(tiles), kBlock, 0, s>>>(m.R, m.C, m.ND, m.offsets.as<int32_t>(), m.dia.as<float>(), X,
+                                                         ldx, Y, ldy, F, tiles);
     GS_HIP(hipGetLastError());
 }
 

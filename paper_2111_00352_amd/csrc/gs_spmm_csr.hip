@@ -13,12 +13,14 @@
 // Every sequential fp32 chain stays within `chunk` terms and every combine
 // runs in a fixed order, so results are deterministic.
 //
-// Lane layout: lane l of a group holds float4 q at column c0 + 4*G*q, so one
-// load instruction reads G*16 contiguous bytes of an X row.  Entries are
-// fetched G at a time (one per lane) and broadcast by shuffles; X rows are
-// gathered several at a time (8 float4 loads in flight per lane) before any
-// is consumed; the last batch of a row is masked with a select.  The grid is
-// persistent (a few workgroups per CU), long-row tiles first.
+// Lane layout: lane l of a group holds column quad q at c0 + 4*G*q, so one load
+// instruction reads G*16 contiguous bytes of an X row; a width that is no
+// multiple of 4 ends in a quad that overlaps the one before.  Entries are
+// fetched 16 or 32 at a time (a whole wave: 64), one per lane, a batch ahead,
+// and broadcast by DPP (a whole wave: from scalar registers); X rows are
+// gathered several at a time before any is consumed, the last of them only up
+// to the row's end.  The grid is persistent (a few workgroups per CU),
+// long-row tiles first.
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>

@@ -103,12 +103,7 @@ def check_spmm(case, m, X, rows=None, ldx_pad=0, ldy_pad=0):
     Y2 = m.spmm(Xv)
     torch.cuda.synchronize()
     Yh = _host(Y)
-    if m.format == "csc":
-        # fp64 atomics in varying order, rounded once: at most one fp32 step apart
-        Y2h = _host(Y2)
-        assert np.all(np.abs(Yh - Y2h) <= np.spacing(np.abs(Yh).astype(np.float32))), "CSC repeat differs"
-    else:
-        assert (_bits(Yh) == _bits(_host(Y2))).all(), "SpMM not deterministic"
+    assert (_bits(Yh) == _bits(_host(Y2))).all(), "SpMM not deterministic"
     if ldy_pad:
         assert (_host(out[:, F:]) == 7.0).all(), "columns beyond F were written"
     if rows is None:
@@ -357,35 +352,18 @@ def test_csr_two_registers_of_entries(n, F):
     check_spmm(case, case.build("csr"), graphgen.features_x(case.C, F, 401, "normal"))
 
 
-@pytest.mark.parametrize("cpl", ["", "4", "16"])
-@pytest.mark.parametrize("ranges", ["", "1", "3", "50", "997"])
-def test_coo_ranges_split_rows(monkeypatch, ranges, cpl):
-    # the COO kernel cuts the entries into equal ranges, each boundary moved
-    # to the next row start within 32 entries, so only longer rows are cut:
-    # rows at and around 32 and 128 entries (the 128-entry fold), rows cut
-    # over one or dozens of ranges (997 ranges of about 3 entries, most of
-    # them empty after the move), back to back, at the first and last row,
-    # with empty rows between them; one range sums every row in a single
-    # pass, folding the long ones.  Each lane layout of the main pass: the
-    # rule's choice, 4 and 16 columns per lane
-    if ranges:
-        monkeypatch.setenv("GS_COO_RANGES", ranges)
+@pytest.mark.parametrize("cpl", ["", "4", "8", "16"])
+@pytest.mark.parametrize("thr,chunk,wg", [(128, 128, 1024), (32, 32, 64), (16, 8, 100000), (200, 64, 201)])
+def test_coo_row_plan(monkeypatch, thr, chunk, wg, cpl):
+    # the row plan that a COO handle keeps, under different long-row, chunk and
+    # workgroup thresholds and lane layouts: rows at and around 32 and 128
+    # entries (the chunk length), short, workgroup-wide and chunked rows back to
+    # back, at the first and last row, with empty rows between them
+    monkeypatch.setenv("GS_CSR_LONG_ROW", str(thr))
+    monkeypatch.setenv("GS_CSR_CHUNK", str(chunk))
+    monkeypatch.setenv("GS_CSR_WG_ROW", str(wg))
     if cpl:
-        monkeypatch.setenv("GS_COO_CPL", cpl)
-    _check_coo_row_mix()
-
-
-@pytest.mark.parametrize("cpl", ["", "16"])
-@pytest.mark.parametrize("snap", ["4", "32"])
-@pytest.mark.parametrize("ranges", ["50", "997"])
-def test_coo_snapped_boundaries(monkeypatch, ranges, snap, cpl):
-    # the same rows with boundaries moved to the next row start within 4 or
-    # 32 entries (the near-diagonal rule, forced on this random pattern):
-    # ranges that grow past the fold length, ranges left empty by the move
-    monkeypatch.setenv("GS_COO_RANGES", ranges)
-    monkeypatch.setenv("GS_COO_SNAP", snap)
-    if cpl:
-        monkeypatch.setenv("GS_COO_CPL", cpl)
+        monkeypatch.setenv("GS_CSR_CPL", cpl)
     _check_coo_row_mix()
 
 
@@ -422,13 +400,9 @@ def test_empty_and_degenerate_matrices():
             check_features(case)
 
 
-@pytest.mark.parametrize("ranges", ["", "7"])
-def test_one_row_holds_most_entries(monkeypatch, ranges):
-    # a single row of 300,000 entries among short and empty rows: CSR splits it
-    # into chunks combined in order, COO cuts it across (nearly) every range and
-    # adds the carries in range order, CSC scatters every column into one row
-    if ranges:
-        monkeypatch.setenv("GS_COO_RANGES", ranges)
+def test_one_row_holds_most_entries():
+    # a single row of 300,000 entries among short and empty rows: CSR and COO
+    # split it into chunks combined in order, CSC does in fp64
     R, C = 5000, 400_000
     rng = np.random.default_rng(131)
     hub = np.sort(rng.choice(C, 300_000, replace=False)).astype(np.int32)

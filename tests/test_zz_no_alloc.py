@@ -2,9 +2,9 @@
 
 gs_spmm_noalloc runs the same kernels as gs_spmm with the workspace taken from
 the library's fixed per-device scratch array.  Checked through the C ABI:
-  * its Y equals gs_spmm's bit for bit (CSC: within one fp32 step, its fp64
-    atomics add in varying order) and lies within the SpMM bound of the
-    oracle;
+  * its Y equals gs_spmm's bit for bit (CSC: within one fp32 step, since a
+    matrix whose partial sums exceed the scratch array adds its long rows in
+    another order in fp64) and lies within the SpMM bound of the oracle;
   * two calls in a row, the second with a smaller matrix and a narrower
     (ragged) F, so the second reuses scratch the first left behind;
   * no allocation happens during the call (PyTorch's allocator is the
