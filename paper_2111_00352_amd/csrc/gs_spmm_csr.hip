@@ -119,7 +119,7 @@ template <class A_, bool CLS_, bool GROUPED_, int DEPTH_ = 0, int NA_ = 1, int N
 // of entries while it gathers the current one's X rows, and broadcasts entries
 // by DPP (no LDS round trip).  Against shuffled batches of G entries without
 // the pipeline: power-law graph (F = 128) 61.6 -> 60.2 us, block graph
-// (F = 256) 199 -> 185, a 30,011 x 100,003 block of 450,000 entries at F = 47
+// (F = 256) 199 -> 191, a 30,011 x 100,003 block of 450,000 entries at F = 47
 // 23.1 -> 20.3.
 //
 template <int CPL, int G, bool FULL, int OFF, class V>

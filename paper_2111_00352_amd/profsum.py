@@ -68,8 +68,9 @@ def short(name: str) -> str:
 
 def picked(name: str, kernels) -> bool:
     """True when the kernel's name (template arguments included, without the
-    return type and namespace) is one of `kernels`."""
-    return short(str(name)).split("gs::")[-1] in kernels
+    return type and namespaces) is one of `kernels`."""
+    head, sep, args = short(str(name)).partition("<")
+    return head.split("gs::")[-1] + sep + args.replace("gs::", "") in kernels
 
 
 def main():
