@@ -7,9 +7,10 @@ Usage:
 --trace: a ``--kernel-trace --stats`` run; per-kernel dispatch count and
 average / median / min duration.
 --fetch / --write: ``--pmc FETCH_SIZE`` and ``--pmc WRITE_SIZE`` runs; the
-counters (KiB per dispatch) are averaged per kernel and scaled by what the
-same counter reads for the calibration kernel, a plain elementwise copy
-(``neg``) of --calib-bytes read and written.  With --traffic-json the scaled
+counters (KiB per dispatch, the median of a kernel's dispatches: the library's
+start-up runs the same kernels once or twice on a tiny matrix) are scaled by
+what the same counter reads for the calibration kernel, a plain elementwise
+copy (``neg``) of --calib-bytes read and written.  With --traffic-json the scaled
 bytes per dispatch of the kernels matching --kernel are written out together
 with a hash of the HIP sources they were measured on.
 """
@@ -61,6 +62,10 @@ def counters(path):
     return agg
 
 
+def median(v) -> float:
+    return sorted(v)[len(v) // 2]
+
+
 def short(name: str) -> str:
     name = name.replace("(anonymous namespace)::", "")
     return name.split("(")[0] if "(" in name else name
@@ -83,7 +88,7 @@ def main():
     ap.add_argument("--calib-bytes", type=float, default=256 * 2**20)
     ap.add_argument("--traffic-json")
     ap.add_argument("--counters", nargs="*", default=[],
-                    help="further --pmc runs: every counter averaged per dispatch of the --kernel kernels")
+                    help="further --pmc runs: every counter, median over the dispatches of the --kernel kernels")
     ap.add_argument("--top", type=int, default=25, help="kernels listed from the trace (by total time)")
     ap.add_argument("--cmd", default="")
     a = ap.parse_args()
@@ -103,12 +108,12 @@ def main():
         c = counters(path)
         calib = [sum(v) / len(v) for (kn, cn), v in c.items() if cn == cname and "neg" in str(kn)]
         factor = (a.calib_bytes / (max(calib) * 1024.0)) if calib else None
-        print(f"\n{cname} (KiB per dispatch, averaged); calibration copy reads {calib and max(calib):.0f} KiB "
+        print(f"\n{cname} (KiB per dispatch, median); calibration copy reads {calib and max(calib):.0f} KiB "
               f"for {a.calib_bytes / 1024:.0f} KiB moved -> factor {factor if factor else float('nan'):.4f}")
         for (kn, cn), v in sorted(c.items(), key=lambda kv: -sum(kv[1])):
             if cn != cname:
                 continue
-            avg = sum(v) / len(v)
+            avg = median(v)
             print(f"  {len(v):5d}x {avg:14.1f} KiB  {short(str(kn))}")
             if picked(kn, kernels) and factor:
                 out[label] = out.get(label, 0.0) + avg * 1024.0 * factor
@@ -116,11 +121,11 @@ def main():
             out[f"{label}_factor"] = factor
     for path in a.counters:
         c = counters(path)
-        print(f"\ncounters of *{a.kernel}* kernels (average per dispatch): {os.path.basename(os.path.dirname(path))}")
+        print(f"\ncounters of *{a.kernel}* kernels (median per dispatch): {os.path.basename(os.path.dirname(path))}")
         per = collections.defaultdict(dict)
         for (kn, cn), v in sorted(c.items()):
             if picked(kn, kernels):
-                per[short(str(kn))][cn] = sum(v) / len(v)
+                per[short(str(kn))][cn] = median(v)
         for kn, cs in per.items():
             line = "  ".join(f"{cn}={val:.4g}" for cn, val in sorted(cs.items()))
             hit, miss = cs.get("TCC_HIT_sum"), cs.get("TCC_MISS_sum")
