@@ -192,3 +192,26 @@ def test_features_at_most_entries(most_entries):
     exp = _band_aggregates(NZ_ROWS, NZ_OFFS)
     exp["nnz"] = (1 << 31) - 329
     assert {k: got[k] for k in exp} == exp
+
+
+@pytest.mark.parametrize("fmt,F", [("csr", 47), ("csr", 64), ("coo", 128), ("csr", 257), ("csr", 18)])
+def test_strides_past_4_gib_at_odd_widths(fmt, F):
+    # X rows 2^25 floats apart (64-bit gather offsets) with rows of 0..30
+    # entries: chains of four, entry batches and tails of the row kernel there
+    C, ld = 41, 1 << 25
+    rng = np.random.default_rng(F)
+    rows, cols = [], []
+    for r in range(300):
+        n = int(rng.integers(0, 31))
+        rows.append(np.full(n, r, np.int32))
+        cols.append(np.sort(rng.choice(C, n, replace=False)).astype(np.int32))
+    row, col = np.concatenate(rows), np.concatenate(cols)
+    val = rng.uniform(0.5, 1.5, row.size).astype(np.float32)
+    X = graphgen.features_x(C, F, F + 1, "normal")
+    flat = torch.empty((C - 1) * ld + F, device="cuda")
+    Xd = flat.as_strided((C, F), (ld, 1))
+    Xd.copy_(torch.from_numpy(X))
+    m = gs.build_format(*(torch.from_numpy(a).cuda() for a in (row, col, val)), (300, C), fmt)
+    Yref, M = oracle.spmm(300, oracle.csr(300, row), col, val, X)
+    ok, worst = oracle.check_spmm(m.spmm(Xd).cpu().numpy(), Yref, M)
+    assert ok, worst

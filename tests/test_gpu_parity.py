@@ -853,6 +853,30 @@ def test_csr_reference_classes(monkeypatch, hot_kb, sort):
     check_spmm(case, case.build("csr"), graphgen.features_x(C, 64, 28, "normal"))
 
 
+@pytest.mark.parametrize("fmt,F,off", [("csr", 47, 0), ("csr", 64, 1), ("csr", 131, 0), ("csr", 7, 2), ("coo", 64, 0),
+                                       ("coo", 128, 0), ("coo", 256, 0), ("coo", 130, 0)])
+@pytest.mark.parametrize("group_min", ["100000", "100"])
+def test_reference_classes_in_chains_of_four(monkeypatch, fmt, F, off, group_min):
+    # gathers by class and the group tier where rows are summed in chains of
+    # four: within the bound of the oracle, and bit for bit the sums of plain
+    # gathers, which keep other numbers of X rows in flight
+    monkeypatch.setenv("GS_CSR_SORT", "2")
+    monkeypatch.setenv("GS_CSR_GROUP_MIN", group_min)
+    case = _uniform_long_rows(500, 3000, 0, 300, 710 + F, hubs=(3, 499))
+    X = graphgen.features_x(case.C, F, 711, "normal")
+    Xd = torch.zeros((case.C, F + off), device=DEV)
+    Xd[:, off:] = _dev(X)
+    ys = []
+    for classes in ("off", "on"):
+        monkeypatch.setenv("GS_CSR_HOTCOLD", classes)
+        monkeypatch.setenv("GS_CSR_HOT_KB", "16")
+        ys.append(_host(case.build(fmt).spmm(Xd[:, off:])))
+    Yref, M = oracle.spmm(case.R, case.rp, case.ccol, case.cval, X)
+    ok, worst = oracle.check_spmm(ys[0], Yref, M)
+    assert ok, worst
+    assert (_bits(ys[0]) == _bits(ys[1])).all()
+
+
 @pytest.mark.parametrize("T,h", [("32", "0"), ("64", "1"), ("256", "1"), ("96", "0")])
 def test_csr_lds_window_tiles(monkeypatch, T, h):
     # row tiles with their X window staged in LDS: communities of consecutive
