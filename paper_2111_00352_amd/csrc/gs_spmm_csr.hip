@@ -127,7 +127,7 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     int64_t n_long, const int32_t *__restrict__ long_rows, const int32_t *__restrict__ rp, int chunk, int64_t n_items,
     const int4 *__restrict__ items, const int32_t *__restrict__ col, const float *__restrict__ val, int zlast,
     const float *__restrict__ X, int64_t ldx, float *__restrict__ Y, int64_t ldy, int64_t F,
-    typename V::A *__restrict__ work, int hot_cls)
+    typename V::A *__restrict__ work, int hot_cls, int by_xcd)
 {
     typedef typename V::A A;
     constexpr bool CLS = V::CLS, GROUPED = V::GROUPED;
@@ -142,11 +142,14 @@ __global__ __launch_bounds__(kBlock) void k_csr_rows(
     const int g = threadIdx.x / G, lane = threadIdx.x % G;
     const Quads<NQ, G, FULL> cols((int64_t)blockIdx.y * (G * CPL), lane, F);
 
-    // long rows first, a workgroup each.  (Tiles in launch order: giving each
+    // long rows first, a workgroup each.  Tiles in launch order: giving each
     // XCD neighbouring rows, so that they share X rows in its L2, made a mesh
     // of 512 x 512 slower (F = 128 77 against 59 us) and 140,001 rows of 20
-    // entries (F = 128 168 against 131).)
+    // entries (F = 128 168 against 131).  Only fp64 tiles of four rows, less
+    // than a community, gain by it (by_xcd; block graph at F = 256 264 -> 248).
     int64_t t = blockIdx.x;
+    if constexpr (G == 64 && sizeof(A) == 8)
+        if (by_xcd) t = xcd_tile(blockIdx.x, gridDim.x);
     for (; t < n_long; t += gridDim.x) {
         const int64_t row = long_rows[t];
         const int64_t s = rp[row], e = rp[row + 1];
@@ -1101,7 +1104,7 @@ bool spmm_csr_vec4(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
                                          m.csr_chunk, n_group_items, m.csr_items.as<int4>() + m.n_medium_chunks,
                                          cols ? cols : m.row_ptr.as<int32_t>(),
                                          m.Z ? m.val.as<float>() : m.row_ptr.as<float>(),
-                                         (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls);
+                                         (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, hot_cls, 0);
             GS_HIP(hipGetLastError());
         };
         auto pick = [&](auto na_t) {
@@ -1218,7 +1221,8 @@ void spmm_rows_f64(gs_matrix_ &m, const float *X, int64_t ldx, float *Y, int64_t
         if (!tiles) return;
         dim3 grid(rows_grid((const void *)fn, 0, tiles, slices, m.csr_sorted ? 4 : 8), (unsigned)slices);
         fn<<<grid, kBlock, 0, s>>>(n_wg, m.long_rows.as<int32_t>(), rp, m.csr_chunk, m.n_items - skip, items + skip, col,
-                                   val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0);
+                                   val, (int)std::max<int64_t>(m.Z - 1, 0), X, ldx, Y, ldy, F, work, 0,
+                                   !m.csr_sorted && m.n_long_rows == 0);
         GS_HIP(hipGetLastError());
         if (n_huge) {
             dim3 g2((unsigned)ceil_div(n_huge, GPB), (unsigned)slices);
