@@ -22,9 +22,15 @@ namespace {
 
 constexpr int kBlock = 256;
 constexpr int kRows = 32;  // rows of H and G per stage
-// Rows after which the running sums of a workgroup join their totals, so that
-// no chain grows with n (512 x 512 leaves a workgroup n / 32 rows).
-constexpr int kFoldRows = 1024;
+// Workgroups of more than kChainRows rows add their running sums into totals
+// every kFoldRows rows, so that no chain grows with n (512 x 512 leaves a
+// workgroup n / 32 rows).  The totals are a second set of registers, which costs
+// the shorter ones more than it gives: n = 2,000,000, 128 x 128 (3,936 rows) in
+// one chain 631 us with an error of 5.0e-8 (2-norm, operands in [0, 1)), folded
+// 760 and 3.5e-8; 512 x 512 (62,528 rows) 8.5 ms and 1.0e-6, folded 11.4 ms and
+// 3.5e-8.  PyTorch's batched product over 2,048-row chunks: 1,830 us and 6.5e-8,
+// 11.7 ms and 6.6e-8.  Adding into the partial in memory instead took 15.0 ms.
+constexpr int kFoldRows = 1024, kChainRows = 4096;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // Rows [r0, r0 + kRows) x columns [c0, c0 + W) of M (n x c, leading dimension
@@ -65,7 +71,7 @@ template <int W> __device__ __forceinline__ void store_stage(float *lds, const f
 // MT x NT (of the a x b product), four waves WM x WN x KS: a wave owns
 // MT / WM x NT / WN of the tile and every KS-th pair of rows, and writes its
 // sums as partial (x * KS + ks).  The next stage's rows are loaded while the
-// current one's are multiplied.  FOLD: per exceeds kFoldRows.
+// current one's are multiplied.  FOLD: per exceeds kChainRows.
 template <int MT, int NT, int WM, int WN, bool FOLD>
 __global__ __launch_bounds__(kBlock) void k_tn_partial(const float *__restrict__ H, int64_t ldh,
                                                        const float *__restrict__ G, int64_t ldg, int64_t n, int a, int b,
@@ -231,7 +237,7 @@ int gs_weight_grad(const float *H, int64_t ldh, const float *G, int64_t ldg, int
         };
         auto tiled = [&](auto mt, auto nt, auto wm, auto wn) {
             if (p.mt != decltype(mt)::value || p.nt != decltype(nt)::value) return;
-            if (p.per > kFoldRows)
+            if (p.per > kChainRows)
                 go(mt, nt, wm, wn, std::true_type{});
             else
                 go(mt, nt, wm, wn, std::false_type{});

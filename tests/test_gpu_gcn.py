@@ -218,7 +218,7 @@ def test_weight_grad_leaves_recorded_products_to_pytorch():
 
 @pytest.mark.parametrize("a,b", [(512, 512), (512, 480), (32, 64), (100, 128)])
 def test_weight_grad_chains_do_not_grow_with_n(a, b):
-    # a workgroup's sums are folded every 1,024 rows.  All products are
+    # workgroups of more than 4,096 rows, as here, fold their sums every 1,024.  All products are
     # 1 + 2^-12: a sum of 1,024 is exact, while one chain loses the 2^-12 of
     # every product once it is past 8,192 (at 16 tiles it would hold 18,750 rows,
     # an error of 1.4e-4).  Depth: at most 1,024 rows and 19 folds with 32
